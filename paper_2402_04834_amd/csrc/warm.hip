@@ -199,18 +199,336 @@ __global__ __launch_bounds__(256) void features_kernel(const uint8_t* __restrict
   }
 }
 
-// Implicit-GEMM 3x3 convolution (zero padding) on the matrix cores, FP32 products and sums. The operand
-// gathered from an activation is never materialised: a 64 x 16 tile is read straight from the shifted
-// sites into LDS. Activations are [row = job * L^2 + r * L + c][channel]; tap t = 3 dy + dx reads site
+// Implicit-GEMM 3x3 convolutions (zero padding) on the matrix cores, FP32 products and sums
+// (v_mfma_f32_16x16x4f32). Activations are [row = job * L^2 + r * L + c][channel]; tap t = 3 dy + dx reads site
 // (r + dy - 1, c + dx - 1). Three uses:
-//   G_FWD  Y[row][co] = act(sum_{t,ci} X[row + t][ci] W[t cin + ci][co] + b[co])      (M rows, N cout, K 9 cin)
-//   G_DX   dX[row][ci] = mask * sum_{t,co} dY[row - t][co] W[t cin + ci][co]           (M rows, N cin, K 9 cout)
+//   G_FWD  Y[row][co] = act(sum_{t,ci} X[row + t][ci] W[t cin + ci][co] + b[co])      (N cout, K 9 cin)
+//   G_DX   dX[row][ci] = mask * sum_{t,co} dY[row - t][co] W[t cin + ci][co]           (N cin, K 9 cout)
 //          (the adjoint of the gather; mask = ReLU'(the layer's input activation) when EPI = 1)
-//   G_DW   dW[t cin + ci][co] += sum_rows X[row + t][ci] dY[row][co]                  (M 9 cin, N cout, K rows)
-//          (K split over grid.z, atomically accumulated into dW, which the caller has zeroed)
-// 64 x 64 output tile per workgroup of four waves (each 32 x 32 = 2 x 2 MFMA 16x16x4 blocks), K in
-// chunks of 16. grid.x = M tiles, grid.y = N tiles.
-enum { G_FWD = 0, G_DX = 1, G_DW = 2 };
+//   conv_dw  dW[t cin + ci][co] = sum_rows X[row + t][ci] dY[row][co]                  (M 9 cin, N cout, K rows)
+enum { G_FWD = 0, G_DX = 1 };
+
+// x / n for x < 2^31 by one multiply: m = ceil(2^32 / n) is at most n - 1 over 2^32 / n, so the quotient is at
+// most one too large, which the remainder corrects
+struct Divide {
+  unsigned n, m;
+};
+inline Divide divide_by(unsigned n) { return Divide{n, (unsigned)(((1ull << 32) + n - 1) / n)}; }
+__device__ __forceinline__ unsigned quotient(unsigned x, Divide d, unsigned& rem) {
+  unsigned q = d.n == 1 ? x : __umulhi(x, d.m);
+  rem = x - q * d.n;
+  if ((int)rem < 0) {
+    --q;
+    rem += d.n;
+  }
+  return q;
+}
+// where a row sits on its grid: bit 0 first grid row, 1 last, 2 first column, 3 last column
+__device__ __forceinline__ unsigned edge_bits(unsigned row, Divide byL, Divide byLL) {
+  unsigned site, c;
+  (void)quotient(row, byLL, site);
+  const unsigned r = quotient(site, byL, c);
+  return (r == 0 ? 1u : 0u) | (r == byL.n - 1 ? 2u : 0u) | (c == 0 ? 4u : 0u) | (c == byL.n - 1 ? 8u : 0u);
+}
+// edge bits with which the neighbour (dr, dc) of a row is outside the grid
+__device__ __forceinline__ unsigned outside_bits(int dr, int dc) {
+  return (dr < 0 ? 1u : 0u) | (dr > 0 ? 2u : 0u) | (dc < 0 ? 4u : 0u) | (dc > 0 ? 8u : 0u);
+}
+
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));   // 16 bytes staged through registers
+// four floats at any float's address: the parameters and the workspace are the caller's, 4-byte aligned
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+
+// Forward and data gradient. What bounds it is the FP32 matrix rate; the gathered operand is read nine times but
+// from L2 (8 bytes per clock and CU with these tiles). A workgroup of four waves computes 128 rows x all NT output
+// channels (2 x 2 waves of 64 x NT/2), so that one 16-deep stage holds 64 (NT = 128) MFMAs of 32 cycles per
+// wave against 8 KB + NT * 64 bytes of loads; the stage after next is in flight in registers while a stage is
+// multiplied out of one of two LDS buffers, one barrier per stage. Both LDS tiles are k-contiguous with a stride of
+// 20 floats (16 rows cover all 64 banks), so that a lane takes its four k of a stage with one 16-byte read: MFMA
+// step ks multiplies k = 4 (lane / 16) + ks, any order of k being as good. The gather is a raw buffer load whose
+// offset lies past the buffer for taps that leave the grid (reads zeros, no branch); the buffer starts at the
+// tile's first neighbour row, so offsets stay below 2^31 whatever the batch. The weights are the MFMA's first operand:
+// a lane ends with four consecutive output channels of a row, one 16-byte store.
+// Measured at d = 17, 16 syndromes (69,696 rows): 128 -> 96 forward 200 us (77 TFLOP/s, half of the FP32 matrix rate),
+// its data gradient 185 us, 128 -> 64 data gradient 133 us, 64 -> 128 forward 128 us. The 64 x 64 tiles with 4-byte
+// gathers and 64-bit index divisions per element before took 542, about 620, 345 and 265 us.
+template <int MODE, int CS, int NT, int EPI>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void conv_f32(
+    int L, int64_t rows, Divide byL, Divide byLL, const float* __restrict__ X, const float* __restrict__ W,
+    float* __restrict__ Y, const float* __restrict__ aux) {
+  constexpr int KD = 9 * CS, NS = (KD + 15) / 16;              // K, stages of 16
+  constexpr int MT = 128, RS = 20, NJ = NT / 32;               // rows per tile, LDS row stride, 16-channel blocks per wave
+  constexpr int UB = (NT * 4 + 255) / 256;                     // 16-byte weight chunks per thread and stage
+  constexpr bool WIDE = CS % 16 == 0;                          // a stage lies inside one tap
+  static_assert(NT % 32 == 0 && NT <= 128 && (WIDE || MODE == G_FWD), "tile shape");
+  __shared__ __align__(16) float As[2][MT * RS];
+  __shared__ __align__(16) float Bs[2][NT * RS];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  // consecutive tiles on one XCD (workgroups are dealt to the eight XCDs in turn): they share neighbour rows
+  const unsigned per = gridDim.x / 8, bid = blockIdx.x;
+  const unsigned tile = bid < 8 * per ? (bid % 8) * per + bid / 8 : bid;
+  const int64_t m0 = (int64_t)tile * MT;
+  const int64_t g0 = m0 > L + 1 ? m0 - L - 1 : 0, g1 = min(rows, m0 + MT + L + 1);
+  const unsigned xbytes = (unsigned)(g1 - g0) * (CS * 4u);
+  const __amdgpu_buffer_rsrc_t xr =
+      __builtin_amdgcn_make_buffer_rsrc((void*)(X + g0 * CS), (short)0, (int)xbytes, 0x00020000);
+  const int kq = tid & 3;
+  unsigned base[2], edge[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int64_t row = m0 + (tid >> 2) + 64 * u;
+    base[u] = (unsigned)(row - g0) * (CS * 4u);
+    edge[u] = row < rows ? edge_bits((unsigned)(row % ((int64_t)byLL.n << 8)), byL, byLL) : 16u;
+  }
+  constexpr int SIGN = MODE == G_FWD ? 1 : -1;
+  u32x4 ra[2];
+  f4 rb[UB];
+  auto load = [&](const int s) {
+    if constexpr (WIDE) {
+      const int t = (16 * s) / CS, ch = (16 * s) % CS + 4 * kq;
+      const int dr = SIGN * (t / 3 - 1), dc = SIGN * (t % 3 - 1);
+      const unsigned out = 16u | outside_bits(dr, dc);
+      const int delta = (dr * L + dc) * (CS * 4);
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const unsigned o = (edge[u] & out) ? xbytes : base[u] + (unsigned)(delta + 4 * ch);
+        ra[u] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(xr, (int)o, 0, 0));
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int k = 16 * s + 4 * kq + j, t = k / CS, ch = k - t * CS;
+        const int dr = t / 3 - 1, dc = t % 3 - 1;
+        const unsigned out = 16u | outside_bits(dr, dc);
+        const int delta = ((dr * L + dc) * CS + ch) * 4;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const unsigned o = (k >= KD || (edge[u] & out)) ? xbytes : base[u] + (unsigned)delta;
+          ra[u][j] = __builtin_amdgcn_raw_buffer_load_b32(xr, (int)o, 0, 0);
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < UB; ++u) {
+      const int q = min(tid + 256 * u, NT * 4 - 1);   // past the last chunk: that one again, not stored
+      if constexpr (MODE == G_FWD) {
+        const int n = q % NT, k = 16 * s + 4 * (q / NT);
+        float v[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = (WIDE || k + j < KD) ? W[(size_t)(k + j) * NT + n] : 0.0f;
+        rb[u] = f4{v[0], v[1], v[2], v[3]};
+      } else {
+        const int t = (16 * s) / CS, ch = (16 * s) % CS + 4 * (q & 3);
+        rb[u] = *(const f4u*)(W + ((size_t)t * NT + (q >> 2)) * CS + ch);
+      }
+    }
+  };
+  auto store = [&](const int buf) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) *(u32x4*)&As[buf][((tid >> 2) + 64 * u) * RS + 4 * kq] = ra[u];
+#pragma unroll
+    for (int u = 0; u < UB; ++u) {
+      const int q = tid + 256 * u;
+      const int n = MODE == G_FWD ? q % NT : q >> 2, k4 = MODE == G_FWD ? q / NT : q & 3;
+      if ((NT * 4) % 256 == 0 || q < NT * 4) *(f4*)&Bs[buf][n * RS + 4 * k4] = rb[u];
+    }
+  };
+  f4 acc[4][NJ];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) acc[i][j] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+  const int wm = (w >> 1) * 64, wn = (w & 1) * (NT / 2), fr = lane & 15, fc = lane >> 4;
+  load(0);
+  store(0);
+  if (NS > 1) load(1);
+  __syncthreads();
+#pragma unroll 1
+  for (int s = 0; s < NS; ++s) {
+    const int cur = s & 1;
+    f4 a[4], b[NJ];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a[i] = *(const f4*)&As[cur][(wm + 16 * i + fr) * RS + 4 * fc];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) b[j] = *(const f4*)&Bs[cur][(wn + 16 * j + fr) * RS + 4 * fc];
+    if (s + 1 < NS) store(cur ^ 1);
+    if (s + 2 < NS) load(s + 2);
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[j][ks], a[i][ks], acc[i][j], 0, 0, 0);
+    __syncthreads();
+  }
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) {
+    const int col = wn + 16 * j + 4 * fc;
+    f4 bias = f4{0.0f, 0.0f, 0.0f, 0.0f};
+    if (MODE == G_FWD) bias = *(const f4u*)(aux + col);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int64_t row = m0 + wm + 16 * i + fr;
+      if (row >= rows) continue;
+      f4 v = acc[i][j];
+      if (MODE == G_FWD) {
+        v += bias;
+        if (EPI)
+          for (int r = 0; r < 4; ++r) v[r] = fmaxf(v[r], 0.0f);
+      } else if (EPI) {
+        const f4 x = *(const f4u*)(aux + row * NT + col);
+        for (int r = 0; r < 4; ++r) v[r] = x[r] > 0.0f ? v[r] : 0.0f;
+      }
+      *(f4u*)(Y + row * NT + col) = v;
+    }
+  }
+}
+
+// Weight gradient, K = rows split over grid.y: workgroup (x, y) sums the rows [y kchunk, (y + 1) kchunk) into the
+// 128 rows m = t CIN + ci from 128 x of its partial matrix P[y], workgroup (0, y) the column sums of dY (the bias
+// gradient) into its row 9 CIN; dw_reduce_kernel adds the partials in order (a
+// fixed order: the gradients of two calls are equal). Bound by the FP32 matrix rate like conv_f32, with the same wave
+// tiles, 16-row stages and two LDS buffers. The LDS tiles keep the activations' layout [row][channel]: MFMA
+// operands are 4-byte reads of 16 consecutive channels at 4 rows, a row stride of 16 modulo 64 floats putting the 64
+// lanes on distinct banks. The partials replace atomic adds of every split into the one gradient. Measured at d = 17,
+// 16 syndromes: 170 us (1152 x 96), 129 us (576 x 128) and 32 us (99 x 64), the reductions 8 us each; before, 399 us on
+// average and 98 us for each bias gradient.
+template <int CIN, int NT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void conv_dw(
+    int L, int64_t rows, Divide byL, Divide byLL, int64_t kchunk, const float* __restrict__ X,
+    const float* __restrict__ dY, float* __restrict__ P) {
+  constexpr int M = 9 * CIN, MT = 128, SA = 144, SB = NT > 80 ? 144 : 80, NJ = NT / 32;
+  constexpr int UB = (NT * 4 + 255) / 256;
+  constexpr bool WIDE = CIN % 4 == 0;
+  __shared__ __align__(16) float As[2][16 * SA];
+  __shared__ __align__(16) float Bs[2][16 * SB];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int m0 = blockIdx.x * MT;
+  const int64_t kb = (int64_t)blockIdx.y * kchunk, ke = min(rows, kb + kchunk);
+  const int64_t g0 = kb > L + 1 ? kb - L - 1 : 0, g1 = min(rows, ke + L + 1);
+  const unsigned xbytes = (unsigned)(g1 - g0) * (CIN * 4u), ybytes = (unsigned)(ke - kb) * (NT * 4u);
+  const __amdgpu_buffer_rsrc_t xr =
+      __builtin_amdgcn_make_buffer_rsrc((void*)(X + g0 * CIN), (short)0, (int)xbytes, 0x00020000);
+  const __amdgpu_buffer_rsrc_t yr =
+      __builtin_amdgcn_make_buffer_rsrc((void*)(dY + kb * NT), (short)0, (int)ybytes, 0x00020000);
+  // this thread stages rows k0 + tid / 32 and + 8, channels m .. m + 3 of the gathered operand
+  constexpr int NM = WIDE ? 1 : 4;
+  int delta[NM];
+  unsigned out[NM];
+#pragma unroll
+  for (int j = 0; j < NM; ++j) {
+    const int m = m0 + 4 * (tid & 31) + j, t = m / CIN, ci = m - t * CIN, dr = t / 3 - 1, dc = t % 3 - 1;
+    delta[j] = ((dr * L + dc) * CIN + ci) * 4;
+    out[j] = 16u | (m < M ? outside_bits(dr, dc) : 32u);
+  }
+  const int n0 = (int)(kb - g0), nk = (int)(ke - kb);
+  const unsigned row0 = (unsigned)(kb % byLL.n);   // the chunk's first row on its grid
+  u32x4 ra[2], rb[UB];
+  f4 bsum[UB];
+#pragma unroll
+  for (int u = 0; u < UB; ++u) bsum[u] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+  auto load = [&](const int k0) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int k = k0 + (tid >> 5) + 8 * u;
+      const unsigned e = (k < nk ? edge_bits(row0 + (unsigned)k, byL, byLL) : 16u) | 32u;
+      const unsigned at = (unsigned)(n0 + k) * (CIN * 4u);
+      if constexpr (WIDE) {
+        const unsigned o = (e & out[0]) ? xbytes : at + (unsigned)delta[0];
+        ra[u] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(xr, (int)o, 0, 0));
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const unsigned o = (e & out[j]) ? xbytes : at + (unsigned)delta[j];
+          ra[u][j] = __builtin_amdgcn_raw_buffer_load_b32(xr, (int)o, 0, 0);
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < UB; ++u) {
+      const int q = tid + 256 * u, kk = q / (NT / 4), c4 = q - kk * (NT / 4);
+      rb[u] = __builtin_bit_cast(
+          u32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                     yr, (int)((kk < 16 && k0 + kk < nk) ? (unsigned)(k0 + kk) * (NT * 4u) + 16u * c4 : ybytes), 0, 0));
+    }
+  };
+  auto store = [&](const int buf) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) *(u32x4*)&As[buf][((tid >> 5) + 8 * u) * SA + 4 * (tid & 31)] = ra[u];
+#pragma unroll
+    for (int u = 0; u < UB; ++u) {
+      const int q = tid + 256 * u, kk = q / (NT / 4), c4 = q - kk * (NT / 4);
+      if ((NT * 4) % 256 == 0 || kk < 16) *(u32x4*)&Bs[buf][kk * SB + 4 * c4] = rb[u];
+      bsum[u] += __builtin_bit_cast(f4, rb[u]);
+    }
+  };
+  f4 acc[4][NJ];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) acc[i][j] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+  const int wm = (w >> 1) * 64, wn = (w & 1) * (NT / 2), fr = lane & 15, fc = lane >> 4;
+  load(0);
+  store(0);
+  load(16);   // (rows past the chunk read zeros)
+  __syncthreads();
+#pragma unroll 1
+  for (int k0 = 0; k0 < nk; k0 += 16) {
+    const int cur = (k0 >> 4) & 1;
+    float a[4][4], b[4][NJ];
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) a[ks][i] = As[cur][(4 * ks + fc) * SA + wm + 16 * i + fr];
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) b[ks][j] = Bs[cur][(4 * ks + fc) * SB + wn + 16 * j + fr];
+    }
+    store(cur ^ 1);
+    load(k0 + 32);
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[ks][j], a[ks][i], acc[i][j], 0, 0, 0);
+    __syncthreads();
+  }
+  float* Pz = P + (size_t)blockIdx.y * (M + 1) * NT;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int m = m0 + wm + 16 * i + fr;
+    if (m >= M) continue;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) *(f4u*)(Pz + (size_t)m * NT + wn + 16 * j + 4 * fc) = acc[i][j];
+  }
+  if (blockIdx.x == 0) {   // row M: the bias gradient, the column sums of dY
+    float* red = &Bs[0][0];   // [16][NT], the stages are done
+#pragma unroll
+    for (int u = 0; u < UB; ++u) {
+      const int q = tid + 256 * u;
+      if ((NT * 4) % 256 == 0 || q < NT * 4) *(f4*)&red[4 * q] = bsum[u];
+    }
+    __syncthreads();
+    if (tid < NT) {
+      float v = 0.0f;
+      for (int kk = 0; kk < 16; ++kk) v += red[kk * NT + tid];
+      Pz[(size_t)M * NT + tid] = v;
+    }
+  }
+}
+
+// dW[i] = sum over the splits of P[z][i], in the order of z
+__global__ __launch_bounds__(256) void dw_reduce_kernel(const float* __restrict__ P, int n, int splits,
+                                                        float* __restrict__ dW) {
+  for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) {
+    float s = 0.0f;
+#pragma unroll 8
+    for (int z = 0; z < splits; ++z) s += P[(size_t)z * n + i];
+    dW[i] = s;
+  }
+}
 
 struct Site {
   int64_t base;
@@ -221,117 +539,10 @@ __device__ __forceinline__ Site site_of(int64_t row, int L) {
   const int s = (int)(row - job * LL);
   return Site{job * LL, s / L, s - (s / L) * L};
 }
-// row of the site shifted by tap (sign +1) or against it (sign -1); -1 outside the grid
-__device__ __forceinline__ int64_t shifted(const Site& s, int tap, int sign, int L) {
-  const int r = s.r + sign * (tap / 3 - 1), c = s.c + sign * (tap % 3 - 1);
-  return (r >= 0 && r < L && c >= 0 && c < L) ? s.base + (int64_t)r * L + c : -1;
-}
-
-template <int MODE, int EPI>
-__global__ __launch_bounds__(256) void conv_gemm(int L, int64_t rows, int cin, int cout, int64_t kchunk,
-                                                 const float* __restrict__ X, const float* __restrict__ Bm,
-                                                 float* __restrict__ C, const float* __restrict__ aux) {
-  __shared__ float As[64][17];
-  __shared__ float Bs[16][65];
-  const int64_t Mdim = (MODE == G_DW) ? 9 * cin : rows;
-  const int Ndim = (MODE == G_DX) ? cin : cout;
-  const int64_t Kdim = (MODE == G_FWD) ? 9 * cin : (MODE == G_DX) ? 9 * cout : rows;
-  const int Cs = (MODE == G_DX) ? cout : cin;     // channels of the gathered activation
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int64_t m0 = (int64_t)blockIdx.x * 64;
-  const int n0 = blockIdx.y * 64;
-  const int wm = (w >> 1) * 32, wn = (w & 1) * 32;
-  const int64_t kb = (int64_t)blockIdx.z * kchunk, ke = std::min(Kdim, kb + kchunk);
-  f4 acc[2][2];
-  for (int i = 0; i < 2; ++i)
-    for (int j = 0; j < 2; ++j) acc[i][j] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-  // the row this thread gathers for (fixed across K for G_FWD / G_DX)
-  Site arow{0, 0, 0};
-  const int amm = tid >> 2, akq = (tid & 3) * 4;
-  if (MODE != G_DW && m0 + amm < Mdim) arow = site_of(m0 + amm, L);
-  for (int64_t k0 = kb; k0 < ke; k0 += 16) {
-    if (MODE != G_DW) {
-      float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-      if (m0 + amm < Mdim)
-        for (int j = 0; j < 4; ++j) {
-          const int64_t k = k0 + akq + j;
-          if (k < ke) {
-            const int tap = (int)(k / Cs), ch = (int)(k - (int64_t)tap * Cs);
-            const int64_t src = shifted(arow, tap, MODE == G_FWD ? 1 : -1, L);
-            if (src >= 0) v[j] = X[src * Cs + ch];
-          }
-        }
-      for (int j = 0; j < 4; ++j) As[amm][akq + j] = v[j];
-    } else {
-      const int kk = tid >> 4, mq = (tid & 15) * 4;
-      const int64_t k = k0 + kk;
-      float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-      if (k < ke) {
-        const Site s = site_of(k, L);
-        for (int j = 0; j < 4; ++j) {
-          const int64_t m = m0 + mq + j;
-          if (m < Mdim) {
-            const int tap = (int)(m / cin), ch = (int)(m - (int64_t)tap * cin);
-            const int64_t src = shifted(s, tap, 1, L);
-            if (src >= 0) v[j] = X[src * cin + ch];
-          }
-        }
-      }
-      for (int j = 0; j < 4; ++j) As[mq + j][kk] = v[j];
-    }
-    if (MODE == G_DX) {
-      const int nn = tid >> 2, kq = (tid & 3) * 4;
-      const int n = n0 + nn;
-      for (int j = 0; j < 4; ++j) {
-        const int64_t k = k0 + kq + j;
-        float v = 0.0f;
-        if (n < Ndim && k < ke) {
-          const int tap = (int)(k / cout), co = (int)(k - (int64_t)tap * cout);
-          v = Bm[((int64_t)tap * cin + n) * cout + co];
-        }
-        Bs[kq + j][nn] = v;
-      }
-    } else {
-      const int kk = tid >> 4, nq = (tid & 15) * 4;
-      const int64_t k = k0 + kk;
-      for (int j = 0; j < 4; ++j) {
-        const int n = n0 + nq + j;
-        Bs[kk][nq + j] = (k < ke && n < Ndim) ? Bm[k * Ndim + n] : 0.0f;
-      }
-    }
-    __syncthreads();
-    for (int ks = 0; ks < 4; ++ks) {
-      const int kk = ks * 4 + (lane >> 4);
-      float a[2], b[2];
-      for (int i = 0; i < 2; ++i) a[i] = As[wm + i * 16 + (lane & 15)][kk];
-      for (int j = 0; j < 2; ++j) b[j] = Bs[kk][wn + j * 16 + (lane & 15)];
-      for (int i = 0; i < 2; ++i)
-        for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], acc[i][j], 0, 0, 0);
-    }
-    __syncthreads();
-  }
-  for (int i = 0; i < 2; ++i)
-    for (int j = 0; j < 2; ++j)
-      for (int r = 0; r < 4; ++r) {
-        const int64_t row = m0 + wm + i * 16 + 4 * (lane >> 4) + r;
-        const int col = n0 + wn + j * 16 + (lane & 15);
-        if (row >= Mdim || col >= Ndim) continue;
-        float v = acc[i][j][r];
-        float* dst = &C[row * Ndim + col];
-        if (MODE == G_FWD) {
-          v += aux[col];
-          *dst = EPI ? fmaxf(v, 0.0f) : v;
-        } else if (MODE == G_DX) {
-          *dst = (EPI && !(aux[row * Ndim + col] > 0.0f)) ? 0.0f : v;
-        } else {
-          atomicAdd(dst, v);
-        }
-      }
-}
 
 // Forward convolution in BF16 (inference): activations and weights stored as BF16, products and sums in FP32
 // on v_mfma_f32_16x16x32_bf16 (lane l supplies row l%16 of A and column l%16 of B with k = 8 (l/16) .. +7 of
-// a 32-step, and holds D rows 4 (l/16) .. +3 of column l%16). Implicit GEMM with the gather of conv_gemm<G_FWD>:
+// a 32-step, and holds D rows 4 (l/16) .. +3 of column l%16). Implicit GEMM with the gather of conv_f32<G_FWD>:
 // Y[row][co] = act(sum_{t, ci} X[row + t][ci] Wt[co][t CIN + ci] + b[co]). One workgroup of four waves computes
 // 128 rows x all NT output channels (2 x 2 waves of 64 x NT/2, i.e. 4 x NT/32 MFMA blocks each), so every
 // gathered activation tile is read once; K advances in steps of 32 through double-buffered, swizzled LDS tiles
@@ -341,7 +552,6 @@ __global__ __launch_bounds__(256) void conv_gemm(int L, int64_t rows, int cin, i
 // BF16 outputs leave through an LDS tile in 16-byte rows. This gather kernel serves grids too large for the
 // haloed tile of conv_halo_bf16 below (L > 49).
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));   // 16 bytes staged through registers
 
 // Wt[co][kp] (kp < kpad) = W[t cin + ci][co] for kp = t cs + ci with ci < cin, else 0 (BF16)
 __global__ void weights_t_kernel(const float* __restrict__ W, int cin, int cs, int cout, int kpad,
@@ -773,19 +983,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void c
   }
 }
 
-// db[c] = sum over rows of dY[row][c]; one workgroup per channel
-__global__ __launch_bounds__(256) void colsum_kernel(const float* __restrict__ dY, int64_t rows, int C,
-                                                     float* __restrict__ db) {
-  __shared__ float red[4];
-  const int c = blockIdx.x;
-  float acc = 0.0f;
-  for (int64_t r = threadIdx.x; r < rows; r += 256) acc += dY[r * C + c];
-  acc = wsum(acc);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
-  __syncthreads();
-  if (threadIdx.x == 0) db[c] = red[0] + red[1] + red[2] + red[3];
-}
-
 // Message head: one wavefront per (job, message). Leg table per message: [K, direction, a_0..a_5, b_0..b_5]
 // (sites r*L + c). TRAIN: loss, d(head outputs) into `dout` [job][M][32], and d(features) into dF (atomic);
 // otherwise the predicted unit message into msgs [job][M][64] (zero beyond 2^K).
@@ -990,60 +1187,60 @@ __global__ __launch_bounds__(64) void head_proj_kernel(const float* __restrict__
   msgs[(job * M + e) * 64 + lane] = m / nrm;
 }
 
-// Head weight gradients: workgroup (direction, slice of 64 input rows of Wu (3 slices) or Wp (6 slices));
-// thread = input row k; sums f_i[k] d(output) over every trained job and every message of the direction.
-__global__ __launch_bounds__(64) void head_grad_kernel(const float* __restrict__ F, const int32_t* __restrict__ legs,
-                                                       int M, int L, int64_t jobs, const uint8_t* __restrict__ use,
-                                                       const float* __restrict__ dout, float* __restrict__ grad) {
-  const int dir = blockIdx.x / 9, slice = blockIdx.x % 9, lane = threadIdx.x;
-  const bool pair = slice >= 3;
-  const int k = (pair ? slice - 3 : slice) * 64 + lane;
-  float* G = grad + OFF.head + (size_t)dir * HEAD;
-  float acc[4] = {0, 0, 0, 0};
-  float bacc[4] = {0, 0, 0, 0};
-  for (int64_t job = 0; job < jobs; ++job) {
+// Head weight gradients. A leg's features enter three blocks of its direction's weights -- Wu with the leg's unary
+// derivatives, the first half of Wp with the pair it opens, the second half with the pair it closes -- so
+// workgroup (direction, x) walks the messages of its jobs x, x + gridDim.x, ... once: thread k holds the rows k of the
+// three blocks (10 sums, in registers) for input k of [F(a_i), F(b_i)], loads that feature of all legs of a message
+// together (the loads' latency bounds this kernel) and adds its sums to the gradient at the end (atomically: the
+// gradient is zeroed before). The derivatives are uniform over the workgroup. Measured at d = 17, 16 syndromes: 76 us;
+// 36 wavefronts that each walked every job and message one after the other took 3268 us.
+__global__ __launch_bounds__(2 * C3) void head_grad_kernel(const float* __restrict__ F, const int32_t* __restrict__ legs,
+                                                           int M, int L, int64_t jobs, const uint8_t* __restrict__ use,
+                                                           const float* __restrict__ dout, float* __restrict__ grad) {
+  const int dir = blockIdx.y, k = threadIdx.x, ch = k < C3 ? k : k - C3, side = k < C3 ? 2 : 2 + MAXK;
+  float u[2] = {0, 0}, open[4] = {0, 0, 0, 0}, close[4] = {0, 0, 0, 0};
+  float bu[2] = {0, 0}, bp[4] = {0, 0, 0, 0};
+  for (int64_t job = blockIdx.x; job < jobs; job += gridDim.x) {
     if (!use[job]) continue;
-    const float* Fj = F + job * (int64_t)L * L * C3;
+    const float* Fj = F + job * (int64_t)L * L * C3 + ch;
     for (int e = 0; e < M; ++e) {
       const int32_t* lg = legs + e * 14;
       if (lg[1] != dir) continue;
       const int K = lg[0];
       const float* dO = dout + (job * M + e) * NOUT;
-      auto feat = [&](int i, int kk) -> float {
-        const int site = (kk < C3) ? lg[2 + i] : lg[2 + MAXK + i];
-        return Fj[(int64_t)site * C3 + (kk < C3 ? kk : kk - C3)];
-      };
-      if (!pair) {
-        for (int i = 0; i < K; ++i) {
-          const float f = feat(i, k);
-          acc[0] += f * dO[2 * i];
-          acc[1] += f * dO[2 * i + 1];
-          bacc[0] += dO[2 * i];
-          bacc[1] += dO[2 * i + 1];
+      const float* dP = dO + 2 * MAXK;
+      float f[MAXK];
+#pragma unroll
+      for (int i = 0; i < MAXK; ++i) f[i] = i < K ? Fj[(int64_t)lg[side + i] * C3] : 0.0f;
+#pragma unroll
+      for (int i = 0; i < MAXK; ++i) {
+        if (i >= K) break;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          u[c] += f[i] * dO[2 * i + c];
+          bu[c] += dO[2 * i + c];
         }
-      } else {
-        for (int i = 0; i + 1 < K; ++i) {
-          const float f = (k < 2 * C3) ? feat(i, k) : feat(i + 1, k - 2 * C3);
+        if (i + 1 < K) {
+#pragma unroll
           for (int q = 0; q < 4; ++q) {
-            acc[q] += f * dO[2 * MAXK + 4 * i + q];
-            bacc[q] += dO[2 * MAXK + 4 * i + q];
+            open[q] += f[i] * dP[4 * i + q];
+            close[q] += f[i + 1 < MAXK ? i + 1 : i] * dP[4 * i + q];
+            bp[q] += dP[4 * i + q];
           }
         }
       }
     }
   }
-  if (!pair) {
-    G[k * 2] = acc[0];
-    G[k * 2 + 1] = acc[1];
-    if (slice == 0 && lane == 0) {
-      G[2 * C3 * 2] = bacc[0];
-      G[2 * C3 * 2 + 1] = bacc[1];
-    }
-  } else {
-    float* Wp = G + 2 * C3 * 2 + 2;
-    for (int q = 0; q < 4; ++q) Wp[k * 4 + q] = acc[q];
-    if (slice == 3 && lane == 0)
-      for (int q = 0; q < 4; ++q) Wp[4 * C3 * 4 + q] = bacc[q];
+  float* G = grad + OFF.head + (size_t)dir * HEAD;
+  float* Wp = G + 2 * C3 * 2 + 2;
+  for (int c = 0; c < 2; ++c) atomicAdd(G + k * 2 + c, u[c]);
+  for (int q = 0; q < 4; ++q) {
+    atomicAdd(Wp + k * 4 + q, open[q]);
+    atomicAdd(Wp + (2 * C3 + k) * 4 + q, close[q]);
+  }
+  if (k == 0) {
+    for (int c = 0; c < 2; ++c) atomicAdd(G + 2 * C3 * 2 + c, bu[c]);
+    for (int q = 0; q < 4; ++q) atomicAdd(Wp + 4 * C3 * 4 + q, bp[q]);
   }
 }
 
@@ -1213,17 +1410,34 @@ WLayout wlayout(int d, int64_t jobs, int M, bool train) {
   return l;
 }
 
-template <int MODE, int EPI>
-int conv(int L, int64_t rows, int cin, int cout, const float* X, const float* Bm, float* C, const float* aux,
-         hipStream_t st) {
-  const int64_t Mdim = (MODE == G_DW) ? 9 * cin : rows;
-  const int Ndim = (MODE == G_DX) ? cin : cout;
-  const int64_t Kdim = (MODE == G_FWD) ? 9 * cin : (MODE == G_DX) ? 9 * cout : rows;
-  int64_t splits = 1;
-  if (MODE == G_DW) splits = std::max<int64_t>(1, std::min<int64_t>(512, rows / 2048));
-  const int64_t kchunk = ((Kdim + splits - 1) / splits + 15) / 16 * 16;
-  const dim3 grid((unsigned)((Mdim + 63) / 64), (unsigned)((Ndim + 63) / 64), (unsigned)((Kdim + kchunk - 1) / kchunk));
-  conv_gemm<MODE, EPI><<<grid, dim3(256), 0, st>>>(L, rows, cin, cout, kchunk, X, Bm, C, aux);
+template <int MODE, int CS, int NT, int EPI>
+int conv(int L, int64_t rows, const float* X, const float* W, float* Y, const float* aux, hipStream_t st) {
+  const dim3 grid((unsigned)((rows + 127) / 128));
+  conv_f32<MODE, CS, NT, EPI><<<grid, dim3(256), 0, st>>>(L, rows, divide_by(L), divide_by(L * L), X, W, Y, aux);
+  W_TRY(hipGetLastError());
+  return BBP_OK;
+}
+
+// Gradient of a convolution's weights and bias (consecutive in the parameters) by conv_dw: about DW_GROUPS
+// workgroups, two per CU, as far as the partials fit in `scratch` (a workspace slot that is free at that point of the
+// backward pass); with no room for two the one split writes the gradient itself.
+constexpr int64_t DW_GROUPS = 512;
+template <int CIN, int NT>
+int conv_weights(int L, int64_t rows, const float* X, const float* dY, float* dW, float* scratch, size_t scratch_bytes,
+                 hipStream_t st) {
+  constexpr int N = (9 * CIN + 1) * NT, TILES = (9 * CIN + 127) / 128;
+  int64_t splits = std::min<int64_t>(DW_GROUPS / TILES, (int64_t)(scratch_bytes / (N * sizeof(float))));
+  splits = std::max<int64_t>(1, std::min<int64_t>(splits, (rows + 255) / 256));
+  // (a split's byte offsets into the activations stay below 2^31)
+  splits = std::max<int64_t>(splits, (rows * std::max(CIN, NT) * 4 + (1 << 30) - 1) / (1 << 30));
+  const int64_t kchunk = ((rows + splits - 1) / splits + 15) / 16 * 16;
+  splits = (rows + kchunk - 1) / kchunk;
+  if (splits > 1 && (size_t)splits * N * sizeof(float) > scratch_bytes)
+    return wfail(BBP_EINVAL, "too many sites for one training batch");
+  conv_dw<CIN, NT><<<dim3(TILES, (unsigned)splits), dim3(256), 0, st>>>(L, rows, divide_by(L), divide_by(L * L), kchunk, X,
+                                                                      dY, splits > 1 ? scratch : dW);
+  if (splits > 1)
+    dw_reduce_kernel<<<dim3((N + 255) / 256), dim3(256), 0, st>>>(scratch, N, (int)splits, dW);
   W_TRY(hipGetLastError());
   return BBP_OK;
 }
@@ -1309,9 +1523,9 @@ int trunk(int d, const uint8_t* syn, const double* pdev, double p, int64_t jobs,
   features_kernel<float, C0><<<dim3((unsigned)(jobs / 4)), dim3(256), 0, st>>>(syn, pdev, (float)p, d, X0);
   W_TRY(hipGetLastError());
   int rc;
-  if ((rc = conv<G_FWD, 1>(L, rows, C0, C1, X0, prm + OFF.w1, A1, prm + OFF.b1, st))) return rc;
-  if ((rc = conv<G_FWD, 1>(L, rows, C1, C2, A1, prm + OFF.w2, A2, prm + OFF.b2, st))) return rc;
-  if ((rc = conv<G_FWD, 0>(L, rows, C2, C3, A2, prm + OFF.w3, F, prm + OFF.b3, st))) return rc;
+  if ((rc = conv<G_FWD, C0, C1, 1>(L, rows, X0, prm + OFF.w1, A1, prm + OFF.b1, st))) return rc;
+  if ((rc = conv<G_FWD, C1, C2, 1>(L, rows, A1, prm + OFF.w2, A2, prm + OFF.b2, st))) return rc;
+  if ((rc = conv<G_FWD, C2, C3, 0>(L, rows, A2, prm + OFF.w3, F, prm + OFF.b3, st))) return rc;
   return BBP_OK;
 }
 
@@ -1418,21 +1632,20 @@ int bbp_warm_loss_grad(int32_t d, double p, const double* p_dev, const uint8_t* 
     head_kernel<true><<<dim3((unsigned)(jobs * M)), dim3(64), 0, st>>>(
         F, lg.dev, M, L, jobs, params_dev, targets_dev, use_dev, 1.0f / (float)trained_messages, nullptr, dout, dF,
         lossb);
-    head_grad_kernel<<<dim3(36), dim3(64), 0, st>>>(F, lg.dev, M, L, jobs, use_dev, dout, grad_dev);
+    // up to 128 workgroups per direction: two per CU, and no more adds into a gradient entry than that
+    head_grad_kernel<<<dim3((unsigned)std::min<int64_t>(jobs, 128), 4), dim3(2 * C3), 0, st>>>(F, lg.dev, M, L, jobs, use_dev,
+                                                                                         dout, grad_dev);
   }
   sum_kernel<<<1, 256, 0, st>>>(lossb, jobs * std::max(M, 1), loss_dev);
   W_TRY(hipGetLastError());
-  // conv3 (no activation)
-  if ((rc = conv<G_DW, 0>(L, rows, C2, C3, A2, dF, grad_dev + OFF.w3, nullptr, st))) return rc;
-  colsum_kernel<<<C3, 256, 0, st>>>(dF, rows, C3, grad_dev + OFF.b3);
-  if ((rc = conv<G_DX, 1>(L, rows, C2, C3, dF, params_dev + OFF.w3, dA2, A2, st))) return rc;
-  // conv2 (ReLU: dA2 is already the gradient of its pre-activation)
-  if ((rc = conv<G_DW, 0>(L, rows, C1, C2, A1, dA2, grad_dev + OFF.w2, nullptr, st))) return rc;
-  colsum_kernel<<<C2, 256, 0, st>>>(dA2, rows, C2, grad_dev + OFF.b2);
-  if ((rc = conv<G_DX, 1>(L, rows, C1, C2, dA2, params_dev + OFF.w2, dA1, A1, st))) return rc;
+  // conv3 (no activation); the weight gradients' partials go where the next gradient is still to be written
+  if ((rc = conv_weights<C2, C3>(L, rows, A2, dF, grad_dev + OFF.w3, dA2, w.dA1 - w.dA2, st))) return rc;
+  if ((rc = conv<G_DX, C3, C2, 1>(L, rows, dF, params_dev + OFF.w3, dA2, A2, st))) return rc;
+  // conv2 (ReLU: dA2 is already the gradient of its pre-activation); dF has been used
+  if ((rc = conv_weights<C1, C2>(L, rows, A1, dA2, grad_dev + OFF.w2, dF, w.dA2 - w.dF, st))) return rc;
+  if ((rc = conv<G_DX, C2, C1, 1>(L, rows, dA2, params_dev + OFF.w2, dA1, A1, st))) return rc;
   // conv1
-  if ((rc = conv<G_DW, 0>(L, rows, C0, C1, X0, dA1, grad_dev + OFF.w1, nullptr, st))) return rc;
-  colsum_kernel<<<C1, 256, 0, st>>>(dA1, rows, C1, grad_dev + OFF.b1);
+  if ((rc = conv_weights<C0, C1>(L, rows, X0, dA1, grad_dev + OFF.w1, dF, w.dA2 - w.dF, st))) return rc;
   W_TRY(hipGetLastError());
   return BBP_OK;
 }

@@ -370,3 +370,47 @@ def test_committed_weights_against_cold_start(dev):
     assert np.all(np.isfinite(hot["loglik"]))
     assert agree >= 0.99
     assert wi <= 1.1 * ci
+
+
+# rows of the training batch at the edges of the convolutions' tiles: 36 (one partial 128-row tile, one split of the
+# weight gradient, fewer than a stage's rows in its last one), 300 (two splits) and 7056 (many)
+@pytest.mark.parametrize("d,k,b", [(2, 2, 1), (3, 2, 3), (11, 6, 4)])
+def test_loss_gradient_tile_edges(dev, d, k, b):
+    """Loss and gradient at ragged row counts against the oracle, with the tolerances of
+    test_loss_gradient_against_oracle (2e-4 of a block's largest entry; its sums over rows are split and added
+    in FP32 here too); a second call gives the same loss bitwise."""
+    import torch
+    import paper_2402_04834_amd as bbp
+    from paper_2402_04834_amd import warm
+    _, syn = workload.make_batch(d, 0.1, b, workload="warm", p_index=330 + d)
+    ps = np.linspace(0.06, 0.14, b)
+    th = _theta(130 + d, head_scale=0.5)
+    plan = blockbp.Plan(d, k, k)
+    rng = np.random.default_rng(1000 + d)
+    targets = np.zeros((b, 4, plan.M, 64), dtype=np.float32)
+    for e, (src, dst, _) in enumerate(plan.edges):
+        t = rng.random((b, 4, 2 ** plan.msg_len(src, dst))) + 0.05
+        targets[:, :, e, :t.shape[2]] = t / np.linalg.norm(t, axis=-1, keepdims=True)
+    use = np.ones(4 * b, dtype=np.uint8)
+    use[-1] = 0
+    opts = bbp.default_opts(block=k, chi=32)
+    args = [torch.from_numpy(x).to(dev) for x in (ps, syn, th, targets, use)]
+    _say(f"[warm grad edges] d={d} k={k} batch {b}: {4 * b * (2 * d - 1) ** 2} rows")
+    loss, grad = warm.loss_grad(d, args[0], args[1], opts, *args[2:])
+    again, _ = warm.loss_grad(d, args[0], args[1], opts, *args[2:])
+    torch.cuda.synchronize()
+    assert torch.equal(loss, again)
+    loss, grad = float(loss.cpu()[0]), grad.cpu().numpy().astype(np.float64)
+    jobs = _oracle_jobs(d, syn, ps)
+    used = np.flatnonzero(use)
+    ref_l, ref_g = 0.0, np.zeros(th.size)
+    for j in used:
+        l, g = warmnet.loss_and_grad(th.astype(np.float64), jobs[j], d, plan,
+                                     targets[j // 4, j % 4].astype(np.float64), list(range(plan.M)))
+        ref_l += l / len(used)
+        ref_g += g / len(used)
+    assert abs(loss - ref_l) <= 1e-5 + 1e-4 * abs(ref_l), (loss, ref_l)
+    gp, rp = warmnet.unpack(grad), warmnet.unpack(ref_g)
+    for n in rp:
+        err = np.abs(gp[n] - rp[n]).max()
+        assert err <= 2e-4 * np.abs(rp[n]).max(), (n, err)
