@@ -1,7 +1,7 @@
 """Build the HIP library libbbp.so in-tree for gfx950 (hipcc; no JIT cache).
 
-The block-sweep kernels are instantiated per sweep length in separate objects (sweep_kernel.hip compiled
-with BBP_KT = 1..6); all objects compile in parallel and are linked into one shared library.
+The block-sweep kernels are instantiated per sweep length and width in separate objects (sweep_kernel.hip compiled
+with BBP_KT, BBP_KP = 1..6); all objects compile in parallel and are linked into one shared library.
 """
 from __future__ import annotations
 
@@ -25,11 +25,11 @@ FLAGS = [
     "-Wno-unused-command-line-argument",
 ]
 
-# (source, extra flags, object name)
-UNITS = [("plan.cpp", [], "plan.o"), ("bbp.hip", [], "bbp.o"), ("warm.hip", [], "warm.o"),
-         ("small_sweep.hip", [], "small_sweep.o"), ("bmps.hip", [], "bmps.o"), ("trunc_sweep.hip", [], "trunc_sweep.o")] + [
-    ("sweep_kernel.hip", [f"-DBBP_KT={k}"], f"sweep_k{k}.o") for k in range(1, 7)
-]
+# (source, extra flags, object name), the longest compiles first
+UNITS = [("trunc_sweep.hip", [], "trunc_sweep.o"), ("bmps.hip", [], "bmps.o"), ("warm.hip", [], "warm.o")] + [
+    ("sweep_kernel.hip", [f"-DBBP_KT={t}", f"-DBBP_KP={p}"], f"sweep_{t}x{p}.o")
+    for t in range(6, 0, -1) for p in range(6, 0, -1)
+] + [("bbp.hip", [], "bbp.o"), ("small_sweep.hip", [], "small_sweep.o"), ("plan.cpp", [], "plan.o")]
 
 
 def _compile(hipcc: str, src: str, extra: list, obj: str, verbose: bool) -> None:

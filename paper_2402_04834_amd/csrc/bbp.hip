@@ -23,6 +23,8 @@
 #include <mutex>
 #include <string>
 #include <tuple>
+#include <type_traits>
+#include <utility>
 #include <vector>
 
 #include "../../include/bbp.h"
@@ -36,7 +38,6 @@ using bbp::SweepDesc;
 namespace {
 
 using bbp::MSTRIDE;
-using bbp::SWEEP_WAVES;
 
 thread_local std::string g_err = "no error";
 
@@ -220,8 +221,6 @@ __global__ __launch_bounds__(256) void finalize_kernel(const double* __restrict_
 }
 
 // --------------------------------------------------------------------------------------------------
-unsigned sweep_groups(int64_t jobs) { return (unsigned)((jobs + SWEEP_WAVES - 1) / SWEEP_WAVES); }
-
 // A run of sweeps of one class inside a device sweep list: one kernel launch.
 struct ClassRun {
   int cls, first, count;
@@ -254,23 +253,26 @@ hipError_t bbp::launch_labels(hipStream_t st, const uint8_t* syn, int d, int64_t
   return hipGetLastError();
 }
 
+// f(integral_constant<int, (kt - 1) * 6 + kp - 1>)
+template <int... I, class F>
+static hipError_t by_shape(int kt, int kp, std::integer_sequence<int, I...>, F&& f) {
+  hipError_t e = hipErrorInvalidValue;
+  ((I == (kt - 1) * 6 + kp - 1 ? (void)(e = f(std::integral_constant<int, I>{})) : (void)0), ...);
+  return e;
+}
+
 hipError_t bbp::launch_sweeps(int cls, hipStream_t st, const SweepArgs& a) {
   if (bbp::trunc_class(cls)) return launch_trunc_sweeps(st, a, (cls & 1) != 0);
   if (a.small) return launch_small_sweeps(st, a);
   bool biased = false;
   for (int k = 0; k < a.ngroups; ++k) biased |= a.g[k].biased != 0;
   if (biased && a.bf16) return hipErrorInvalidValue;   // refused earlier by resolve()
-  const int variant = (cls & 15) | (a.bf16 ? 16 : 0) | (biased ? 32 : 0), kt = (cls >> 4) + 1;
-  const dim3 grid(sweep_groups(a.items));
-  switch (kt) {
-    case 1: return launch_sweeps_k1(variant, grid, st, a);
-    case 2: return launch_sweeps_k2(variant, grid, st, a);
-    case 3: return launch_sweeps_k3(variant, grid, st, a);
-    case 4: return launch_sweeps_k4(variant, grid, st, a);
-    case 5: return launch_sweeps_k5(variant, grid, st, a);
-    case 6: return launch_sweeps_k6(variant, grid, st, a);
-    default: return hipErrorInvalidValue;
-  }
+  if (a.items >= (int64_t)1 << 31) return hipErrorInvalidValue;
+  const int variant = (cls & 7) | (a.bf16 ? 8 : 0) | (biased ? 16 : 0);
+  return by_shape(class_kt(cls), class_kp(cls), std::make_integer_sequence<int, 36>{}, [&](auto shape) {
+    return launch_sweeps_of<decltype(shape)::value / 6 + 1, decltype(shape)::value % 6 + 1>(variant, (unsigned)a.items, st,
+                                                                                       a);
+  });
 }
 
 namespace {
@@ -610,7 +612,12 @@ int enqueue(std::vector<GroupRun>& gr, const bbp_opts* opts, const Tune& tn, hip
           sa.tws = g.tws;
           sa.tws_slots = g.lay.tws_slots;
         }
-        items += g.jobs * (int64_t)r.count;
+        const bool wave = !sa.small && !bbp::trunc_class(c);   // wavefront kernels: several jobs per item
+        const int64_t blocks = wave ? (g.jobs + bbp::sweep_jobs_per_wave(bbp::class_kp(c)) - 1) /
+                                          bbp::sweep_jobs_per_wave(bbp::class_kp(c))
+                                    : g.jobs;
+        G.by = bbp::divide_by((uint32_t)(tn.order == 0 ? blocks : r.count));
+        items += blocks * (int64_t)r.count;
       }
       sa.items = items;
       hipStream_t s = streams_of((int)li);
@@ -696,7 +703,10 @@ int collect_timing(std::vector<GroupRun>& gr, const bbp_opts* opts, std::vector<
   timing->top_class = -1;
   for (auto& kv : per_class)
     if (std::get<0>(kv.second) > timing->top_ms) {
-      timing->top_class = kv.first;
+      const int c = kv.first;
+      timing->top_class = bbp::trunc_class(c)
+                              ? c
+                              : (((bbp::class_kt(c) - 1) * 4 + (c >> 1 & 3)) * 2 + (bbp::class_kp(c) == 1 ? 1 : 0)) * 2 + (c & 1);
       timing->top_ms = std::get<0>(kv.second);
       timing->top_launches = std::get<1>(kv.second);
       timing->top_flops = std::get<2>(kv.second);

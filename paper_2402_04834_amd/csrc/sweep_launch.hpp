@@ -9,12 +9,30 @@
 
 namespace bbp {
 
-#ifndef BBP_SWEEP_WAVES
-#define BBP_SWEEP_WAVES 1
+// lane bits of one sweep in the wavefront kernels: its 2^kp configurations, at least 8 (kp = 0: not known at
+// compile time, a whole wavefront)
+constexpr int sweep_lane_bits(int kp) { return kp == 0 ? 6 : kp < 3 ? 3 : kp; }
+// consecutive jobs that one wavefront runs through a sweep of kp positions
+constexpr int sweep_jobs_per_wave(int kp) { return 64 >> sweep_lane_bits(kp); }
+
+// x / n for x < 2^31 by one multiply: m = ceil(2^32 / n) is less than 1 above 2^32 / n, so the quotient is at most
+// one too large, which the remainder corrects
+struct Divide {
+  uint32_t n, m;
+};
+inline Divide divide_by(uint32_t n) { return Divide{n, (uint32_t)(((1ull << 32) + n - 1) / n)}; }
+#if defined(__HIP__)
+__device__ __forceinline__ unsigned quotient(unsigned x, Divide d, unsigned& rem) {
+  unsigned q = d.n == 1 ? x : __umulhi(x, d.m);
+  rem = x - q * d.n;
+  if ((int)rem < 0) {
+    --q;
+    rem += d.n;
+  }
+  return q;
+}
 #endif
-// independent sweeps (wavefronts) per workgroup: one, so that the wavefront of a converged job, or one
-// that finishes early, frees its slot at once
-constexpr int SWEEP_WAVES = BBP_SWEEP_WAVES;
+
 constexpr int MSTRIDE = 64;      // floats per stored message (2^6) for plans whose blocks are at most 6 wide
 
 constexpr int MAX_GROUPS = 8;   // (d, p) groups of one mixed batch
@@ -29,6 +47,7 @@ struct SweepGroup {
   double* lnW;               // [job][nblocks] (closing sweeps)
   int64_t jobs;
   int64_t item0;             // first item of the group in the launch
+  Divide by;                 // wavefront kernels: the group's job blocks per sweep (order 0) or its sweeps (order 1)
   int32_t count;             // sweeps of this class in the group
   int32_t d, M, nblocks;
   float p00, pe;             // depolarizing noise entries: 1 - p and p / 3
@@ -42,10 +61,10 @@ struct SweepGroup {
 
 struct SweepArgs {
   SweepGroup g[MAX_GROUPS];
-  int64_t items;             // sum over groups of jobs * count: one wavefront each
+  int64_t items;             // sum over groups of count * jobs (wavefront kernels: job blocks): one wavefront each
   int32_t ngroups;
   int32_t mode;              // 0: message update, 1: closing sweep (W_v)
-  int32_t order;             // item order inside a group: 0 sweep-major (item = sweep * jobs + job), 1 job-major
+  int32_t order;             // item order inside a group: 0 sweep-major (item = sweep * jobs + job), 1 job-major (job blocks)
   int32_t bf16;              // 1: products of BF16-rounded inputs (precision mode 1); 0: FP32 products
   float eta;                 // damping
   int32_t small;             // 1: every block is at most 2x2 tensors: one lane per item (small_sweep.hip)
@@ -65,13 +84,15 @@ size_t trunc_slot_bytes();
 // launch the a.items truncating sweeps (in chunks of a.tws_slots items), all of the narrow form or none
 hipError_t launch_trunc_sweeps(hipStream_t st, const SweepArgs& a, bool narrow);
 
-// Class of a sweep: the kernel instantiation that runs it -- length, caps present, one position across,
-// first site a qubit: code (((kt - 1) * 4 + top * 2 + bottom) * 2 + single) * 2 + q00.
+// Class of a sweep: the kernel instantiation that runs it -- length, positions across, caps present, first site a
+// qubit: code (((kt - 1) * 6 + kp - 1) * 4 + top * 2 + bottom) * 2 + q00.
 inline int sweep_class(const SweepDesc& s) {
   if (s.trunc) return TRUNC_CLASS | (s.trunc == 2 ? 1 : 0);
-  return (((s.kt - 1) * 4 + (s.msg_top >= 0 ? 2 : 0) + (s.msg_bot >= 0 ? 1 : 0)) * 2 + (s.kp == 1 ? 1 : 0)) * 2 +
+  return (((s.kt - 1) * 6 + s.kp - 1) * 4 + (s.msg_top >= 0 ? 2 : 0) + (s.msg_bot >= 0 ? 1 : 0)) * 2 +
          ((s.geo & GEO_Q00) ? 1 : 0);
 }
+inline int class_kt(int cls) { return cls / 48 + 1; }
+inline int class_kp(int cls) { return cls / 8 % 6 + 1; }
 
 // Launch the a.items (job, sweep) items of class `cls` on stream st.
 hipError_t launch_sweeps(int cls, hipStream_t st, const SweepArgs& a);
@@ -79,13 +100,9 @@ hipError_t launch_sweeps(int cls, hipStream_t st, const SweepArgs& a);
 // blocks of at most 2x2 tensors, any class, FP32 (small_sweep.hip)
 hipError_t launch_small_sweeps(hipStream_t st, const SweepArgs& a);
 
-// per-length launchers (one translation unit each); variant = class code modulo 16, plus 16 for the
-// BF16-input kernels or 32 for the biased-noise kernels
-hipError_t launch_sweeps_k1(int variant, dim3 grid, hipStream_t st, const SweepArgs& a);
-hipError_t launch_sweeps_k2(int variant, dim3 grid, hipStream_t st, const SweepArgs& a);
-hipError_t launch_sweeps_k3(int variant, dim3 grid, hipStream_t st, const SweepArgs& a);
-hipError_t launch_sweeps_k4(int variant, dim3 grid, hipStream_t st, const SweepArgs& a);
-hipError_t launch_sweeps_k5(int variant, dim3 grid, hipStream_t st, const SweepArgs& a);
-hipError_t launch_sweeps_k6(int variant, dim3 grid, hipStream_t st, const SweepArgs& a);
+// per-shape launchers (one translation unit each, 1 <= KT, KP <= 6); variant = class code modulo 8, plus 8 for the
+// BF16-input kernels or 16 for the biased-noise kernels
+template <int KT, int KP>
+hipError_t launch_sweeps_of(int variant, unsigned items, hipStream_t st, const SweepArgs& a);
 
 }  // namespace bbp

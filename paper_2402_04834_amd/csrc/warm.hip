@@ -35,8 +35,13 @@
 
 #include "../../include/bbp.h"
 #include "plan.hpp"
+#include "sweep_launch.hpp"
 
 namespace {
+
+using bbp::Divide;
+using bbp::divide_by;
+using bbp::quotient;
 
 constexpr int C0 = 11, C1 = 64, C2 = 128, C3 = 96;
 constexpr int MAXK = 6;                                   // legs of a message (block size <= 6)
@@ -208,21 +213,6 @@ __global__ __launch_bounds__(256) void features_kernel(const uint8_t* __restrict
 //   conv_dw  dW[t cin + ci][co] = sum_rows X[row + t][ci] dY[row][co]                  (M 9 cin, N cout, K rows)
 enum { G_FWD = 0, G_DX = 1 };
 
-// x / n for x < 2^31 by one multiply: m = ceil(2^32 / n) is at most n - 1 over 2^32 / n, so the quotient is at
-// most one too large, which the remainder corrects
-struct Divide {
-  unsigned n, m;
-};
-inline Divide divide_by(unsigned n) { return Divide{n, (unsigned)(((1ull << 32) + n - 1) / n)}; }
-__device__ __forceinline__ unsigned quotient(unsigned x, Divide d, unsigned& rem) {
-  unsigned q = d.n == 1 ? x : __umulhi(x, d.m);
-  rem = x - q * d.n;
-  if ((int)rem < 0) {
-    --q;
-    rem += d.n;
-  }
-  return q;
-}
 // where a row sits on its grid: bit 0 first grid row, 1 last, 2 first column, 3 last column
 __device__ __forceinline__ unsigned edge_bits(unsigned row, Divide byL, Divide byLL) {
   unsigned site, c;

@@ -17,7 +17,10 @@
 // fixed by the sweep length (bond j of a K-site message carries 2^min(j, K-j) values in the open-leg
 // reading), and qubits and checks alternate along both axes, so with the sweep length, the caps present
 // and the kind of the first site as template parameters every register index and every qubit/check
-// decision is a compile-time constant. No LDS, no barriers: a workgroup holds independent sweeps.
+// decision is a compile-time constant; so is the number of positions (KP) where the kernel is instantiated for
+// it. A sweep of kp < 6 positions has only 2^kp configurations: it takes 2^LB lanes (LB = kp, at least 3) and a
+// wavefront runs 64 >> LB jobs through the same sweep side by side, with the labels and messages that are wave-uniform
+// in a whole-wavefront sweep then per lane. No barriers: a workgroup holds independent sweeps.
 //
 // Side-message caps: psi over the old cap index, phi over the new one and the emitted vertical bond v (see
 // Cap below). Any placement of the dense core along the message gives the same exact contraction; a sweep
@@ -67,6 +70,13 @@ __device__ __forceinline__ void sfor(F&& f) {
   sfor_(f, std::make_integer_sequence<int, N>{});
 }
 
+// f(0, false), which also takes the term of index 1, then f(a, true) for a = 2 .. N-1
+template <int N, class F>
+__device__ __forceinline__ void first_then_rest(F&& f) {
+  f(std::integral_constant<int, 0>{}, std::false_type{});
+  if constexpr (N > 2) sfor<N - 2>([&](auto k) { f(std::integral_constant<int, k + 2>{}, std::true_type{}); });
+}
+
 typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf4 __attribute__((ext_vector_type(4)));
 typedef float fl2 __attribute__((ext_vector_type(2)));
@@ -92,6 +102,13 @@ __device__ __forceinline__ V splat(float x) { return V{x}; }
 __device__ __forceinline__ float tof(float x) { return x; }
 // a * b + c, fused
 __device__ __forceinline__ float fmav(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+// a b + c d with one product rounded and the other fused into the sum: c d rounded, or a b when AB. Every two-product
+// sum of the sweep says which, so that its result does not depend on how a compiler orders a sum's operands in the
+// one or the other instantiation: a sweep gives the same bits whatever kernel it runs in.
+template <bool AB = false>
+__device__ __forceinline__ float mul2(float a, float b, float c, float d) {
+  return AB ? fmav(c, d, a * b) : fmav(a, b, c * d);
+}
 
 // value of x in lane (lane ^ M)
 template <int M, class V>
@@ -128,9 +145,17 @@ __device__ __forceinline__ f4 mfma4(float a, float b, f4 acc) { return __builtin
 // BF16 values (k = 0..3), lane 4b+j column j of B, and holds acc[i] = D[i][j] in FP32.
 __device__ __forceinline__ f4 mfma4b(bf4 a, bf4 b, f4 acc) { return __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(a, b, acc, 0, 0, 0); }
 
+// sum over the 2^LB lanes of a sweep of v, or of v^2 (the first addition fused with the lane's own square)
+template <int LB>
 __device__ __forceinline__ float wave_sum(float v) {
-  sfor<6>([&](auto k) { v += xchg<(1 << k)>(v); });
+  sfor<LB>([&](auto k) { v += xchg<(1 << k)>(v); });
   return v;
+}
+template <int LB>
+__device__ __forceinline__ float wave_sum_sq(float v) {
+  float t = fmav(v, v, xchg<1>(v * v));
+  sfor<LB - 1>([&](auto k) { t += xchg<(2 << k)>(t); });
+  return t;
 }
 
 // ------------------------------------------------------------------------------------------- cap shapes
@@ -166,7 +191,7 @@ __device__ __forceinline__ auto phi(G&& g, Msg&& m) {
     return g(std::integral_constant<int, V * C::PN + NP>{});
   } else {
     R acc = splat<R>(0.0f);
-    sfor<C::PO>([&](auto a) { acc += m(std::integral_constant<int, C::idx(a, V, NP)>{}) * g(a); });
+    sfor<C::PO>([&](auto a) { acc = fmav(m(std::integral_constant<int, C::idx(a, V, NP)>{}), g(a), acc); });
     return acc;
   }
 }
@@ -185,31 +210,98 @@ __device__ __forceinline__ auto phi2(G0&& g0, G1&& g1, Msg&& m) {
   } else {
     R acc = splat<R>(0.0f);
     sfor<C::PO>([&](auto a) {
-      acc += m(std::integral_constant<int, C::idx(a, 0, NP)>{}) * g0(a);
-      acc += m(std::integral_constant<int, C::idx(a, 1, NP)>{}) * g1(a);
+      acc = fmav(m(std::integral_constant<int, C::idx(a, 0, NP)>{}), g0(a), acc);
+      acc = fmav(m(std::integral_constant<int, C::idx(a, 1, NP)>{}), g1(a), acc);
     });
     return acc;
   }
 }
 
 // ------------------------------------------------------------------------------------- sweep context
-// V = float: the value type of the state.
-template <class V>
+// V_ = float: the value type of the state. LB_: lane bits of one sweep; a wavefront holds 64 >> LB sweeps of the same
+// block for consecutive jobs, each on its own 2^LB lanes. KP_: positions across the sweep, 0 = known at run time
+// only (kp).
+template <class V_, int LB_, int KP_, bool BIASED_>
 struct Ctx {
-  int h;                // lane = crossing-bond configuration (lane-bit layout above)
-  int kp;               // positions across the sweep
+  using V = V_;
+  static constexpr int LB = LB_, KP = KP_;
+  static constexpr bool BIASED = BIASED_;   // compiled for launches with biased noise
+  static constexpr bool WHOLE = LB == 6;   // one sweep per wavefront: its labels and messages are wave-uniform
+  int h;                // lane of the sweep = crossing-bond configuration (lane-bit layout above)
+  int kp_rt;            // positions across the sweep where KP = 0
   int geo;              // GEO_* flags
-  float labv;           // lane l < kt*kp: coset label of the site at (step l / kp, position l % kp)
-  V mtv, mbv;           // lane l: entry l of the top / bottom side message (legs in sweep order)
+  // coset labels of the sites, index step * kp + position: x and z bits as lane masks (WHOLE), or two bits each in
+  // words of 16 sites that every lane of the sweep holds
+  unsigned long long lx, lz;
+  unsigned lw[2];
+  V mtv, mbv;           // WHOLE: lane l holds entry l of the top / bottom side message (legs in sweep order)
+  const float *mts, *mbs;   // else: the messages in LDS
   float p00, pe;        // depolarizing entries
   int biased;           // 1: entries from pib instead
   int pib[4];           // float bits of the Pauli probabilities by code x + 2z (I, X, Z, Y)
   int exp2;             // accumulated power-of-two scale (state values are true values * 2^-exp2)
+
+  __device__ __forceinline__ int kp() const { return KP ? KP : kp_rt; }
+  // entry idx of the top / bottom message: the same index in every lane (top, bot), or an index of the lane's own
+  template <class I>
+  __device__ __forceinline__ V top(I idx) const { return WHOLE ? readlane_v(mtv, idx) : V{mts[idx]}; }
+  template <class I>
+  __device__ __forceinline__ V bot(I idx) const { return WHOLE ? readlane_v(mbv, idx) : V{mbs[idx]}; }
+  __device__ __forceinline__ V top_at(int idx) const { return WHOLE ? V{lane_get(mtv, idx)} : V{mts[idx]}; }
+  __device__ __forceinline__ V bot_at(int idx) const { return WHOLE ? V{lane_get(mbv, idx)} : V{mbs[idx]}; }
+  __device__ __forceinline__ int label(int t, int i) const {
+    const int n = t * kp() + i;
+    if constexpr (WHOLE) return (int)((lx >> n) & 1) | ((int)((lz >> n) & 1) << 1);
+    else return (int)((n < 16 ? lw[0] >> (2 * n) : lw[1] >> (2 * n - 32)) & 3);
+  }
 };
 
 __device__ __forceinline__ int bit(int h, int b) { return (h >> b) & 1; }
 // lane-bit index of position i
-__device__ __forceinline__ int pshift(int kp, int i) { return i == 0 ? 0 : (i == kp - 1 ? 1 : i + 1); }
+__host__ __device__ constexpr int pshift(int kp, int i) { return i == 0 ? 0 : (i == kp - 1 ? 1 : i + 1); }
+
+// lanes whose index has an odd number of the bits `bits` set
+constexpr unsigned long long parity_lanes(int bits) {
+  unsigned long long m = 0;
+  for (int l = 0; l < 64; ++l) {
+    int p = 0;
+    for (int b = 0; b < 6; ++b) p ^= ((l & bits) >> b) & 1;
+    if (p) m |= 1ull << l;
+  }
+  return m;
+}
+
+// The parity of a qubit's two vertical bonds (lane bits `bits`, xor `flip`) as the coefficients take it. With one
+// sweep per wavefront and the bits known at compile time it is a constant lane mask and the comparisons with the
+// (uniform) label bits run on the scalar unit, leaving one select per coefficient; else a value per lane.
+template <class C>
+struct Parity {
+  unsigned long long mask;
+  int value;
+  // bits: a captureless function of the number of positions
+  template <class F>
+  static __device__ __forceinline__ Parity of(const C& c, F bits, bool flip) {
+    Parity p;
+    if constexpr (C::WHOLE && C::KP > 0) {
+      constexpr unsigned long long odd_lanes = parity_lanes(bits(C::KP));
+      p.mask = flip ? ~odd_lanes : odd_lanes;
+      p.value = 0;
+    } else {
+      p.mask = 0;
+      p.value = (__builtin_popcount(c.h & bits(c.kp())) & 1) ^ (flip ? 1 : 0);
+    }
+    return p;
+  }
+  __device__ __forceinline__ bool odd() const {
+    if constexpr (C::WHOLE && C::KP > 0) return __builtin_amdgcn_inverse_ballot_w64(mask);
+    else return value != 0;
+  }
+  // lanes where the parity equals b and `on` holds (both uniform where the labels are)
+  __device__ __forceinline__ bool equals(int b, bool on) const {
+    if constexpr (C::WHOLE && C::KP > 0) return __builtin_amdgcn_inverse_ballot_w64(on ? (b ? mask : ~mask) : 0ull);
+    else return value == b && on;
+  }
+};
 
 template <class V>
 struct QC {
@@ -227,21 +319,21 @@ __device__ __forceinline__ float pick4(const int* pib, int k) {
 // bond parity is pv and output crossing bit ho; scaled by sc. The crossing parity (0 for the lane's own
 // value, 1 for the partner's) flips x when swap and z otherwise; pv flips the other component. Depolarizing:
 // the entry is p00 iff the flipped label is the identity.
-__device__ __forceinline__ QC<float> qcoef(float p00, float pe, int biased, const int* pib, int lb, int swap, int pv,
-                                           int ho, bool in_abs, bool out_abs, float sc) {
+template <class C>
+__device__ __forceinline__ QC<float> qcoef(const C& c, int lb, int swap, const Parity<C>& pv, int ho, bool in_abs,
+                                           bool out_abs, float sc) {
   QC<float> q;
-  if (biased) {
+  if (c.biased) {
     const int F = swap ? 1 : 2, G = F ^ 3;
-    const float s0 = pick4(pib, lb), f0 = pick4(pib, lb ^ F), s1 = pick4(pib, lb ^ G), f1 = pick4(pib, lb ^ 3);
-    q.cs = (pv ? s1 : s0) * sc;
-    q.cf = (pv ? f1 : f0) * sc;
+    const float s0 = pick4(c.pib, lb), f0 = pick4(c.pib, lb ^ F), s1 = pick4(c.pib, lb ^ G), f1 = pick4(c.pib, lb ^ 3);
+    q.cs = (pv.odd() ? s1 : s0) * sc;
+    q.cf = (pv.odd() ? f1 : f0) * sc;
   } else {
     const int lx = lb & 1, lz = (lb >> 1) & 1;
     const int A = swap ? lx : lz, B = swap ? lz : lx;
-    const bool m = (pv == B);
-    const float hi = p00 * sc, lo = pe * sc;
-    q.cs = (m && A == 0) ? hi : lo;
-    q.cf = (m && A == 1) ? hi : lo;
+    const float hi = c.p00 * sc, lo = c.pe * sc;
+    q.cs = pv.equals(B, A == 0) ? hi : lo;
+    q.cf = pv.equals(B, A == 1) ? hi : lo;
   }
   if (in_abs) {   // the input crossing bit must be 0
     q.cs = ho ? 0.0f : q.cs;
@@ -254,33 +346,30 @@ __device__ __forceinline__ QC<float> qcoef(float p00, float pe, int biased, cons
   return q;
 }
 
-template <class V>
-__device__ __forceinline__ int label_at(const Ctx<V>& c, int t, int i) {
-  return __float_as_int(readlane_f(c.labv, t * c.kp + i)) & 3;
-}
-
 // Coefficients of the qubit at (step t, position i).
-template <class V>
-__device__ __forceinline__ QC<V> qcoefs(const Ctx<V>& c, int t, int i, int swap, int pv, int ho, bool in_abs,
+template <class C, class V>
+__device__ __forceinline__ QC<V> qcoefs(const C& c, int t, int i, int swap, const Parity<C>& pv, int ho, bool in_abs,
                                         bool out_abs, V sc) {
-  const QC<float> q = qcoef(c.p00, c.pe, c.biased, c.pib, label_at(c, t, i), swap, pv, ho, in_abs, out_abs, tof(sc));
+  const QC<float> q = qcoef(c, c.label(t, i), swap, pv, ho, in_abs, out_abs, tof(sc));
   return QC<V>{V{q.cs}, V{q.cf}};
 }
 
 // lane mask of the checks of a column (q0t: its site 0 is a qubit)
-template <class V>
-__device__ __forceinline__ int check_lanes(const Ctx<V>& c, bool q0t) {
+template <class C>
+__device__ __forceinline__ int check_lanes(const C& c, bool q0t) {
   int m = 0;
-  for (int i = 0; i < c.kp; ++i)
-    if (!(q0t ^ (i & 1))) m |= 1 << pshift(c.kp, i);
+#pragma unroll
+  for (int i = 0; i < 6; ++i)
+    if (i < c.kp() && !(q0t ^ (i & 1))) m |= 1 << pshift(c.kp(), i);
   return m;
 }
 
 // Sum over the variables of the checks whose out-leg leaves the grid (lane bits oa): the result sits at
 // those bits = 0.
-template <class V, int N>
-__device__ __forceinline__ void project_out_edge(V (&Y)[N], const Ctx<V>& c, int oa) {
-  for (int b = 1; b < 64; b <<= 1) {
+template <class V, int N, class C>
+__device__ __forceinline__ void project_out_edge(V (&Y)[N], const C& c, int oa) {
+#pragma unroll
+  for (int b = 1; b < (1 << C::LB); b <<= 1) {
     if (!(oa & b)) continue;
     const bool zero = (c.h & b) != 0;
     sfor<N>([&](auto e) {
@@ -291,15 +380,17 @@ __device__ __forceinline__ void project_out_edge(V (&Y)[N], const Ctx<V>& c, int
 }
 
 // --------------------------------------------------------------------------------- column, kp >= 2
-template <class V, int KT, bool TOP, bool BOT, bool Q00, bool BF, int T>
+template <class V, int KT, bool TOP, bool BOT, bool Q00, bool BF, int T, class C>
 __device__ __forceinline__ void column_multi(const V (&X)[Cap<TOP, KT, T>::PO * Cap<BOT, KT, T>::PO],
-                                             V (&Y)[Cap<TOP, KT, T>::PN * Cap<BOT, KT, T>::PN], Ctx<V>& c,
+                                             V (&Y)[Cap<TOP, KT, T>::PN * Cap<BOT, KT, T>::PN], C& c,
                                              V sc) {
   using CT = Cap<TOP, KT, T>;
   using CB = Cap<BOT, KT, T>;
   constexpr int PTO = CT::PO, PTN = CT::PN, PSO = CB::PO, PSN = CB::PN;
   constexpr bool Q0 = Q00 ^ (T & 1);   // site 0 of this column is a qubit
-  const int h = c.h, kp = c.kp;
+  // rounding order (mul2) of the end qubits' transforms next to a routing cap
+  constexpr bool SWAP = !C::BIASED && T == 0 && KT > 1;
+  const int h = c.h, kp = c.kp();
   const int swap = ((c.geo & GEO_SWAP0) ? 1 : 0) ^ (T & 1);
   const bool in_abs = (T == 0) && (c.geo & GEO_IN_EDGE);
   const bool out_abs = (T == KT - 1) && (c.geo & GEO_OUT_EDGE);
@@ -309,15 +400,16 @@ __device__ __forceinline__ void column_multi(const V (&X)[Cap<TOP, KT, T>::PO * 
   const V sc0 = Q0 ? sc : one;
   const V sc1 = (!Q0 && kp >= 3) ? sc : one;
   const V scl = (!Q0 && kp == 2) ? sc : one;
-  auto mt = [&](auto idx) { return readlane_v(c.mtv, idx); };
-  auto mb = [&](auto idx) { return readlane_v(c.mbv, idx); };
+  auto mt = [&](auto idx) { return c.top(idx); };
+  auto mb = [&](auto idx) { return c.bot(idx); };
 
   // ---- top cap + site 0 (lane bit 0)
   V Z[PTN * PSO];
   if constexpr (Q0) {
-    const int ho = bit(h, 0), vo = bit(h, pshift(kp, 1));
-    const QC<V> q0 = qcoefs(c, T, 0, swap, vo, ho, in_abs, out_abs, sc0);
-    QC<V> q1 = qcoefs(c, T, 0, swap, vo ^ 1, ho, in_abs, out_abs, sc0);
+    const int ho = bit(h, 0);
+    constexpr auto vo = [](int k) { return 1 << pshift(k, 1); };
+    const QC<V> q0 = qcoefs(c, T, 0, swap, Parity<C>::of(c, vo, false), ho, in_abs, out_abs, sc0);
+    QC<V> q1 = qcoefs(c, T, 0, swap, Parity<C>::of(c, vo, true), ho, in_abs, out_abs, sc0);
     if (c.geo & GEO_TOP_EDGE) q1.cs = q1.cf = splat<V>(0.0f);
     if constexpr (BF && CT::kind == K_EQ && PTN == 4) {
       // T is the middle step (never the first or last), so no edge absorption depends on the lane's own bit
@@ -328,10 +420,10 @@ __device__ __forceinline__ void column_multi(const V (&X)[Cap<TOP, KT, T>::PO * 
         sfor<PTO / 2>([&](auto k) {
           float ao[2], ap[2];
           sfor<2>([&](auto u) {
-            const float m0 = lane_get(c.mtv, CT::idx(2 * k + u, 0, 0) + (h & 3));
-            const float m1 = lane_get(c.mtv, CT::idx(2 * k + u, 1, 0) + (h & 3));
-            ao[u] = m0 * q0.cs + m1 * q1.cs;
-            ap[u] = m0 * q0.cf + m1 * q1.cf;
+            const float m0 = c.top_at(CT::idx(2 * k + u, 0, 0) + (h & 3));
+            const float m1 = c.top_at(CT::idx(2 * k + u, 1, 0) + (h & 3));
+            ao[u] = mul2(m0, q0.cs, m1, q1.cs);
+            ap[u] = mul2(m0, q0.cf, m1, q1.cf);
           });
           A[k] = pk4(ao[0], ap[0], ao[1], ap[1]);
         });
@@ -347,17 +439,17 @@ __device__ __forceinline__ void column_multi(const V (&X)[Cap<TOP, KT, T>::PO * 
         // FP32 transform per lane, BF16 contraction with the message: K = (a, v) for two old cap values
         bf4 A[PTO / 2];
         sfor<PTO / 2>([&](auto k) {
-          A[k] = pk4(lane_get(c.mtv, CT::idx(2 * k, 0, 0) + (h & 3)), lane_get(c.mtv, CT::idx(2 * k, 1, 0) + (h & 3)),
-                     lane_get(c.mtv, CT::idx(2 * k + 1, 0, 0) + (h & 3)),
-                     lane_get(c.mtv, CT::idx(2 * k + 1, 1, 0) + (h & 3)));
+          A[k] = pk4(c.top_at(CT::idx(2 * k, 0, 0) + (h & 3)), c.top_at(CT::idx(2 * k, 1, 0) + (h & 3)),
+                     c.top_at(CT::idx(2 * k + 1, 0, 0) + (h & 3)),
+                     c.top_at(CT::idx(2 * k + 1, 1, 0) + (h & 3)));
         });
         sfor<PSO>([&](auto s) {
           f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
           sfor<PTO / 2>([&](auto k) {
             const V x0 = X[(2 * k) * PSO + s], xf0 = xchg<1>(x0);
             const V x1 = X[(2 * k + 1) * PSO + s], xf1 = xchg<1>(x1);
-            acc = mfma4b(A[k], pk4(q0.cs * x0 + q0.cf * xf0, q1.cs * x0 + q1.cf * xf0, q0.cs * x1 + q0.cf * xf1,
-                                   q1.cs * x1 + q1.cf * xf1), acc);
+            acc = mfma4b(A[k], pk4(mul2(q0.cs, x0, q0.cf, xf0), mul2(q1.cs, x0, q1.cf, xf0), mul2(q0.cs, x1, q0.cf, xf1),
+                                   mul2(q1.cs, x1, q1.cf, xf1)), acc);
           });
           sfor<4>([&](auto n) { Z[n * PSO + s] = acc[(int)n]; });
         });
@@ -365,15 +457,15 @@ __device__ __forceinline__ void column_multi(const V (&X)[Cap<TOP, KT, T>::PO * 
     } else if constexpr (CT::kind == K_EQ && PTN == 4) {
       float mA[PTO][2];
       sfor<PTO>([&](auto a) {
-        mA[a][0] = lane_get(c.mtv, CT::idx(a, 0, 0) + (h & 3));
-        mA[a][1] = lane_get(c.mtv, CT::idx(a, 1, 0) + (h & 3));
+        mA[a][0] = c.top_at(CT::idx(a, 0, 0) + (h & 3));
+        mA[a][1] = c.top_at(CT::idx(a, 1, 0) + (h & 3));
       });
       sfor<PSO>([&](auto s) {
         f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
         sfor<PTO>([&](auto a) {
           const V x = X[a * PSO + s], xf = xchg<1>(x);
-          acc = mfma4(mA[a][0], q0.cs * x + q0.cf * xf, acc);
-          acc = mfma4(mA[a][1], q1.cs * x + q1.cf * xf, acc);
+          acc = mfma4(mA[a][0], mul2(q0.cs, x, q0.cf, xf), acc);
+          acc = mfma4(mA[a][1], mul2(q1.cs, x, q1.cf, xf), acc);
         });
         sfor<4>([&](auto n) { Z[n * PSO + s] = acc[(int)n]; });
       });
@@ -383,12 +475,12 @@ __device__ __forceinline__ void column_multi(const V (&X)[Cap<TOP, KT, T>::PO * 
       sfor<PTO>([&](auto a) {
         sfor<PSO>([&](auto s) {
           const V x = X[a * PSO + s], xf = xchg<1>(x);
-          const V y0 = q0.cs * x + q0.cf * xf, y1 = q1.cs * x + q1.cf * xf;
+          const V y0 = mul2(q0.cs, x, q0.cf, xf), y1 = mul2(q1.cs, x, q1.cf, xf);
           sfor<PTN>([&](auto n) {
             V& z = Z[n * PSO + s];
-            const V t = mt(std::integral_constant<int, CT::idx(a, 0, n)>{}) * y0;
-            z = (a == 0) ? t : z + t;
-            z += mt(std::integral_constant<int, CT::idx(a, 1, n)>{}) * y1;
+            const V m0 = mt(std::integral_constant<int, CT::idx(a, 0, n)>{});
+            const V m1 = mt(std::integral_constant<int, CT::idx(a, 1, n)>{});
+            z = (a == 0) ? mul2(m0, y0, m1, y1) : fmav(m1, y1, fmav(m0, y0, z));
           });
         });
       });
@@ -397,8 +489,8 @@ __device__ __forceinline__ void column_multi(const V (&X)[Cap<TOP, KT, T>::PO * 
         V y0[PTO], y1[PTO];
         sfor<PTO>([&](auto a) {
           const V x = X[a * PSO + s], xf = xchg<1>(x);
-          y0[a] = q0.cs * x + q0.cf * xf;
-          y1[a] = (CT::kind != K_NONE) ? q1.cs * x + q1.cf * xf : splat<V>(0.0f);
+          y0[a] = mul2<SWAP>(q0.cs, x, q0.cf, xf);
+          y1[a] = (CT::kind != K_NONE) ? mul2<SWAP>(q1.cs, x, q1.cf, xf) : splat<V>(0.0f);
         });
         sfor<PTN>([&](auto n) {
           Z[n * PSO + s] = phi2<CT, n>([&](auto a) { return y0[a]; }, [&](auto a) { return y1[a]; }, mt);
@@ -414,8 +506,8 @@ __device__ __forceinline__ void column_multi(const V (&X)[Cap<TOP, KT, T>::PO * 
       sfor<PTO / 4>([&](auto k) {
         float m[2][4];
         sfor<4>([&](auto u) {
-          m[0][u] = lane_get(c.mtv, CT::idx(4 * k + u, 0, 0) + (h & 3));
-          m[1][u] = lane_get(c.mtv, CT::idx(4 * k + u, 1, 0) + (h & 3));
+          m[0][u] = c.top_at(CT::idx(4 * k + u, 0, 0) + (h & 3));
+          m[1][u] = c.top_at(CT::idx(4 * k + u, 1, 0) + (h & 3));
         });
         A0[k] = pk4(m[0][0], m[0][1], m[0][2], m[0][3]);
         A1[k] = pk4(m[1][0], m[1][1], m[1][2], m[1][3]);
@@ -433,8 +525,8 @@ __device__ __forceinline__ void column_multi(const V (&X)[Cap<TOP, KT, T>::PO * 
     } else if constexpr (CT::kind == K_EQ && PTN == 4) {
       float mA[PTO][2];
       sfor<PTO>([&](auto a) {
-        mA[a][0] = lane_get(c.mtv, CT::idx(a, 0, 0) + (h & 3));
-        mA[a][1] = lane_get(c.mtv, CT::idx(a, 1, 0) + (h & 3));
+        mA[a][0] = c.top_at(CT::idx(a, 0, 0) + (h & 3));
+        mA[a][1] = c.top_at(CT::idx(a, 1, 0) + (h & 3));
       });
       // the emitted bond equals the check's own bit v1: one accumulator per value of v1, unmasked operands,
       // and the lane keeps the one of its own v1 (the other's products never enter)
@@ -448,19 +540,23 @@ __device__ __forceinline__ void column_multi(const V (&X)[Cap<TOP, KT, T>::PO * 
         sfor<4>([&](auto n) { Z[n * PSO + s] = v1 ? acc1[(int)n] : acc0[(int)n]; });
       });
     } else if constexpr (CT::kind == K_EQ) {
-      sfor<PTO>([&](auto a) {
-        V ms[PTN];
+      // both entries of a pair read unconditionally: a lane read cannot sit under a lane-dependent branch
+      auto entry = [&](auto a, auto n) {
+        const V m0 = mt(std::integral_constant<int, CT::idx(a, 0, n)>{});
+        const V m1 = mt(std::integral_constant<int, CT::idx(a, 1, n)>{});
+        return v1 ? m1 : m0;
+      };
+      first_then_rest<PTO>([&](auto a, auto rest) {
         sfor<PTN>([&](auto n) {
-          // both entries read unconditionally: a lane read cannot sit under a lane-dependent branch
-          const V m0 = mt(std::integral_constant<int, CT::idx(a, 0, n)>{});
-          const V m1 = mt(std::integral_constant<int, CT::idx(a, 1, n)>{});
-          ms[n] = v1 ? m1 : m0;
-        });
-        sfor<PSO>([&](auto s) {
-          sfor<PTN>([&](auto n) {
-            const V t = ms[n] * X[a * PSO + s];
-            Z[n * PSO + s] = (a == 0) ? t : Z[n * PSO + s] + t;
-          });
+          const V ma = entry(a, n);
+          if constexpr (rest) {
+            sfor<PSO>([&](auto s) { Z[n * PSO + s] = fmav(ma, X[a * PSO + s], Z[n * PSO + s]); });
+          } else if constexpr (PTO == 1) {
+            sfor<PSO>([&](auto s) { Z[n * PSO + s] = ma * X[s]; });
+          } else {
+            const V mb1 = entry(std::integral_constant<int, 1>{}, n);
+            sfor<PSO>([&](auto s) { Z[n * PSO + s] = mul2(ma, X[s], mb1, X[PSO + s]); });
+          }
         });
       });
     } else {
@@ -479,9 +575,8 @@ __device__ __forceinline__ void column_multi(const V (&X)[Cap<TOP, KT, T>::PO * 
     constexpr int i = j + 1;
     if constexpr (Q0 ^ (i & 1)) {
       if (i <= kp - 2) {
-        const int vi = bit(h, i == 1 ? 0 : i);
-        const int vo = (i + 1 == kp - 1) ? bit(h, 1) : bit(h, i + 2);
-        const QC<V> q = qcoefs(c, T, i, swap, vi ^ vo, bit(h, i + 1), in_abs, out_abs, i == 1 ? sc1 : one);
+        constexpr auto vv = [](int k) { return (1 << pshift(k, i - 1)) | (1 << pshift(k, i + 1)); };
+        const QC<V> q = qcoefs(c, T, i, swap, Parity<C>::of(c, vv, false), bit(h, i + 1), in_abs, out_abs, i == 1 ? sc1 : one);
         sfor<PTN * PSO>([&](auto e) {
           const V zx = xchg<(2 << i)>(Z[e]);
           Z[e] = fmav(q.cf, zx, q.cs * Z[e]);
@@ -492,9 +587,10 @@ __device__ __forceinline__ void column_multi(const V (&X)[Cap<TOP, KT, T>::PO * 
 
   // ---- bottom cap + last site (lane bit 1)
   if (last_q) {
-    const int ho = bit(h, 1), vi = bit(h, pshift(kp, kp - 2));
-    const QC<V> q0 = qcoefs(c, T, kp - 1, swap, vi, ho, in_abs, out_abs, scl);
-    QC<V> q1 = qcoefs(c, T, kp - 1, swap, vi ^ 1, ho, in_abs, out_abs, scl);
+    const int ho = bit(h, 1);
+    constexpr auto vi = [](int k) { return 1 << pshift(k, k - 2); };
+    const QC<V> q0 = qcoefs(c, T, kp - 1, swap, Parity<C>::of(c, vi, false), ho, in_abs, out_abs, scl);
+    QC<V> q1 = qcoefs(c, T, kp - 1, swap, Parity<C>::of(c, vi, true), ho, in_abs, out_abs, scl);
     if (c.geo & GEO_BOT_EDGE) q1.cs = q1.cf = splat<V>(0.0f);
     if constexpr (BF && CB::kind == K_EQ && PSN == 4) {
       // as for the top cap; with kp >= 3 the coefficients depend on lane bit kp-1 >= 2 only (vi)
@@ -504,10 +600,10 @@ __device__ __forceinline__ void column_multi(const V (&X)[Cap<TOP, KT, T>::PO * 
         sfor<PSO / 2>([&](auto k) {
           float ao[2], ap[2];
           sfor<2>([&](auto u) {
-            const float m0 = lane_get(c.mbv, CB::idx(2 * k + u, 0, 0) + (h & 3));
-            const float m1 = lane_get(c.mbv, CB::idx(2 * k + u, 1, 0) + (h & 3));
-            ao[u] = m0 * q0.cs + m1 * q1.cs;
-            ap[u] = m0 * q0.cf + m1 * q1.cf;
+            const float m0 = c.bot_at(CB::idx(2 * k + u, 0, 0) + (h & 3));
+            const float m1 = c.bot_at(CB::idx(2 * k + u, 1, 0) + (h & 3));
+            ao[u] = mul2(m0, q0.cs, m1, q1.cs);
+            ap[u] = mul2(m0, q0.cf, m1, q1.cf);
           });
           A[k] = pk4(ao[0], ap[0], ao[1], ap[1]);
         });
@@ -522,17 +618,17 @@ __device__ __forceinline__ void column_multi(const V (&X)[Cap<TOP, KT, T>::PO * 
       } else {
         bf4 A[PSO / 2];
         sfor<PSO / 2>([&](auto k) {
-          A[k] = pk4(lane_get(c.mbv, CB::idx(2 * k, 0, 0) + (h & 3)), lane_get(c.mbv, CB::idx(2 * k, 1, 0) + (h & 3)),
-                     lane_get(c.mbv, CB::idx(2 * k + 1, 0, 0) + (h & 3)),
-                     lane_get(c.mbv, CB::idx(2 * k + 1, 1, 0) + (h & 3)));
+          A[k] = pk4(c.bot_at(CB::idx(2 * k, 0, 0) + (h & 3)), c.bot_at(CB::idx(2 * k, 1, 0) + (h & 3)),
+                     c.bot_at(CB::idx(2 * k + 1, 0, 0) + (h & 3)),
+                     c.bot_at(CB::idx(2 * k + 1, 1, 0) + (h & 3)));
         });
         sfor<PTN>([&](auto n) {
           f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
           sfor<PSO / 2>([&](auto k) {
             const V z0 = Z[n * PSO + 2 * k], zf0 = xchg<2>(z0);
             const V z1 = Z[n * PSO + 2 * k + 1], zf1 = xchg<2>(z1);
-            acc = mfma4b(A[k], pk4(q0.cs * z0 + q0.cf * zf0, q1.cs * z0 + q1.cf * zf0, q0.cs * z1 + q0.cf * zf1,
-                                   q1.cs * z1 + q1.cf * zf1), acc);
+            acc = mfma4b(A[k], pk4(mul2(q0.cs, z0, q0.cf, zf0), mul2(q1.cs, z0, q1.cf, zf0), mul2(q0.cs, z1, q0.cf, zf1),
+                                   mul2(q1.cs, z1, q1.cf, zf1)), acc);
           });
           sfor<4>([&](auto sp) { Y[n * PSN + sp] = acc[(int)sp]; });
         });
@@ -540,15 +636,15 @@ __device__ __forceinline__ void column_multi(const V (&X)[Cap<TOP, KT, T>::PO * 
     } else if constexpr (CB::kind == K_EQ && PSN == 4) {
       float mB[PSO][2];
       sfor<PSO>([&](auto b) {
-        mB[b][0] = lane_get(c.mbv, CB::idx(b, 0, 0) + (h & 3));
-        mB[b][1] = lane_get(c.mbv, CB::idx(b, 1, 0) + (h & 3));
+        mB[b][0] = c.bot_at(CB::idx(b, 0, 0) + (h & 3));
+        mB[b][1] = c.bot_at(CB::idx(b, 1, 0) + (h & 3));
       });
       sfor<PTN>([&](auto n) {
         f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
         sfor<PSO>([&](auto b) {
           const float z = Z[n * PSO + b], zf = xchg<2>(z);
-          acc = mfma4(mB[b][0], q0.cs * z + q0.cf * zf, acc);
-          acc = mfma4(mB[b][1], q1.cs * z + q1.cf * zf, acc);
+          acc = mfma4(mB[b][0], mul2(q0.cs, z, q0.cf, zf), acc);
+          acc = mfma4(mB[b][1], mul2(q1.cs, z, q1.cf, zf), acc);
         });
         sfor<4>([&](auto sp) { Y[n * PSN + sp] = acc[(int)sp]; });
       });
@@ -556,12 +652,12 @@ __device__ __forceinline__ void column_multi(const V (&X)[Cap<TOP, KT, T>::PO * 
       sfor<PSO>([&](auto b) {
         sfor<PTN>([&](auto n) {
           const V z = Z[n * PSO + b], zf = xchg<2>(z);
-          const V y0 = q0.cs * z + q0.cf * zf, y1 = q1.cs * z + q1.cf * zf;
+          const V y0 = mul2(q0.cs, z, q0.cf, zf), y1 = mul2(q1.cs, z, q1.cf, zf);
           sfor<PSN>([&](auto sp) {
             V& y = Y[n * PSN + sp];
-            const V t = mb(std::integral_constant<int, CB::idx(b, 0, sp)>{}) * y0;
-            y = (b == 0) ? t : y + t;
-            y += mb(std::integral_constant<int, CB::idx(b, 1, sp)>{}) * y1;
+            const V m0 = mb(std::integral_constant<int, CB::idx(b, 0, sp)>{});
+            const V m1 = mb(std::integral_constant<int, CB::idx(b, 1, sp)>{});
+            y = (b == 0) ? mul2(m0, y0, m1, y1) : fmav(m1, y1, fmav(m0, y0, y));
           });
         });
       });
@@ -570,8 +666,8 @@ __device__ __forceinline__ void column_multi(const V (&X)[Cap<TOP, KT, T>::PO * 
         V y0[PSO], y1[PSO];
         sfor<PSO>([&](auto b) {
           const V z = Z[n * PSO + b], zf = xchg<2>(z);
-          y0[b] = q0.cs * z + q0.cf * zf;
-          y1[b] = (CB::kind != K_NONE) ? q1.cs * z + q1.cf * zf : splat<V>(0.0f);
+          y0[b] = mul2<SWAP>(q0.cs, z, q0.cf, zf);
+          y1[b] = (CB::kind != K_NONE) ? mul2<SWAP>(q1.cs, z, q1.cf, zf) : splat<V>(0.0f);
         });
         sfor<PSN>([&](auto sp) {
           Y[n * PSN + sp] = phi2<CB, sp>([&](auto b) { return y0[b]; }, [&](auto b) { return y1[b]; }, mb);
@@ -586,8 +682,8 @@ __device__ __forceinline__ void column_multi(const V (&X)[Cap<TOP, KT, T>::PO * 
       sfor<PSO / 4>([&](auto k) {
         float m[2][4];
         sfor<4>([&](auto u) {
-          m[0][u] = lane_get(c.mbv, CB::idx(4 * k + u, 0, 0) + (h & 3));
-          m[1][u] = lane_get(c.mbv, CB::idx(4 * k + u, 1, 0) + (h & 3));
+          m[0][u] = c.bot_at(CB::idx(4 * k + u, 0, 0) + (h & 3));
+          m[1][u] = c.bot_at(CB::idx(4 * k + u, 1, 0) + (h & 3));
         });
         A0[k] = pk4(m[0][0], m[0][1], m[0][2], m[0][3]);
         A1[k] = pk4(m[1][0], m[1][1], m[1][2], m[1][3]);
@@ -604,8 +700,8 @@ __device__ __forceinline__ void column_multi(const V (&X)[Cap<TOP, KT, T>::PO * 
     } else if constexpr (CB::kind == K_EQ && PSN == 4) {
       float mB[PSO][2];
       sfor<PSO>([&](auto b) {
-        mB[b][0] = lane_get(c.mbv, CB::idx(b, 0, 0) + (h & 3));
-        mB[b][1] = lane_get(c.mbv, CB::idx(b, 1, 0) + (h & 3));
+        mB[b][0] = c.bot_at(CB::idx(b, 0, 0) + (h & 3));
+        mB[b][1] = c.bot_at(CB::idx(b, 1, 0) + (h & 3));
       });
       sfor<PTN>([&](auto n) {
         f4 acc0 = {0.0f, 0.0f, 0.0f, 0.0f}, acc1 = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -617,18 +713,22 @@ __device__ __forceinline__ void column_multi(const V (&X)[Cap<TOP, KT, T>::PO * 
         sfor<4>([&](auto sp) { Y[n * PSN + sp] = v1 ? acc1[(int)sp] : acc0[(int)sp]; });
       });
     } else if constexpr (CB::kind == K_EQ) {
-      sfor<PSO>([&](auto b) {
-        V ms[PSN];
+      auto entry = [&](auto b, auto sp) {
+        const V m0 = mb(std::integral_constant<int, CB::idx(b, 0, sp)>{});
+        const V m1 = mb(std::integral_constant<int, CB::idx(b, 1, sp)>{});
+        return v1 ? m1 : m0;
+      };
+      first_then_rest<PSO>([&](auto b, auto rest) {
         sfor<PSN>([&](auto sp) {
-          const V m0 = mb(std::integral_constant<int, CB::idx(b, 0, sp)>{});
-          const V m1 = mb(std::integral_constant<int, CB::idx(b, 1, sp)>{});
-          ms[sp] = v1 ? m1 : m0;
-        });
-        sfor<PTN>([&](auto n) {
-          sfor<PSN>([&](auto sp) {
-            const V t = ms[sp] * Z[n * PSO + b];
-            Y[n * PSN + sp] = (b == 0) ? t : Y[n * PSN + sp] + t;
-          });
+          const V ma = entry(b, sp);
+          if constexpr (rest) {
+            sfor<PTN>([&](auto n) { Y[n * PSN + sp] = fmav(ma, Z[n * PSO + b], Y[n * PSN + sp]); });
+          } else if constexpr (PSO == 1) {
+            sfor<PTN>([&](auto n) { Y[n * PSN + sp] = ma * Z[n * PSO]; });
+          } else {
+            const V mb1 = entry(std::integral_constant<int, 1>{}, sp);
+            sfor<PTN>([&](auto n) { Y[n * PSN + sp] = mul2(ma, Z[n * PSO], mb1, Z[n * PSO + 1]); });
+          }
         });
       });
     } else {
@@ -645,11 +745,34 @@ __device__ __forceinline__ void column_multi(const V (&X)[Cap<TOP, KT, T>::PO * 
 }
 
 // --------------------------------------------------------------------------------- column, kp == 1
+// Rounding order (mul2) of the transforms of a one-position sweep: step T, emitted top bond y, emitted bottom bond
+// vb, bottom cap index s.
+template <int KT, bool TOP, bool BOT, bool Q00, bool BIASED>
+struct SingleOrder {
+  static constexpr bool swapped(int T, int y, int vb, int s) {
+    if (BIASED || KT == 1) return false;
+    if (T == 0) return TOP ? (y == 1 && vb == 0) : BOT ? (y == 0 && vb == 1) : false;
+    if (T == 1 || (y == 1 && !TOP)) return false;
+    const bool first = vb == 0;
+    if (Q00) {   // qubits at T = 2, 4
+      if (T == 4) return first && (y == 0 || (KT == 6 && BOT));
+      if (KT == 3) return first && y == 0;
+      if (TOP && BOT) return first && (KT == 6 || s == 0);
+      return first || (BOT && !TOP);
+    }
+    // qubits at T = 3, 5
+    if (!TOP && !BOT) return first;
+    if (KT < 6) return false;
+    if (T == 3) return first && (!TOP || !BOT || s == 0);
+    return first && BOT;
+  }
+};
+
 // The single site of the column meets both caps: a qubit sums both emitted bonds (the bottom one is kept
 // as an extra index between the two cap steps), a check emits its own variable on both.
-template <class V, int KT, bool TOP, bool BOT, bool Q00, int T>
+template <class V, int KT, bool TOP, bool BOT, bool Q00, int T, class C>
 __device__ __forceinline__ void column_single(const V (&Xin)[Cap<TOP, KT, T>::PO * Cap<BOT, KT, T>::PO],
-                                              V (&Y)[Cap<TOP, KT, T>::PN * Cap<BOT, KT, T>::PN], Ctx<V>& c,
+                                              V (&Y)[Cap<TOP, KT, T>::PN * Cap<BOT, KT, T>::PN], C& c,
                                               V sc) {
   using CT = Cap<TOP, KT, T>;
   using CB = Cap<BOT, KT, T>;
@@ -659,24 +782,25 @@ __device__ __forceinline__ void column_single(const V (&Xin)[Cap<TOP, KT, T>::PO
   const int swap = ((c.geo & GEO_SWAP0) ? 1 : 0) ^ (T & 1);
   const bool in_abs = (T == 0) && (c.geo & GEO_IN_EDGE);
   const bool out_abs = (T == KT - 1) && (c.geo & GEO_OUT_EDGE);
-  auto mt = [&](auto idx) { return readlane_v(c.mtv, idx); };
-  auto mb = [&](auto idx) { return readlane_v(c.mbv, idx); };
+  using SO = SingleOrder<KT, TOP, BOT, Q00, C::BIASED>;
+  auto mt = [&](auto idx) { return c.top(idx); };
+  auto mb = [&](auto idx) { return c.bot(idx); };
   V X[PTO * PSO];
   sfor<PTO * PSO>([&](auto e) { X[e] = Xin[e] * sc; });   // no qubit transform may follow: scale here
   if constexpr (Q0) {
     const V one = splat<V>(1.0f), zero = splat<V>(0.0f);
     V Z[2][PTN * PSO];   // [emitted bottom bond][np][s]
     sfor<2>([&](auto vb) {
-      QC<V> q0 = qcoefs(c, T, 0, swap, vb, ho, in_abs, out_abs, one);       // emitted top bond 0
-      QC<V> q1 = qcoefs(c, T, 0, swap, vb ^ 1, ho, in_abs, out_abs, one);   // emitted top bond 1
+      QC<V> q0 = qcoefs(c, T, 0, swap, Parity<C>::of(c, [](int) { return 0; }, vb == 1), ho, in_abs, out_abs, one);   // emitted top bond 0
+      QC<V> q1 = qcoefs(c, T, 0, swap, Parity<C>::of(c, [](int) { return 0; }, vb == 0), ho, in_abs, out_abs, one);   // emitted top bond 1
       if (c.geo & GEO_TOP_EDGE) q1.cs = q1.cf = zero;
       if (vb == 1 && (c.geo & GEO_BOT_EDGE)) q0.cs = q0.cf = q1.cs = q1.cf = zero;
       sfor<PSO>([&](auto s) {
         V y0[PTO], y1[PTO];
         sfor<PTO>([&](auto a) {
           const V x = X[a * PSO + s], xf = xchg<1>(x);
-          y0[a] = q0.cs * x + q0.cf * xf;
-          y1[a] = q1.cs * x + q1.cf * xf;
+          y0[a] = mul2<SO::swapped(T, 0, vb, s)>(q0.cs, x, q0.cf, xf);
+          y1[a] = mul2<SO::swapped(T, 1, vb, s)>(q1.cs, x, q1.cf, xf);
         });
         sfor<PTN>([&](auto n) {
           Z[vb][n * PSO + s] = phi2<CT, n>([&](auto a) { return y0[a]; }, [&](auto a) { return y1[a]; }, mt);
@@ -713,16 +837,16 @@ __device__ __forceinline__ void column_single(const V (&Xin)[Cap<TOP, KT, T>::PO
 // ------------------------------------------------------------------------------------------ the sweep
 // Power-of-two rescale of a state with squared norm ss: returns the factor to apply and accumulates its
 // exponent.
-template <class V>
-__device__ __forceinline__ V pow2_scale(float ss, Ctx<V>& c) {
+template <class V, class C>
+__device__ __forceinline__ V pow2_scale(float ss, C& c) {
   const int e = (ss > 0.0f && ss < INFINITY) ? (__builtin_amdgcn_frexp_expf(ss) >> 1) : 0;
   c.exp2 += e;
   return V{__builtin_amdgcn_ldexpf(1.0f, -e)};
 }
 
 // Absorb columns T .. KT-1 into the state X (pending scale sc); returns the final state of this lane.
-template <class V, int KT, bool TOP, bool BOT, bool SINGLE, bool Q00, bool BF, int T>
-__device__ __forceinline__ V run(const V (&X)[Cap<TOP, KT, T>::PO * Cap<BOT, KT, T>::PO], Ctx<V>& c, V sc) {
+template <class V, int KT, bool TOP, bool BOT, bool SINGLE, bool Q00, bool BF, int T, class C>
+__device__ __forceinline__ V run(const V (&X)[Cap<TOP, KT, T>::PO * Cap<BOT, KT, T>::PO], C& c, V sc) {
   constexpr int NY = Cap<TOP, KT, T>::PN * Cap<BOT, KT, T>::PN;
   V Y[NY];
   if constexpr (SINGLE) column_single<V, KT, TOP, BOT, Q00, T>(X, Y, c, sc);
@@ -731,7 +855,7 @@ __device__ __forceinline__ V run(const V (&X)[Cap<TOP, KT, T>::PO * Cap<BOT, KT,
     if constexpr (T & 1) {
       float ss = 0.0f;
       sfor<NY>([&](auto e) { ss += tof(Y[e]) * tof(Y[e]); });
-      return run<V, KT, TOP, BOT, SINGLE, Q00, BF, T + 1>(Y, c, pow2_scale(wave_sum(ss), c));
+      return run<V, KT, TOP, BOT, SINGLE, Q00, BF, T + 1>(Y, c, pow2_scale<V>(wave_sum<C::LB>(ss), c));
     } else {
       return run<V, KT, TOP, BOT, SINGLE, Q00, BF, T + 1>(Y, c, splat<V>(1.0f));
     }
@@ -742,8 +866,8 @@ __device__ __forceinline__ V run(const V (&X)[Cap<TOP, KT, T>::PO * Cap<BOT, KT,
 
 // The whole sweep from the entering state x0 (one value per lane). SINGLE: one position across
 // (kp == 1); Q00: the first site of the first column is a qubit; BF: the middle-site contractions in BF16.
-template <class V, int KT, bool TOP, bool BOT, bool SINGLE, bool Q00, bool BF>
-__device__ __forceinline__ V sweep(V x0, Ctx<V>& c) {
+template <class V, int KT, bool TOP, bool BOT, bool SINGLE, bool Q00, bool BF, class C>
+__device__ __forceinline__ V sweep(V x0, C& c) {
   const V X[1] = {x0};
   return run<V, KT, TOP, BOT, SINGLE, Q00, BF, 0>(X, c, splat<V>(1.0f));
 }

@@ -362,3 +362,34 @@ def test_residual_gate_against_oracle(dev):
     assert err.max() < 2e-3
     assert np.all(np.abs(got["iters"] - ref["iters"]) <= 3)
     _decisions_agree(got["coset"], ref["loglik"], ref["coset"], ref["delta"], 1e-2)
+
+
+# widths 1 .. 6 across a sweep (block and remainder): 2^kp lanes per sweep, 64 >> max(kp, 3) jobs per wavefront. The
+# batch is odd, so that the last wavefront of an 8-job class is half empty and jobs of one wavefront converge apart.
+@pytest.mark.parametrize("d,k,precision,extra", [
+    (5, 2, 1, {}),                      # kp 2 (and 1) on the wavefront kernels
+    (6, 3, 0, {}), (7, 3, 1, {}),       # kp 3, remainders 2 and 1
+    (6, 4, 0, {}), (7, 4, 1, {}),       # kp 4, remainders 3 and 1
+    (6, 5, 0, {}), (7, 5, 1, {}),       # kp 5, remainders 1 and 3
+    (6, 6, 0, {}), (9, 6, 1, {}),       # kp 6, remainder 5
+    (7, 3, 0, {"gate": 1e-4}), (6, 4, 0, {"noise": True}), (6, 3, 0, {"noise": True}),
+])
+def test_packed_jobs_equal_single_decodes(dev, d, k, precision, extra):
+    """Every sweep class runs several jobs per wavefront where its width leaves lanes free; a job's result does
+    not depend on its neighbours: a ragged batch equals each of its syndromes decoded alone, bitwise, through
+    early exits at different iterations, skipped updates (gate) and biased noise."""
+    import torch
+    import paper_2402_04834_amd as bbp
+    p, b = 0.12, 5
+    _, syn = workload.make_batch(d, p, b, workload="test", p_index=700 + 10 * d + k)
+    s = torch.from_numpy(syn).to(dev)
+    noise = workload.biased_probs(p, 3.0) if extra.get("noise") else p
+    opts = bbp.default_opts(block=k, chi=32, max_iter=20, precision=precision, gate=extra.get("gate", 0.0))
+    _say(f"[packed] d={d} k={k} precision {precision} {extra}")
+    whole, _, _ = bbp.decode_groups([(d, noise, s)], opts, messages=True)
+    iters = whole[0]["iters"].cpu().numpy()
+    for i in range(b):
+        one, _, _ = bbp.decode_groups([(d, noise, s[i:i + 1])], opts, messages=True)
+        for key in ("loglik", "delta", "iters", "coset", "correction", "messages"):
+            assert torch.equal(whole[0][key][i:i + 1].view(torch.uint8), one[0][key].view(torch.uint8)), (i, key)
+    assert iters.min() < iters.max()   # jobs of one wavefront left at different iterations
