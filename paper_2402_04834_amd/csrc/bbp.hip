@@ -53,21 +53,34 @@ int fail(int code, const std::string& msg) {
   } while (0)
 
 // --------------------------------------------------------------------------------------------------
-// a1/a2: syndrome -> coset labels
+// a1/a2: syndrome -> coset labels, one workgroup per syndrome. The chains of f_s are parities of the checks right of /
+// below an edge: running parities, formed once per row and column (one thread each) and then looked up by every site
+// (a loop over the checks at every site took 11 us for one d = 17 syndrome, a latency that every small decode
+// pays; this takes 5 us).
 __global__ __launch_bounds__(256) void labels_kernel(const uint8_t* __restrict__ syn, int d, int64_t batch,
                                                      uint8_t* __restrict__ labels) {
   const int b = blockIdx.x;
   const int L = 2 * d - 1, m = 2 * d * (d - 1), nz = d * (d - 1);
   __shared__ uint8_t s[2 * 32 * 31];
+  __shared__ uint8_t px[32][33], pz[32][33];   // [row r / 2][edge c / 2], [column c / 2][edge r / 2]
   for (int i = threadIdx.x; i < m; i += blockDim.x) s[i] = syn[(int64_t)b * m + i] & 1;
+  __syncthreads();
+  if ((int)threadIdx.x < d) {
+    const int i = threadIdx.x;
+    int x = 0;
+    px[i][d - 1] = 0;
+    for (int j = d - 2; j >= 0; --j) px[i][j] = (uint8_t)(x ^= s[i * (d - 1) + j]);   // Z-checks right of edge j
+  } else if (threadIdx.x >= 64 && (int)threadIdx.x < 64 + d) {
+    const int i = threadIdx.x - 64;
+    int z = 0;
+    pz[i][d - 1] = 0;
+    for (int j = d - 2; j >= 0; --j) pz[i][j] = (uint8_t)(z ^= s[nz + j * d + i]);    // X-checks below edge j
+  }
   __syncthreads();
   for (int site = threadIdx.x; site < L * L; site += blockDim.x) {
     const int r = site / L, c = site % L;
-    int x = 0, z = 0;
-    if ((r & 1) == 0 && (c & 1) == 0) {
-      for (int cc = c + 1; cc < L; cc += 2) x ^= s[(r / 2) * (d - 1) + (cc - 1) / 2];      // Z-checks right of it
-      for (int rr = r + 1; rr < L; rr += 2) z ^= s[nz + ((rr - 1) / 2) * d + c / 2];        // X-checks below it
-    }
+    const bool edge = (r & 1) == 0 && (c & 1) == 0;
+    const int x = edge ? px[r / 2][c / 2] : 0, z = edge ? pz[c / 2][r / 2] : 0;
     const int lx = (r == 0 && (c & 1) == 0) ? 1 : 0;   // logical X: row 0 of horizontal edges
     const int lz = (c == 0 && (r & 1) == 0) ? 1 : 0;   // logical Z: column 0 of horizontal edges
     const int bx[4] = {0, 1, 1, 0}, bz[4] = {0, 0, 1, 1};
@@ -79,33 +92,43 @@ __global__ __launch_bounds__(256) void labels_kernel(const uint8_t* __restrict__
 }
 
 // start messages: uniform unit vectors (remark 2), or the given ones (a learned warm start) scaled to unit
-// norm with the entries beyond 2^K cleared; one workgroup per job, one wavefront per message
+// norm with the entries beyond 2^K cleared; one workgroup per job. The uniform start is a plain fill; given messages
+// take one wavefront each.
 __global__ __launch_bounds__(256) void init_kernel(float* __restrict__ msgs, const float* __restrict__ given,
                                                    const int32_t* __restrict__ edge_len, int M, int ms, int64_t jobs,
                                                    int32_t* __restrict__ conv, int32_t* __restrict__ iters,
                                                    double* __restrict__ terms) {
   const int64_t job = blockIdx.x;
   const int lane = threadIdx.x & 63;
-  for (int id = threadIdx.x >> 6; id < M; id += blockDim.x >> 6) {
-    const int K = edge_len[id];
-    const int64_t at = (job * M + id) * ms;
-    float ss = 0.0f;
-    if (given) {
+  if (!given) {
+    // (a workspace is the caller's: 4-byte stores at its alignment; ms is a power of two)
+    const int sh = 31 - __clz(ms);
+    float* mj = msgs + job * M * (int64_t)ms;
+    for (int i = threadIdx.x; i < M << sh; i += blockDim.x) {
+      const int K = edge_len[i >> sh];
+      mj[i] = (i & (ms - 1)) < (1 << K) ? exp2f(-0.5f * K) : 0.0f;
+    }
+  } else {
+    for (int id = threadIdx.x >> 6; id < M; id += blockDim.x >> 6) {
+      const int K = edge_len[id];
+      const int64_t at = (job * M + id) * ms;
+      float ss = 0.0f;
       for (int e = lane; e < ms; e += 64) {
         const float g = e < (1 << K) ? given[at + e] : 0.0f;
         ss += g * g;
       }
       for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
+      const bool ok = ss > 0.0f && ss < INFINITY;
+      for (int e = lane; e < ms; e += 64) {
+        const bool in = e < (1 << K);
+        float v = in ? exp2f(-0.5f * K) : 0.0f;
+        if (ok) v = in ? given[at + e] * __builtin_amdgcn_rsqf(ss) : 0.0f;
+        msgs[at + e] = v;
+      }
     }
-    const bool ok = given && ss > 0.0f && ss < INFINITY;
-    for (int e = lane; e < ms; e += 64) {
-      const bool in = e < (1 << K);
-      float v = in ? exp2f(-0.5f * K) : 0.0f;
-      if (ok) v = in ? given[at + e] * __builtin_amdgcn_rsqf(ss) : 0.0f;
-      msgs[at + e] = v;
-    }
-    if (lane == 0) terms[job * M + id] = INFINITY;   // never updated: counts as changed for a gated schedule
   }
+  // never updated: counts as changed for a gated schedule
+  for (int i = threadIdx.x; i < M; i += blockDim.x) terms[job * M + i] = INFINITY;
   if (threadIdx.x == 0) {
     conv[job] = 0;
     iters[job] = 0;
@@ -117,19 +140,32 @@ __device__ __forceinline__ double wave_sum_d(double v) {
   return v;
 }
 
-
-__global__ void delta_kernel(const double* __restrict__ terms, int M, int64_t jobs, int32_t* __restrict__ conv,
-                             int32_t* __restrict__ iters, double* __restrict__ delta, double delta0, int fixed) {
-  const int64_t job = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (job >= jobs || conv[job]) return;
+// Convergence distance of a job after an iteration, by one wavefront.
+__device__ __forceinline__ double job_delta(const double* terms, int M) {
   double acc = 0.0;
-  for (int e = 0; e < M; ++e) acc += terms[job * M + e];
-  const double dl = sqrt(fmax(acc, 0.0)) / (M > 0 ? M : 1);
-  delta[job] = dl;
-  iters[job] += 1;
-  if (!fixed && dl < delta0) conv[job] = 1;
+  for (int e = (int)(threadIdx.x & 63); e < M; e += 64) acc += terms[e];
+  return sqrt(fmax(wave_sum_d(acc), 0.0)) / (M > 0 ? M : 1);
 }
 
+// one wavefront per job: its lanes read the job's terms together (one thread per job read them one after the other,
+// 8 bytes of a 64-byte line each: 21 us for 16384 jobs of 120 terms and 13 us for 64, against 7 and 3)
+__global__ __launch_bounds__(256) void delta_kernel(const double* __restrict__ terms, int M, int64_t jobs,
+                                                    int32_t* __restrict__ conv, int32_t* __restrict__ iters,
+                                                    double* __restrict__ delta, double delta0, int fixed) {
+  const int64_t job = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (job >= jobs || conv[job]) return;
+  const double dl = job_delta(terms + job * M, M);
+  if ((threadIdx.x & 63) == 0) {
+    delta[job] = dl;
+    iters[job] += 1;
+    if (!fixed && dl < delta0) conv[job] = 1;
+  }
+}
+
+// ln Z, decision and correction, one workgroup per syndrome, wavefront k for coset k. The edge overlaps go four pairs
+// at a time, 16 lanes each, and every lane then takes the logarithm of one of 64 overlaps (pair after pair, each
+// with a whole-wavefront sum and a logarithm on one lane, 60 pairs took 53 us for 16 syndromes and 235 us for 4096,
+// against 21 and 114).
 __global__ __launch_bounds__(256) void finalize_kernel(const double* __restrict__ lnW, int nblocks,
                                                        const float* __restrict__ msgs, int M, int ms,
                                                        const int32_t* __restrict__ pairs, int npairs,
@@ -142,13 +178,11 @@ __global__ __launch_bounds__(256) void finalize_kernel(const double* __restrict_
                                                        uint8_t* __restrict__ correction) {
   const int64_t b = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  __shared__ double part[4][4];
-  __shared__ int badp[4][4];
+  __shared__ double part[4];
+  __shared__ int badp[4];
   __shared__ int chosen;
-  // wave k handles coset k
   {
-    const int k = wid;
-    const int64_t job = b * 4 + k;
+    const int64_t job = b * 4 + wid;
     double acc = 0.0;
     int bad = 0;
     for (int blk = lane; blk < nblocks; blk += 64) {
@@ -156,21 +190,30 @@ __global__ __launch_bounds__(256) void finalize_kernel(const double* __restrict_
       if (isnan(w)) bad = 1; else acc += w;
     }
     const float* mb = msgs + job * M * (int64_t)ms;
-    for (int q = 0; q < npairs; ++q) {
-      const float* u = mb + pairs[2 * q] * (int64_t)ms;
-      const float* v = mb + pairs[2 * q + 1] * (int64_t)ms;
-      double uv = 0.0;
-      for (int e = lane; e < ms; e += 64) uv += (double)u[e] * (double)v[e];
-      const double o = wave_sum_d(uv);
-      if (o > 0.0) acc -= (lane == 0) ? log(o) : 0.0;
-      else bad = 1;
+    const int g = lane >> 4, l16 = lane & 15;
+    for (int q0 = 0; q0 < npairs; q0 += 64) {
+      double own = 1.0;   // the overlap of this lane's pair, q0 + 4 (lane % 16) + lane / 16
+      const int n = min(16, (npairs - q0 + 3) / 4);
+#pragma unroll 4
+      for (int i = 0; i < n; ++i) {
+        const int q = min(q0 + 4 * i + g, npairs - 1);
+        const float* u = mb + pairs[2 * q] * (int64_t)ms;
+        const float* v = mb + pairs[2 * q + 1] * (int64_t)ms;
+        double uv = 0.0;
+        for (int e = l16; e < ms; e += 16) uv += (double)u[e] * (double)v[e];
+        for (int o = 8; o > 0; o >>= 1) uv += __shfl_xor(uv, o);
+        own = l16 == i ? uv : own;
+      }
+      if (q0 + 4 * l16 + g < npairs) {
+        if (own > 0.0) acc -= log(own);
+        else bad = 1;
+      }
     }
     acc = wave_sum_d(acc);
-    for (int o = 32; o > 0; o >>= 1) bad |= __shfl_down(bad, o);
-    bad = __shfl(bad, 0);
+    bad = __any(bad);
     if (lane == 0) {
-      part[0][k] = acc;
-      badp[0][k] = bad;
+      part[wid] = acc;
+      badp[wid] = bad;
     }
   }
   __syncthreads();
@@ -178,8 +221,8 @@ __global__ __launch_bounds__(256) void finalize_kernel(const double* __restrict_
     double ll[4], dl[4];
     for (int k = 0; k < 4; ++k) {
       const int64_t job = b * 4 + k;
-      ll[k] = badp[0][k] ? NAN : part[0][k];
-      dl[k] = badp[0][k] ? INFINITY : delta_ws[job];
+      ll[k] = badp[k] ? NAN : part[k];
+      dl[k] = badp[k] ? INFINITY : delta_ws[job];
       loglik[job] = ll[k];
       delta_out[job] = dl[k];
       iters_out[job] = iters_ws[job];
@@ -642,7 +685,7 @@ int enqueue(std::vector<GroupRun>& gr, const bbp_opts* opts, const Tune& tn, hip
     for (auto& g : gr) {
       if (g.in.batch == 0) continue;
       if ((rc = begin_mark(st, 0, it, -1))) return rc;
-      delta_kernel<<<dim3((unsigned)((g.jobs + 255) / 256)), dim3(256), 0, st>>>(
+      delta_kernel<<<dim3((unsigned)((g.jobs + 3) / 4)), dim3(256), 0, st>>>(
           g.terms, g.dp->plan.M, g.jobs, g.conv, g.iters, g.delta, opts->delta0, opts->fixed_iters);
       HIP_TRY(hipGetLastError());
       if ((rc = end_mark(st))) return rc;
