@@ -233,9 +233,10 @@ typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
 // from L2 (8 bytes per clock and CU with these tiles). A workgroup of four waves computes 128 rows x all NT output
 // channels (2 x 2 waves of 64 x NT/2), so that one 16-deep stage holds 64 (NT = 128) MFMAs of 32 cycles per
 // wave against 8 KB + NT * 64 bytes of loads; the stage after next is in flight in registers while a stage is
-// multiplied out of one of two LDS buffers, one barrier per stage. Both LDS tiles are k-contiguous with a stride of
-// 20 floats (16 rows cover all 64 banks), so that a lane takes its four k of a stage with one 16-byte read: MFMA
-// step ks multiplies k = 4 (lane / 16) + ks, any order of k being as good. The gather is a raw buffer load whose
+// multiplied out of one of two LDS buffers, one barrier per stage. Both LDS tiles hold a row's 16 k in the order 0, 4,
+// 8, 12, 1, 5, ..., rows 20 floats apart (16 rows cover all 64 banks), so that a lane takes its four k of a stage, lane
+// / 16 + 4 ks at MFMA step ks, with one 16-byte read and every sum still runs over k in order (an activation's sign, and
+// with it the gradient's ReLU mask, then does not depend on the tiling). The gather is a raw buffer load whose
 // offset lies past the buffer for taps that leave the grid (reads zeros, no branch); the buffer starts at the
 // tile's first neighbour row, so offsets stay below 2^31 whatever the batch. The weights are the MFMA's first operand:
 // a lane ends with four consecutive output channels of a row, one 16-byte store.
@@ -315,12 +316,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void c
   };
   auto store = [&](const int buf) {
 #pragma unroll
-    for (int u = 0; u < 2; ++u) *(u32x4*)&As[buf][((tid >> 2) + 64 * u) * RS + 4 * kq] = ra[u];
+    for (int u = 0; u < 2; ++u) {
+      const f4 v = __builtin_bit_cast(f4, ra[u]);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) As[buf][((tid >> 2) + 64 * u) * RS + 4 * j + kq] = v[j];
+    }
 #pragma unroll
     for (int u = 0; u < UB; ++u) {
       const int q = tid + 256 * u;
       const int n = MODE == G_FWD ? q % NT : q >> 2, k4 = MODE == G_FWD ? q / NT : q & 3;
-      if ((NT * 4) % 256 == 0 || q < NT * 4) *(f4*)&Bs[buf][n * RS + 4 * k4] = rb[u];
+      if ((NT * 4) % 256 == 0 || q < NT * 4) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) Bs[buf][n * RS + 4 * j + k4] = rb[u][j];
+      }
     }
   };
   f4 acc[4][NJ];
