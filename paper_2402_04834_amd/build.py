@@ -1,7 +1,7 @@
 """Build the HIP library libbbp.so in-tree for gfx950 (hipcc; no JIT cache).
 
 The block-sweep kernels are instantiated per sweep length and width in separate objects (sweep_kernel.hip compiled
-with BBP_KT, BBP_KP = 1..6); all objects compile in parallel and are linked into one shared library.
+with BBP_KT, BBP_KP = 1..6), the fused small-batch kernels per block and remainder size; all objects compile in parallel and are linked into one shared library.
 """
 from __future__ import annotations
 
@@ -25,10 +25,16 @@ FLAGS = [
     "-Wno-unused-command-line-argument",
 ]
 
+# block and remainder sizes of the fused kernels (FUSED_SHAPES of sweep_launch.hpp)
+FUSED_SHAPES = [(6, 1), (6, 3), (6, 5), (5, 0), (5, 1), (5, 2), (5, 3), (5, 4), (4, 1), (4, 3), (3, 0), (3, 1), (3, 2)]
+
 # (source, extra flags, object name), the longest compiles first
 UNITS = [("trunc_sweep.hip", [], "trunc_sweep.o"), ("bmps.hip", [], "bmps.o"), ("warm.hip", [], "warm.o")] + [
     ("sweep_kernel.hip", [f"-DBBP_KT={t}", f"-DBBP_KP={p}"], f"sweep_{t}x{p}.o")
     for t in range(6, 0, -1) for p in range(6, 0, -1)
+] + [
+    ("fused_sweep.hip", [f"-DBBP_K={k}", f"-DBBP_R={r}", f"-DBBP_BF={b}"], f"fused_{k}_{r}_{b}.o")
+    for k, r in FUSED_SHAPES for b in ((0, 1) if k >= 5 else (0,))
 ] + [("bbp.hip", [], "bbp.o"), ("small_sweep.hip", [], "small_sweep.o"), ("plan.cpp", [], "plan.o")]
 
 

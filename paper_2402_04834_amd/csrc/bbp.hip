@@ -31,6 +31,7 @@
 #include "geom.hpp"
 #include "plan.hpp"
 #include "bmps_launch.hpp"
+#include "sweep_item.hpp"
 #include "sweep_launch.hpp"
 
 using bbp::SweepDesc;
@@ -135,18 +136,6 @@ __global__ __launch_bounds__(256) void init_kernel(float* __restrict__ msgs, con
   }
 }
 
-__device__ __forceinline__ double wave_sum_d(double v) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  return v;
-}
-
-// Convergence distance of a job after an iteration, by one wavefront.
-__device__ __forceinline__ double job_delta(const double* terms, int M) {
-  double acc = 0.0;
-  for (int e = (int)(threadIdx.x & 63); e < M; e += 64) acc += terms[e];
-  return sqrt(fmax(wave_sum_d(acc), 0.0)) / (M > 0 ? M : 1);
-}
-
 // one wavefront per job: its lanes read the job's terms together (one thread per job read them one after the other,
 // 8 bytes of a 64-byte line each: 21 us for 16384 jobs of 120 terms and 13 us for 64, against 7 and 3)
 __global__ __launch_bounds__(256) void delta_kernel(const double* __restrict__ terms, int M, int64_t jobs,
@@ -154,7 +143,7 @@ __global__ __launch_bounds__(256) void delta_kernel(const double* __restrict__ t
                                                     double* __restrict__ delta, double delta0, int fixed) {
   const int64_t job = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (job >= jobs || conv[job]) return;
-  const double dl = job_delta(terms + job * M, M);
+  const double dl = bbp::job_delta(terms + job * M, M);
   if ((threadIdx.x & 63) == 0) {
     delta[job] = dl;
     iters[job] += 1;
@@ -209,7 +198,7 @@ __global__ __launch_bounds__(256) void finalize_kernel(const double* __restrict_
         else bad = 1;
       }
     }
-    acc = wave_sum_d(acc);
+    acc = bbp::wave_sum_d(acc, 64);
     bad = __any(bad);
     if (lane == 0) {
       part[wid] = acc;
@@ -318,7 +307,42 @@ hipError_t bbp::launch_sweeps(int cls, hipStream_t st, const SweepArgs& a) {
   });
 }
 
+template <int... I>
+static hipError_t fused_by_shape(int code, std::integer_sequence<int, I...>, unsigned groups, int waves, hipStream_t st,
+                                 const bbp::FusedArgs& a) {
+  hipError_t e = hipErrorInvalidValue;
+  // (below five steps nothing runs on the matrix cores: one instantiation for both precisions)
+  ((I == code ? (void)(e = bbp::launch_fused_of<bbp::FUSED_SHAPES[I / 2][0], bbp::FUSED_SHAPES[I / 2][1],
+                                                (bbp::FUSED_SHAPES[I / 2][0] >= 5 ? I % 2 : 0)>(groups, waves, st, a))
+              : (void)0),
+   ...);
+  return e;
+}
+
+hipError_t bbp::launch_fused(int shape, bool bf16, unsigned groups, int waves, hipStream_t st, const FusedArgs& a) {
+  return fused_by_shape(2 * shape + (bf16 ? 1 : 0), std::make_integer_sequence<int, 2 * NUM_FUSED_SHAPES>{}, groups, waves,
+                        st, a);
+}
+
 namespace {
+
+// Index into FUSED_SHAPES of a plan's block sizes, -1 where the fused kernels do not serve it: truncating sweeps,
+// blocks of other sizes, more than two sizes.
+int fused_shape(const bbp::Plan& p) {
+  if (p.trunc_sweeps > 0) return -1;
+  int hi = 0, lo = 0;
+  for (const std::vector<int>* v : {&p.rowsz, &p.colsz})
+    for (int n : *v) hi = std::max(hi, n);
+  for (const std::vector<int>* v : {&p.rowsz, &p.colsz})
+    for (int n : *v)
+      if (n != hi) {
+        if (lo != 0 && n != lo) return -1;
+        lo = n;
+      }
+  for (int i = 0; i < bbp::NUM_FUSED_SHAPES; ++i)
+    if (bbp::FUSED_SHAPES[i][0] == hi && bbp::FUSED_SHAPES[i][1] == lo) return i;
+  return -1;
+}
 
 struct DevPlan {
   bbp::Plan plan;
@@ -543,6 +567,66 @@ struct Mark {
   std::vector<std::pair<int, double>> work;   // (group, per-job flops of the group's sweeps of this class)
 };
 
+// How the sweeps of a decode are launched: per class and round (sweep_kernel.hip and the others), all classes of a
+// round at once, or everything of a job in one workgroup (fused_sweep.hip). Results do not depend on it.
+enum class Route { classes, rounds, loop };
+
+// The route with the smallest estimated time. The estimates (microseconds for a decode of up to 20 iterations, whose
+// number scales all three) are straight lines through decodes timed at d = 3 .. 25, blocks 3 .. 6, 1 to 400 syndromes:
+//   classes  4.6 for every class launch of an iteration and 20 of them, plus a slope per wavefront of a round's
+//            launches of unpacked width (packed widths carry several jobs each): the launches, until the chip fills;
+//   rounds   a start per set of groups with equal block sizes (its own launches), plus a steeper slope per (job, sweep):
+//            the waves of one launch run different code, one job each, so they use the chip worse;
+//   loop     60 plus, for every 256 jobs (one workgroup per CU) of a set, a cost per sweep of a round: 16 wavefronts
+//            share them.
+// The slopes grow with the block width; plans with a remainder of one site at width 6 run twice as long in the fused
+// kernels (their one-position sweeps of six steps spill at 128 registers). For a graph, whose replays on several
+// streams overlap, only a third of the waiting counts (d = 7 and 13 mixed, 32 syndromes, three graphs in turn: 744 us
+// a decode by classes, 1297 by rounds, against 1870 and 1441 eager). Measured around the lines: d = 5, 3 x 3, 1
+// syndrome: 634 / 235 / 76 us (classes / rounds / loop); d = 17, 6 x 6, BF16: 1647 / 502 / 1325 for 1 syndrome,
+// 1750 / 972 / 1350 for 16, 2163 / 2310 / 1505 for 64, 2738 / 3986 / 2942 for 128.
+Route choose_route(const std::vector<GroupRun>& gr, const bbp_opts* opts) {
+  if (opts->block_rows <= 2 && opts->block_cols <= 2 && opts->precision == 0) return Route::classes;   // small_sweep.hip
+  static const double round_start[7] = {0, 0, 0, 280.0, 300.0, 330.0, 420.0};
+  static const double round_slope[7] = {0, 0, 0, 0.027, 0.031, 0.040, 0.125};
+  static const double loop_slope[7] = {0, 0, 0, 6.4, 8.1, 12.0, 23.0};
+  static const double class_slope[7] = {0, 0, 0, 0.004, 0.006, 0.013, 0.040};
+  struct Set {
+    double waves = 0, jobs = 0, sweeps = 0;
+    int wide = 0, odd = 0;
+  };
+  std::map<int, Set> sets;
+  std::map<int, int> classes[2];
+  double t_classes = 100.0, t_rounds = 0.0, t_loop = 0.0;
+  for (const GroupRun& g : gr) {
+    if (g.in.batch == 0) continue;
+    const bbp::Plan& p = g.dp->plan;
+    const int shape = g.biased ? -1 : fused_shape(p);
+    if (shape < 0 || g.jobs * (int64_t)std::max<size_t>(1, p.M) >= (int64_t)1 << 24) return Route::classes;
+    Set& s = sets[shape];
+    const double n = (double)std::max(p.round[0].size(), p.round[1].size());
+    s.waves += g.jobs * n;
+    s.jobs += g.jobs;
+    s.sweeps = std::max(s.sweeps, n);
+    s.wide = bbp::FUSED_SHAPES[shape][0];
+    s.odd = s.wide == 6 && bbp::FUSED_SHAPES[shape][1] == 1;
+    for (int c = 0; c < 2; ++c)
+      for (const ClassRun& r : g.dp->runs[c]) classes[c][r.cls] = 1;
+  }
+  // waiting (launches, a round's latency) overlaps with other replays where a program keeps several graphs in flight
+  const double alone = opts->graph ? 1.0 / 3.0 : 1.0;
+  t_classes = alone * (t_classes + 20 * 4.6 * (double)(classes[0].size() + classes[1].size()));
+  for (const auto& kv : sets) {
+    const Set& s = kv.second;
+    const double per = loop_slope[s.wide] * (s.odd ? 1.7 : 1.0) * s.sweeps;
+    t_classes += class_slope[s.wide] * s.waves;
+    t_rounds += alone * round_start[s.wide] + round_slope[s.wide] * (s.odd ? 2.0 : 1.0) * s.waves;
+    t_loop += std::max(alone * (60.0 + per * std::ceil(s.jobs / 256.0)), per * s.jobs / 256.0);
+  }
+  if (t_loop <= t_rounds && t_loop <= t_classes) return Route::loop;
+  return t_rounds <= t_classes ? Route::rounds : Route::classes;
+}
+
 // Enqueue the whole decode of the groups on st (and the auxiliary streams of the tune).
 int enqueue(std::vector<GroupRun>& gr, const bbp_opts* opts, const Tune& tn, hipStream_t st,
             Aux* aux, std::vector<Mark>* marks) {
@@ -588,6 +672,32 @@ int enqueue(std::vector<GroupRun>& gr, const bbp_opts* opts, const Tune& tn, hip
     HIP_TRY(hipGetLastError());
     if ((rc = end_mark(st))) return rc;
   }
+  // a group's state as the sweep kernels take it
+  auto fill = [&](bbp::SweepGroup& G, const GroupRun& g, int64_t item0) {
+    G.labels = g.labels;
+    G.msgs = g.msgs;
+    G.terms = g.terms;
+    G.conv = g.conv;
+    G.lnW = g.lnw;
+    G.jobs = g.jobs;
+    G.item0 = item0;
+    G.d = g.in.d;
+    G.M = g.dp->plan.M;
+    G.nblocks = g.dp->plan.nblocks;
+    G.p00 = 1.0f - (float)g.in.p;
+    G.pe = (float)g.in.p / 3.0f;
+    G.pdev = g.in.p_dev;
+    G.biased = g.biased;
+    for (int k = 0; k < 4; ++k) G.pi[k] = (float)g.in.noise[k];
+    if (g.biased) {
+      for (int k = 0; k < 4; ++k) G.pq[k] = g.in.noise[k];
+    } else {
+      G.pq[0] = 1.0 - g.in.p;
+      G.pq[1] = G.pq[2] = G.pq[3] = g.in.p / 3.0;
+    }
+    G.mstride = g.dp->plan.mstride;
+    G.chi = g.opts.chi;
+  };
   const int S = std::max(1, std::min(tn.streams, 4));
   auto streams_of = [&](int i) -> hipStream_t { return (i % S) == 0 ? st : aux->s[(i % S) - 1]; };
   // one colour round (list 0 / 1) or the closing sweeps (list 2): one launch per class over all groups
@@ -626,31 +736,9 @@ int enqueue(std::vector<GroupRun>& gr, const bbp_opts* opts, const Tune& tn, hip
         const GroupRun& g = gr[members[k].first];
         const ClassRun& r = *members[k].second;
         bbp::SweepGroup& G = sa.g[k];
+        fill(G, g, items);
         G.sweeps = ((list == 2) ? g.dp->bethe : g.dp->round[list]) + r.first;
-        G.labels = g.labels;
-        G.msgs = g.msgs;
-        G.terms = g.terms;
-        G.conv = g.conv;
-        G.lnW = g.lnw;
-        G.jobs = g.jobs;
-        G.item0 = items;
         G.count = r.count;
-        G.d = g.in.d;
-        G.M = g.dp->plan.M;
-        G.nblocks = g.dp->plan.nblocks;
-        G.p00 = 1.0f - (float)g.in.p;
-        G.pe = (float)g.in.p / 3.0f;
-        G.pdev = g.in.p_dev;
-        G.biased = g.biased;
-        for (int k = 0; k < 4; ++k) G.pi[k] = (float)g.in.noise[k];
-        if (g.biased) {
-          for (int k = 0; k < 4; ++k) G.pq[k] = g.in.noise[k];
-        } else {
-          G.pq[0] = 1.0 - g.in.p;
-          G.pq[1] = G.pq[2] = G.pq[3] = g.in.p / 3.0;
-        }
-        G.mstride = g.dp->plan.mstride;
-        G.chi = g.opts.chi;
         if (bbp::trunc_class(c) && !sa.tws) {
           sa.tws = g.tws;
           sa.tws_slots = g.lay.tws_slots;
@@ -679,9 +767,53 @@ int enqueue(std::vector<GroupRun>& gr, const bbp_opts* opts, const Tune& tn, hip
     }
     return BBP_OK;
   };
-  for (int it = 0; it < opts->max_iter; ++it) {
+  // small decodes: the fused kernels, one launch per set of groups with the same block sizes
+  const Route route = marks ? Route::classes : choose_route(gr, opts);
+  std::map<int, std::vector<int>> sets;
+  if (route != Route::classes)
+    for (int g = 0; g < ng; ++g)
+      if (gr[g].in.batch > 0) sets[fused_shape(gr[g].dp->plan)].push_back(g);
+  auto fused = [&](int list) -> int {
+    for (auto& kv : sets) {
+      bbp::FusedArgs fa;
+      std::memset(&fa, 0, sizeof(fa));
+      fa.loop = route == Route::loop ? 1 : 0;
+      fa.list = list;
+      fa.max_iter = opts->max_iter;
+      fa.fixed = opts->fixed_iters;
+      fa.delta0 = opts->delta0;
+      fa.s.ngroups = (int)kv.second.size();
+      fa.s.eta = (float)opts->damping;
+      fa.s.gate = opts->gate;
+      fa.s.bf16 = opts->precision == 1 ? 1 : 0;
+      int64_t items = 0;
+      int most = 1;
+      for (int k = 0; k < fa.s.ngroups; ++k) {
+        const GroupRun& g = gr[kv.second[k]];
+        bbp::SweepGroup& G = fa.s.g[k];
+        fill(G, g, items);
+        G.by = bbp::divide_by((uint32_t)g.jobs);
+        if (fa.loop) G.conv = nullptr;
+        bbp::FusedGroup& F = fa.f[k];
+        for (int c = 0; c < 3; ++c) {
+          F.sweeps[c] = c < 2 ? g.dp->round[c] : g.dp->bethe;
+          F.count[c] = (int)(c < 2 ? g.dp->plan.round[c] : g.dp->plan.bethe).size();
+          most = std::max(most, F.count[c]);
+        }
+        F.iters = g.iters;
+        F.delta = g.delta;
+        items += fa.loop ? g.jobs : g.jobs * F.count[list];
+      }
+      fa.s.items = items;
+      if (items == 0) continue;
+      HIP_TRY(bbp::launch_fused(kv.first, opts->precision == 1, (unsigned)items, fa.loop ? std::min(most, 16) : 1, st, fa));
+    }
+    return BBP_OK;
+  };
+  if (route == Route::loop && (rc = fused(0))) return rc;
+  for (int it = 0; it < opts->max_iter && route != Route::loop; ++it) {
     for (int c = 0; c < 2; ++c)
-      if ((rc = round(c, it))) return rc;
+      if ((rc = route == Route::rounds ? fused(c) : round(c, it))) return rc;
     for (auto& g : gr) {
       if (g.in.batch == 0) continue;
       if ((rc = begin_mark(st, 0, it, -1))) return rc;
@@ -691,7 +823,7 @@ int enqueue(std::vector<GroupRun>& gr, const bbp_opts* opts, const Tune& tn, hip
       if ((rc = end_mark(st))) return rc;
     }
   }
-  if ((rc = round(2, opts->max_iter))) return rc;
+  if (route != Route::loop && (rc = route == Route::rounds ? fused(2) : round(2, opts->max_iter))) return rc;
   for (auto& g : gr) {
     if (g.in.batch == 0) continue;
     const bbp::Plan& P = g.dp->plan;

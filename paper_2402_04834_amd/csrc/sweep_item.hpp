@@ -11,6 +11,13 @@ __device__ __forceinline__ double wave_sum_d(double v, int lanes) {
   return v;
 }
 
+// Convergence distance of a job after an iteration, by one wavefront.
+__device__ __forceinline__ double job_delta(const double* terms, int M) {
+  double acc = 0.0;
+  for (int e = (int)__lane_id(); e < M; e += 64) acc += terms[e];
+  return sqrt(fmax(wave_sum_d(acc, 64), 0.0)) / (M > 0 ? M : 1);
+}
+
 // entry index of a K-leg dense message with its legs in reverse order
 __device__ __forceinline__ int reverse_legs(int idx, int K) { return (int)(__brev((unsigned)idx) >> (32 - K)); }
 
@@ -23,16 +30,16 @@ constexpr int sweep_lds_floats() { return LB == 6 ? 1 : (64 >> LB) * (2 * (1 << 
 // mode 1; FP32 everywhere else), else FP32 throughout (precision 0). BIASED: some group of the launch has
 // biased Pauli noise (otherwise the depolarizing entries are compiled in and the biased selection is removed).
 // KP: positions across, 0 where only s.kp tells. job: the lane's job (wave-uniform with LB = 6); active: it takes part
-// (inactive lanes follow along on a valid job and write nothing).
+// (inactive lanes follow along on a valid job and write nothing). mode as in sweep_kernel.hip.
 template <bool BF, int KT, int KP, bool TOP, bool BOT, bool SINGLE, bool Q00, bool BIASED>
-__device__ __forceinline__ void sweep_item(const SweepArgs& a, const SweepGroup& G, const SweepDesc& s, int64_t job,
-                                           bool active, float* lds) {
+__device__ __forceinline__ void sweep_item(const SweepArgs& a, int mode, const SweepGroup& G, const SweepDesc& s,
+                                           int64_t job, bool active, float* lds) {
   using V = float;
   constexpr int LB = sweep_lane_bits(KP), LANES = 1 << LB, SUBS = 64 / LANES;
   using C = wave::Ctx<V, LB, KP, BIASED>;
   const int lane = (int)__lane_id(), h = lane & (LANES - 1), sub = lane >> LB;
-  if (a.mode == 0) {
-    active = active && !G.conv[job];
+  if (mode == 0) {
+    active = active && !(G.conv && G.conv[job]);
     if (a.gate > 0.0) {
       // residual-gated schedule: skip the update when the message and every input message have settled
       const double* tj = G.terms + job * G.M;
@@ -140,7 +147,7 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, const SweepGroup&
   float fin = wave::sweep<V, KT, TOP, BOT, SINGLE, Q00, BF>(x0, c);
   fin = valid ? fin : 0.0f;
 
-  if (a.mode == 1) {
+  if (mode == 1) {
     // closing contraction with the message from the receiver side (or the grid edge)
     double w = 0.0;
     if (s.msg_close >= 0) w = valid ? (double)mbase[s.msg_close * MSTRIDE + mi] * (double)fin : 0.0;

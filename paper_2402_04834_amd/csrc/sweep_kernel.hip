@@ -51,14 +51,15 @@ void sweep_kernel(SweepArgs a) {
     active = job < G.jobs;
     job = active ? job : G.jobs - 1;
   }
-  sweep_item<BF, KT, KP, TOP, BOT, KP == 1, Q00, BIASED>(a, G, G.sweeps[sw], job, active, lds);
+  sweep_item<BF, KT, KP, TOP, BOT, KP == 1, Q00, BIASED>(a, a.mode, G, G.sweeps[sw], job, active, lds);
 }
 
 // variants 0..23: bits 0..2 first site a qubit, bottom and top message present; 8 BF16 middle-site contractions
 // (precision 1), 16 biased noise (FP32 only)
+// (a sweep of fewer than five steps has no contraction on the matrix cores: both precisions run the FP32 kernel)
 template <int V>
 void launch_variant(dim3 grid, hipStream_t st, const SweepArgs& a) {
-  constexpr bool TOP = (V >> 2) & 1, BOT = (V >> 1) & 1, Q00 = V & 1, BF = (V >> 3) & 1, BIASED = (V >> 4) & 1;
+  constexpr bool TOP = (V >> 2) & 1, BOT = (V >> 1) & 1, Q00 = V & 1, BF = ((V >> 3) & 1) && BBP_KT >= 5, BIASED = (V >> 4) & 1;
   sweep_kernel<BF, BBP_KT, BBP_KP, TOP, BOT, Q00, BIASED><<<grid, dim3(64), 0, st>>>(a);
 }
 

@@ -43,7 +43,7 @@ struct SweepGroup {
   const uint8_t* labels;     // [job][L*L] coset labels
   float* msgs;               // [job][M][MSTRIDE] dense messages, position 0 most significant
   double* terms;             // [job][M] distance terms of the last update
-  const int32_t* conv;       // [job] converged flags
+  const int32_t* conv;       // [job] converged flags (NULL: none has converged)
   double* lnW;               // [job][nblocks] (closing sweeps)
   int64_t jobs;
   int64_t item0;             // first item of the group in the launch
@@ -104,5 +104,29 @@ hipError_t launch_small_sweeps(hipStream_t st, const SweepArgs& a);
 // BF16-input kernels or 16 for the biased-noise kernels
 template <int KT, int KP>
 hipError_t launch_sweeps_of(int variant, unsigned items, hipStream_t st, const SweepArgs& a);
+
+// All classes of a round in one launch, or a job's whole decode in one workgroup (fused_sweep.hip).
+struct FusedGroup {
+  const SweepDesc* sweeps[3];   // the two colour rounds and the closing sweeps
+  int32_t count[3];
+  int32_t* iters;               // [job] results of the loop form
+  double* delta;
+};
+struct FusedArgs {
+  SweepArgs s;                  // group state; items = jobs (loop) or jobs * sweeps of the list (round)
+  FusedGroup f[MAX_GROUPS];
+  int32_t loop;                 // 1: one workgroup per job runs everything; 0: one wavefront per (sweep, job) of `list`
+  int32_t list;
+  int32_t max_iter, fixed;
+  double delta0;
+};
+// one translation unit each: (K, R) in FUSED_SHAPES, BF 0 or (K >= 5) 1; `groups` workgroups of `waves` wavefronts
+template <int K, int R, int BF>
+hipError_t launch_fused_of(unsigned groups, int waves, hipStream_t st, const FusedArgs& a);
+// block and remainder sizes that occur for odd grid sizes and blocks of 3 to 6 (a grid of one block of 3 or 5 included)
+constexpr int FUSED_SHAPES[][2] = {{3, 0}, {3, 1}, {3, 2}, {4, 1}, {4, 3}, {5, 0}, {5, 1},
+                                   {5, 2}, {5, 3}, {5, 4}, {6, 1}, {6, 3}, {6, 5}};
+constexpr int NUM_FUSED_SHAPES = sizeof(FUSED_SHAPES) / sizeof(FUSED_SHAPES[0]);
+hipError_t launch_fused(int shape, bool bf16, unsigned groups, int waves, hipStream_t st, const FusedArgs& a);
 
 }  // namespace bbp

@@ -393,3 +393,66 @@ def test_packed_jobs_equal_single_decodes(dev, d, k, precision, extra):
         for key in ("loglik", "delta", "iters", "coset", "correction", "messages"):
             assert torch.equal(whole[0][key][i:i + 1].view(torch.uint8), one[0][key].view(torch.uint8)), (i, key)
     assert iters.min() < iters.max()   # jobs of one wavefront left at different iterations
+
+
+# small decodes take the fused kernels -- a whole job per workgroup (few sweeps, or up to 256 jobs) or one launch per
+# round (many sweeps, few jobs) -- for every pair of block and remainder size; a call that asks for timing takes the
+# class launches
+@pytest.mark.parametrize("d,k,b,precision,extra", [
+    (2, 3, 3, 0, {}), (3, 6, 5, 1, {}),                                   # a single block of 3, of 5: no messages
+    (5, 3, 1, 0, {}), (6, 3, 2, 0, {}), (7, 3, 70, 0, {}), (7, 3, 1, 1, {}),   # blocks 3, remainders 0, 2, 1
+    (5, 4, 2, 1, {}), (6, 4, 90, 0, {}), (14, 4, 1, 0, {}),               # 4: 1, 3, 3
+    (8, 5, 1, 0, {}), (3, 5, 2, 1, {}), (6, 5, 3, 1, {}), (11, 5, 1, 0, {}), (4, 5, 5, 0, {}), (7, 5, 66, 1, {}), (10, 5, 1, 1, {}),
+    (5, 6, 1, 1, {}), (7, 6, 2, 0, {}), (9, 6, 65, 1, {}), (17, 6, 2, 1, {}), (17, 6, 2, 0, {}), (13, 6, 1, 1, {}),
+    (5, 3, 3, 0, {"fixed_iters": 1, "max_iter": 3}), (17, 6, 1, 0, {"fixed_iters": 1, "max_iter": 2}),
+    (5, 3, 9, 0, {"gate": 1e-4}), (11, 4, 2, 0, {"gate": 1e-4}), (5, 6, 4, 1, {"max_iter": 1}),
+])
+def test_fused_routes_equal_class_launches(dev, d, k, b, precision, extra):
+    """Every output of a small decode, per-syndrome rates and given start messages included, equals the class
+    launches' bitwise."""
+    import torch
+    import paper_2402_04834_amd as bbp
+    _, syn = workload.make_batch(d, 0.12, b, workload="test", p_index=900 + 10 * d + k)
+    s = torch.from_numpy(syn).to(dev)
+    ps = torch.linspace(0.06, 0.16, b, dtype=torch.float64, device=dev)
+    opts = bbp.default_opts(block=k, chi=32, precision=precision, **extra)
+    info = bbp.plan_query(d, opts)
+    init = torch.rand((b, 4, max(info.num_messages, 1), 64), generator=torch.Generator().manual_seed(d * 31 + k)).to(dev) + 0.1
+    _say(f"[fused] d={d} k={k} batch {b} precision {precision} {extra}")
+    for groups in ([(d, 0.1, s)], [(d, ps, s, 0, init)]):
+        small, _, _ = bbp.decode_groups(groups, opts, messages=True)
+        classes, _, _ = bbp.decode_groups(groups, opts, messages=True, timing=True)
+        for key in ("loglik", "delta", "iters", "coset", "correction", "messages"):
+            x, y = (o[0][key] for o in (small, classes))
+            if key == "messages":
+                x, y = x[:, :, :info.num_messages], y[:, :, :info.num_messages]
+            assert torch.equal(x.contiguous().view(torch.uint8), y.contiguous().view(torch.uint8)), key
+
+
+@pytest.mark.parametrize("ds,b", [((5, 9), 6), ((5, 11, 17), 4), ((9, 13, 17, 21), 3)])
+def test_fused_routes_mixed_groups_and_graph(dev, ds, b):
+    """Groups of several distances, whose plans fall into one or several sets of block sizes, eager and as a
+    graph replayed three times with other work between: bitwise the class launches' results."""
+    import torch
+    import paper_2402_04834_amd as bbp
+    groups = []
+    for d in ds:
+        _, syn = workload.make_batch(d, 0.1, b, workload="test", p_index=950 + d)
+        groups.append((d, torch.linspace(0.05, 0.15, b, dtype=torch.float64, device=dev), torch.from_numpy(syn).to(dev)))
+    _say(f"[fused groups] d={ds} x {b}")
+    ref, _, _ = bbp.decode_groups(groups, bbp.default_opts(block=6, chi=32, precision=1), timing=True)
+    eager, _, _ = bbp.decode_groups(groups, bbp.default_opts(block=6, chi=32, precision=1))
+    st = torch.cuda.Stream()
+    opts = bbp.default_opts(block=6, chi=32, precision=1, graph=1)
+    torch.cuda.synchronize()
+    outs, ws = None, None
+    for replay in range(3):
+        outs, ws, _ = bbp.decode_groups(groups, opts, stream=st, outs=outs, workspace=ws)
+        st.synchronize()
+        for g in range(len(ds)):
+            for key in ("loglik", "delta", "iters", "coset", "correction"):
+                r = ref[g][key].view(torch.uint8)
+                assert torch.equal(outs[g][key].view(torch.uint8), r), (replay, g, key)
+                assert torch.equal(eager[g][key].view(torch.uint8), r), (g, key)
+                outs[g][key].zero_()
+        torch.cuda.synchronize()
