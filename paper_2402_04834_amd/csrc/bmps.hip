@@ -123,12 +123,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     const bool last = (c == L - 1);
     for (int i = ln; i < 32 * 32; i += 64) Rsh[i] = (i == 0) ? T(1) : T(0);
     if (ln < 32) vch[ln] = (ln == 0) ? T(1) : T(0);
-    __syncthreads();
+    wave_sync();
 
     // ---------------- pass 1 (or the chain of the last column) ----------------
     for (int r = 0; r < L; ++r) {
       for (int i = ln; i < SITE_A; i += 64) Ash[i] = (c == 0) ? (i == 0 ? T(1) : T(0)) : Aj[(int64_t)r * SITE_A + i];
-      __syncthreads();
+      wave_sync();
       const int lb = lab[r * L + c];
       if (last) {
         // v'[ri] = sum_li v[li] B[li][0][ri], li = (a, u), ri = (b, dn)
@@ -144,10 +144,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
           }
         }
         const T mx = wmax(fabs(nv));
-        __syncthreads();
+        wave_sync();
         if (ln < 32) vch[ln] = (mx > T(0)) ? nv / mx : nv;
         logs += log((double)mx);
-        __syncthreads();
+        wave_sync();
         continue;
       }
       // lane (col, par): column col = (b, dn) of M_r = R B_r in the rows (k, t = par)
@@ -167,7 +167,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
           for (int k = 0; k < 32; ++k) x[k] += Rsh[k * 32 + aa * 2] * b0 + Rsh[k * 32 + aa * 2 + 1] * b1;
         }
       }
-      __syncthreads();   // every lane has read R
+      wave_sync();   // every lane has read R
       T* Qr = Qj + (int64_t)r * SITE_Q;
       if (r == L - 1) {
         // the bottom row's right bond has one value: M has the single column (0, 0), kept as is
@@ -182,7 +182,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
       logs += store_r(x, rd, Rsh);
       store_v(x, 32, Hb, Qr);
     }
-    __syncthreads();
+    wave_sync();
     if (last) break;
 
     // ---------------- pass 2: truncating SVD sweep, bottom row to top row ----------------

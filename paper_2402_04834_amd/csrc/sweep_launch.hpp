@@ -83,6 +83,9 @@ inline bool trunc_class(int cls) { return (cls & ~1) == TRUNC_CLASS; }
 size_t trunc_slot_bytes();
 // launch the a.items truncating sweeps (in chunks of a.tws_slots items), all of the narrow form or none
 hipError_t launch_trunc_sweeps(hipStream_t st, const SweepArgs& a, bool narrow);
+// the narrow form (trunc_narrow.hip): workspace bytes of one item, launch of one chunk
+size_t trunc_narrow_slot_bytes();
+void launch_trunc_narrow(unsigned items, hipStream_t st, const SweepArgs& a);
 
 // Class of a sweep: the kernel instantiation that runs it -- length, positions across, caps present, first site a
 // qubit: code (((kt - 1) * 6 + kp - 1) * 4 + top * 2 + bottom) * 2 + q00.

@@ -21,8 +21,7 @@
 //            singular vectors are the new site, N V (unit norm) the carry; the top cap takes Q C.
 //   end      the chain contracted to the dense 2^kp message; normalisation (remark 3), damping (remark 7) and
 //            distance term (remark 4) as in the dense kernels, or the closing overlap of Lemma 3.1.
-//   narrow   with every bond within 8 (trunc_shape.hpp) the factorisations, reflections and SVDs run on the
-//            blocks that can be nonzero, in layouts that keep all 64 lanes busy (trunc_sweep_kernel<true>).
+// Sweeps whose every bond stays within 8 (trunc_shape.hpp) have a kernel of their own, trunc_narrow.hip.
 // Keeping the chi largest values at every bond is the textbook QR + truncated-SVD compression: the part left
 // of a bond is an isometry when it is truncated, so each cut keeps the chi largest Schmidt values of the
 // current state. Where a bond carries at most chi values the SVD keeps them all (the state is unchanged).
@@ -93,17 +92,17 @@ __device__ __forceinline__ void chain(double* W, double* Hv, double* Hb, int K, 
       }
       if (ln < 32) Hv[c * 32 + ln] = (ln == c) ? vj : ((ln > c && ln < m) ? xr : 0.0);
       if (ln == 0) Hb[c] = beta;
-      __syncthreads();
+      wave_sync();
       for (int col = c + 1 + ln; col < n; col += 64) {
         double w = 0.0;
         for (int r = c; r < m; ++r) w += Hv[c * 32 + r] * W[r * n + col];
         w *= beta;
         for (int r = c; r < m; ++r) W[r * n + col] -= w * Hv[c * 32 + r];
       }
-      __syncthreads();
+      wave_sync();
       if (ln == 0) W[c * n + c] = diag;
       if (ln > c && ln < m) W[ln * n + c] = 0.0;
-      __syncthreads();
+      wave_sync();
     }
     // Q (m x k): lane q forms column q by applying the reflections to the unit vector e_q
     if (ln < k) {
@@ -127,7 +126,7 @@ __device__ __forceinline__ void chain(double* W, double* Hv, double* Hb, int K, 
         else out[j * TS + a * 32 + v * 16 + ln] = qv[r];
       }
     }
-    __syncthreads();   // W now holds R (k x n): rows 0 .. k-1, the next step's (2k) x (n/2) matrix
+    wave_sync();   // W now holds R (k x n): rows 0 .. k-1, the next step's (2k) x (n/2) matrix
     b = k;
   }
   // last site: A_{K-1}[a][v][0] = rest[a][v]
@@ -136,245 +135,9 @@ __device__ __forceinline__ void chain(double* W, double* Hv, double* Hb, int K, 
     if (transposed) out[0 * TS + v * 16 + a] = W[e];
     else out[(K - 1) * TS + a * 32 + v * 16] = W[e];
   }
-  __syncthreads();
+  wave_sync();
 }
 
-// A crossing site's factorisation in the narrow form: M (rows (k, h) < 32 with R row k < 16, columns (b, dn)
-// < 16) held as x[k] = M[4 k + q][c] by lane (c, q) = (ln >> 2, ln & 3), k < 8 -- the block of the padded
-// 64 x 32 site matrix that can be nonzero, spread so that every lane holds 8 of its rows (the 64 x 32 layout
-// of qr64u would leave half the lanes on zero columns). Householder QR with 16 reflections
-// (vectors broadcast through LDS as in qr64u, sums over a column's four lanes by two exchanges), then R (unit
-// Frobenius norm, zero in the columns >= 16) into Rsh [row][col] and the vectors and coefficients into the
-// factor slot in store_v's format (rows < 32). Returns ln |R|_F.
-__device__ __forceinline__ double factor_narrow(double (&x)[8], double* vb, double* Hb, double* Rsh, double* Vg) {
-  const int ln = threadIdx.x, c = ln >> 2, q = ln & 3;
-  double rd = 0.0;
-#pragma unroll
-  for (int j = 0; j < 16; ++j) {
-    const int kj = j >> 2, qj = j & 3;   // pivot row j = 4 kj + qj
-    double* v = vb + (j & 1) * 64;
-    if (c == j) {
-#pragma unroll
-      for (int k = kj; k < 8; ++k) v[4 * k + q] = x[k];
-    }
-    __syncthreads();
-    double hv[8], pn = 0.0;
-#pragma unroll
-    for (int k = kj; k < 8; ++k) {
-      hv[k] = v[4 * k + q];
-      if (k == kj) hv[k] = q < qj ? 0.0 : hv[k];   // rows above the pivot are not part of the vector
-      pn += hv[k] * hv[k];
-    }
-    pn += __shfl_xor(pn, 1);
-    pn += __shfl_xor(pn, 2);
-    const double nrm = sqrt(pn);
-    const double alpha = v[j];
-    double beta = 0.0, vj = alpha, diag = alpha;
-    if (nrm > 0.0) {
-      const double sg = (alpha >= 0.0) ? 1.0 : -1.0;
-      vj = alpha + sg * nrm;
-      beta = 1.0 / (nrm * (nrm + fabs(alpha)));
-      diag = -sg * nrm;
-    }
-    hv[kj] = (q == qj) ? vj : hv[kj];   // the pivot entry of the vector is v_j, not alpha
-    double pw = 0.0;
-#pragma unroll
-    for (int k = kj; k < 8; ++k) pw += hv[k] * x[k];
-    pw += __shfl_xor(pw, 1);
-    pw += __shfl_xor(pw, 2);
-    const double w = pw * beta;
-    if (c > j) {
-#pragma unroll
-      for (int k = kj; k < 8; ++k) x[k] -= w * hv[k];
-    } else if (c == j) {
-      rd = diag;
-      if (q == qj) x[kj] = vj;
-    }
-    if (ln == 0) Hb[j] = beta;
-  }
-  __syncthreads();
-  double f = 0.0;
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    const int row = 4 * k + q;
-    const double r = row < c ? x[k] : (row == c ? rd : 0.0);
-    f += r * r;
-  }
-  const double fro = sqrt(wsum(f));
-  const double inv = (fro > 0.0) ? 1.0 / fro : 0.0;
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    const int row = 4 * k + q;
-    Rsh[row * 32 + c] = (row < c ? x[k] : (row == c ? rd : 0.0)) * inv;
-    Rsh[row * 32 + 16 + c] = 0.0;
-    Vg[c * 64 + row] = (row >= c) ? x[k] : 0.0;
-  }
-  if (ln < 16) Vg[2048 + ln] = Hb[ln];
-  __syncthreads();
-  return log(fro);
-}
-
-// apply_q and cols_to_rows (wave_mps.hpp) in the narrow form: X = Q C with 16 reflections for the rows < 32
-// and the columns k < 8 that can be nonzero. Lane (kc, g) = (ln & 7, ln >> 3) holds rows 4 g + r (r < 4) of
-// column kc; a reflection is a 4-term partial product, a sum over the eight row groups (three exchanges) and
-// a 4-term update, with the next reflection's entries loaded meanwhile. Then, in svd_narrow's layout, lane
-// (l, u) takes y[e] = X[2 l + u / 2][4 (u % 2) + e].
-__device__ __forceinline__ void apply_q_narrow(const double* Vg, const double* Csh, double* Xsh, double (&y)[4]) {
-  const int ln = threadIdx.x, kc = ln & 7, g = ln >> 3;
-  double X[4], vn[4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    X[r] = Csh[(4 * g + r) * 16 + kc];
-    vn[r] = Vg[15 * 64 + 4 * g + r];
-  }
-  double bn = Vg[2048 + 15];
-  for (int j = 15; j >= 0; --j) {
-    double v[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) v[r] = vn[r];
-    const double beta = bn;
-    if (j > 0) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) vn[r] = Vg[(j - 1) * 64 + 4 * g + r];
-      bn = Vg[2048 + j - 1];
-    }
-    double p = 0.0;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) p += v[r] * X[r];
-    p += __shfl_xor(p, 8);
-    p += __shfl_xor(p, 16);
-    p += __shfl_xor(p, 32);
-    const double w = p * beta;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) X[r] -= w * v[r];
-  }
-#pragma unroll
-  for (int r = 0; r < 4; ++r) Xsh[(4 * g + r) * XS + kc] = X[r];
-  __syncthreads();
-  const int l = ln >> 2, u = ln & 3;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) y[e] = Xsh[(2 * l + (u >> 1)) * XS + 4 * (u & 1) + e];
-  __syncthreads();
-}
-
-// svd_step (wave_mps.hpp) in the narrow form: N has at most 16 nonzero rows, each with 2 x 8 nonzero entries
-// (t, k), held as y[e] = N[l][(t, k)] with t = u / 2, k = 4 (u % 2) + e by lane (l, u) = (ln >> 2, ln & 3).
-// The same one-sided Jacobi rotations, stopping test and outputs (kept right singular vectors as site rows,
-// zero beyond chi and beyond k = 8; the carry C = N V / |.|_F into Csh [l][j], rows 16..31 cleared); the
-// round-robin pairs 16 rows (15 rounds per sweep), and a round exchanges 4 entries and a norm per lane and
-// sums a pair's product over the row's four lanes by two exchanges.
-__device__ __forceinline__ double svd_narrow(double (&y)[4], int chi, double* Xsh, double* Csh, double* sig,
-                                             double* site, bool bottom) {
-  constexpr int XN = 5;   // exchange row stride: 4 entries and the row norm
-  const int ln = threadIdx.x, l = ln >> 2, u = ln & 3, t = u >> 1, k0 = 4 * (u & 1);
-  double y0[4];
-#pragma unroll
-  for (int e = 0; e < 4; ++e) y0[e] = y[e];
-  double nf2 = 0.0;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) nf2 += y[e] * y[e];
-  const double thr2 = wsum(nf2) * (RANKTOL * RANKTOL);
-  auto rowsum = [](double v) {
-    v += __shfl_xor(v, 1);
-    return v + __shfl_xor(v, 2);
-  };
-  for (int sw = 0; sw < SWEEPS; ++sw) {
-    int rotated = 0;
-    double c2max = 0.0;
-    double own = 0.0;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) own += y[e] * y[e];
-    own = rowsum(own);
-    // round rd pairs rows l and pl: 15 and rd, the others (2 rd - l) mod 15, stepped by 2 each round
-    int cyc = (30 - l) % 15;
-    for (int rd = 0; rd < 15; ++rd, cyc = (cyc + 2 >= 15) ? cyc + 2 - 15 : cyc + 2) {
-      const int pl = (l == 15) ? rd : (l == rd) ? 15 : cyc;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) Xsh[ln * XN + e] = y[e];
-      Xsh[ln * XN + 4] = own;
-      __syncthreads();
-      double z[4], gg = 0.0;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        z[e] = Xsh[(4 * pl + u) * XN + e];
-        gg += y[e] * z[e];
-      }
-      const double other = Xsh[(4 * pl + u) * XN + 4];
-      __syncthreads();
-      gg = rowsum(gg);
-      const bool lower = l < pl;
-      const double al = lower ? own : other, be = lower ? other : own;
-      const double c2 = (al > thr2 && be > thr2) ? gg * gg * __builtin_amdgcn_rcp(al * be) : 0.0;
-      c2max = c2 > c2max ? c2 : c2max;
-      if (c2 > JAC * JAC) {
-        // the angle as in svd_step: tan in FP32, cos and sin in FP64 from it
-        const float zf = (float)(be - al) * __builtin_amdgcn_rcpf(2.0f * (float)gg), azf = fabsf(zf);
-        const float denf = azf + (azf < 1e18f ? __builtin_amdgcn_sqrtf(fmaf(zf, zf, 1.0f)) : azf);
-        const double tt = (double)copysignf(__builtin_amdgcn_rcpf(denf), zf);
-        const double xx = tt * tt + 1.0;
-        double cs = __builtin_amdgcn_rsq(xx);
-        cs = cs * (1.5 - 0.5 * xx * cs * cs);
-        cs = cs * (1.5 - 0.5 * xx * cs * cs);
-        const double sn = cs * tt;
-        const double sz = lower ? -sn : sn;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) y[e] = fma(sz, z[e], cs * y[e]);
-        const double cc = cs * cs;
-        own = lower ? cc * (al - 2.0 * tt * gg + tt * tt * be) : cc * (be + 2.0 * tt * gg + tt * tt * al);
-        rotated = 1;
-      }
-    }
-    if (!__any(rotated) || wmax(c2max) < 1e-12) break;
-  }
-  double s2 = 0.0;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) s2 += y[e] * y[e];
-  const double s2r = rowsum(s2);
-  const double sv = (s2r > thr2) ? sqrt(s2r) : 0.0;
-  const double key = (sv == sv) ? sv : -1.0;
-  if (u == 0) sig[l] = key;
-  __syncthreads();
-  int rank = 0;
-  for (int i = 0; i < 16; ++i) {
-    const double o = sig[i];
-    rank += (o > key || (o == key && i < l)) ? 1 : 0;
-  }
-  const bool kept = rank < chi && sv > 0.0;
-  const double inv = kept ? 1.0 / sv : 0.0;
-  double* Vsh = Xsh;   // the exchange buffer is free now
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    if (bottom) {
-      if (t == 0) {
-        site[rank * 16 + k0 + e] = y[e] * inv;
-        site[rank * 16 + 8 + k0 + e] = 0.0;
-      }
-    } else {
-      site[(rank * 2 + t) * 16 + k0 + e] = y[e] * inv;
-      site[(rank * 2 + t) * 16 + 8 + k0 + e] = 0.0;
-    }
-    Vsh[rank * 32 + t * 16 + k0 + e] = y[e] * inv;
-  }
-  const double fro = sqrt(wsum((u == 0 && kept) ? sv * sv : 0.0));
-  __syncthreads();
-  const double finv = (fro > 0.0) ? 1.0 / fro : 0.0;
-#pragma unroll
-  for (int j = 0; j < 16; ++j) {
-    double acc = 0.0;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) acc += y0[e] * Vsh[j * 32 + t * 16 + k0 + e];
-    acc = rowsum(acc);
-    if ((j >> 2) == u) Csh[l * 16 + j] = acc * finv;
-  }
-#pragma unroll
-  for (int e = 0; e < 4; ++e) Csh[(16 + l) * 16 + 4 * u + e] = 0.0;
-  __syncthreads();
-  return log(fro);
-}
-
-// NARROW: the sweeps of the narrow form (trunc_shape.hpp), factored and decomposed at half size; each form has
-// its own instantiation so that neither pays the other's registers.
-template <bool NARROW>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void trunc_sweep_kernel(SweepArgs a) {
   const int ln = threadIdx.x, hi = ln >> 1, par = ln & 1;
   const int64_t item = a.item_base + (int64_t)blockIdx.x;
@@ -429,7 +192,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void tr
   if (bot)
     for (int e = ln; e < kt * TS; e += 64) CT[KM * TS + e] = 0.0;
   for (int e = ln; e < (kp + 2) * TS; e += 64) A[e] = 0.0;
-  __syncthreads();
+  wave_sync();
   {
     double* W = pool;
     double* Hv = pool + 256;
@@ -438,12 +201,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void tr
       const int id = side == 0 ? s.msg_top : s.msg_bot;
       if (id < 0) continue;
       for (int w = ln; w < (1 << kt); w += 64) W[w] = (double)mbase[id * (int64_t)ms + (fwd ? bitrev(w, kt) : w)];
-      __syncthreads();
+      wave_sync();
       chain(W, Hv, Hb, kt, CT + side * KM * TS, true);
     }
     if (s.msg_init >= 0) {
       for (int w = ln; w < (1 << kp); w += 64) W[w] = (double)mbase[s.msg_init * (int64_t)ms + w];
-      __syncthreads();
+      wave_sync();
       chain(W, Hv, Hb, kp, A + TS, false);
     } else {
       for (int i = 1; i <= kp; ++i)
@@ -454,7 +217,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void tr
       A[(kp + 1) * TS] = 1.0;      // bottom cap [d = 0][q = 0]
     }
   }
-  __syncthreads();
+  wave_sync();
 
   double logs = 0.0;
   for (int t = 0; t < kt; ++t) {
@@ -470,7 +233,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void tr
     for (int e = ln; e < 256; e += 64) Ash[e] = A[e];
     if (top)
       for (int e = ln; e < TS; e += 64) CTs[e] = CT[t * TS + e];
-    __syncthreads();
+    wave_sync();
     {
       const int d = hi >> 1, v = hi & 1;
 #pragma unroll
@@ -488,57 +251,35 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void tr
     qr64u<16, 8>(x, rd, vb, Hb);   // rows q' < 16: registers k < 8
     logs += store_r(x, rd, Rsh);
     store_v(x, 16, Hb, Q);
-    // crossing sites: M [(k, h)][(b, dn)] = sum_(a, u) R[k][(a, u)] (A_i T)[(a, u)][(h, b, dn)], factored; in the
-    // narrow form R has at most 16 rows and the site's bonds at most 8, so M is 32 x 16 (factor_narrow)
+    // crossing sites: M [(k, h)][(b, dn)] = sum_(a, u) R[k][(a, u)] (A_i T)[(a, u)][(h, b, dn)], factored
     for (int i = 1; i <= kp; ++i) {
       for (int e = ln; e < TS; e += 64) Ash[e] = A[i * TS + e];
-      __syncthreads();
-      if constexpr (NARROW) {
-        // lane (c, q): column c = (b, dn), rows 4 k + q = (R row 2 k + q / 2, leg q % 2)
-        const int c = ln >> 2, q = ln & 3, b = c >> 1, dn = c & 1, h = q & 1, k0 = q >> 1;
-        const double t00 = tab(s, L, lab, pq, t, i - 1, 0 * 8 + 0 * 4 + dn * 2 + h);
-        const double t01 = tab(s, L, lab, pq, t, i - 1, 0 * 8 + 1 * 4 + dn * 2 + h);
-        const double t10 = tab(s, L, lab, pq, t, i - 1, 1 * 8 + 0 * 4 + dn * 2 + h);
-        const double t11 = tab(s, L, lab, pq, t, i - 1, 1 * 8 + 1 * 4 + dn * 2 + h);
-        double xn[8];
+      wave_sync();
+      {
+        const int b = hi >> 1, dn = hi & 1;
+        const double t00 = tab(s, L, lab, pq, t, i - 1, 0 * 8 + 0 * 4 + dn * 2 + par);
+        const double t01 = tab(s, L, lab, pq, t, i - 1, 0 * 8 + 1 * 4 + dn * 2 + par);
+        const double t10 = tab(s, L, lab, pq, t, i - 1, 1 * 8 + 0 * 4 + dn * 2 + par);
+        const double t11 = tab(s, L, lab, pq, t, i - 1, 1 * 8 + 1 * 4 + dn * 2 + par);
 #pragma unroll
-        for (int k = 0; k < 8; ++k) xn[k] = 0.0;
-        for (int aa = 0; aa < 8; ++aa) {
+        for (int k = 0; k < 32; ++k) x[k] = 0.0;
+        for (int aa = 0; aa < 16; ++aa) {
           const double a0 = Ash[(aa * 2 + 0) * 16 + b], a1 = Ash[(aa * 2 + 1) * 16 + b];
           const double b0 = a0 * t00 + a1 * t01, b1 = a0 * t10 + a1 * t11;
 #pragma unroll
-          for (int k = 0; k < 8; ++k)
-            xn[k] += Rsh[(2 * k + k0) * 32 + aa * 2] * b0 + Rsh[(2 * k + k0) * 32 + aa * 2 + 1] * b1;
+          for (int k = 0; k < 32; ++k) x[k] += Rsh[k * 32 + aa * 2] * b0 + Rsh[k * 32 + aa * 2 + 1] * b1;
         }
-        __syncthreads();   // every lane has read R
-        logs += factor_narrow(xn, vb, Hb, Rsh, Q + i * TQ);
-      } else {
-        {
-          const int b = hi >> 1, dn = hi & 1;
-          const double t00 = tab(s, L, lab, pq, t, i - 1, 0 * 8 + 0 * 4 + dn * 2 + par);
-          const double t01 = tab(s, L, lab, pq, t, i - 1, 0 * 8 + 1 * 4 + dn * 2 + par);
-          const double t10 = tab(s, L, lab, pq, t, i - 1, 1 * 8 + 0 * 4 + dn * 2 + par);
-          const double t11 = tab(s, L, lab, pq, t, i - 1, 1 * 8 + 1 * 4 + dn * 2 + par);
-#pragma unroll
-          for (int k = 0; k < 32; ++k) x[k] = 0.0;
-          for (int aa = 0; aa < 16; ++aa) {
-            const double a0 = Ash[(aa * 2 + 0) * 16 + b], a1 = Ash[(aa * 2 + 1) * 16 + b];
-            const double b0 = a0 * t00 + a1 * t01, b1 = a0 * t10 + a1 * t11;
-#pragma unroll
-            for (int k = 0; k < 32; ++k) x[k] += Rsh[k * 32 + aa * 2] * b0 + Rsh[k * 32 + aa * 2 + 1] * b1;
-          }
-        }
-        __syncthreads();   // every lane has read R
-        qr64u<32>(x, rd, vb, Hb);
-        logs += store_r(x, rd, Rsh);
-        store_v(x, 32, Hb, Q + i * TQ);
       }
+      wave_sync();   // every lane has read R
+      qr64u<32>(x, rd, vb, Hb);
+      logs += store_r(x, rd, Rsh);
+      store_v(x, 32, Hb, Q + i * TQ);
     }
     // bottom cap: Bb[(d, v)][q'] = sum_P S[d][P] CT[P][v][q'], then M[l][q'] = sum R[l][(d, v)] Bb[(d, v)][q']
     for (int e = ln; e < 256; e += 64) Ash[e] = A[(kp + 1) * TS + e];
     if (bot)
       for (int e = ln; e < TS; e += 64) CTs[e] = CT[(KM + t) * TS + e];
-    __syncthreads();
+    wave_sync();
     {
       double bv[8];
 #pragma unroll
@@ -552,11 +293,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void tr
         }
         bv[u] = acc;
       }
-      __syncthreads();   // every lane has read the operator before Bb overwrites it
+      wave_sync();   // every lane has read the operator before Bb overwrites it
 #pragma unroll
       for (int u = 0; u < 8; ++u) Bb[ln + 64 * u] = bv[u];
     }
-    __syncthreads();
+    wave_sync();
     {
       double* Mg = Q + (kp + 1) * TQ;
 #pragma unroll 1
@@ -568,7 +309,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void tr
         Mg[hi * 16 + q] = acc;
       }
     }
-    __syncthreads();
+    wave_sync();
 
     // ---------------- pass 2: truncating SVD sweep, bottom to top ----------------
     double* Xsh = pool;
@@ -576,29 +317,17 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void tr
     double* sig = Csh + 32 * 16;
     for (int i = kp + 1; i >= 1; --i) {
       const double* Mg = Q + (kp + 1) * TQ;   // the bottom cap's M [l][q']
-      if constexpr (NARROW) {
-        double y[4];
-        if (i == kp + 1) {
-          const int l = ln >> 2, u = ln & 3;
+      double y[16];
+      if (i == kp + 1) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) y[e] = (u < 2) ? Mg[l * 16 + 4 * u + e] : 0.0;
-        } else {
-          apply_q_narrow(Q + i * TQ, Csh, Xsh, y);   // N = Q_i C
-        }
-        logs += svd_narrow(y, chi, Xsh, Csh, sig, A + i * TS, i == kp + 1);
+        for (int k = 0; k < 16; ++k) y[k] = par == 0 ? Mg[hi * 16 + k] : 0.0;
       } else {
-        double y[16];
-        if (i == kp + 1) {
-#pragma unroll
-          for (int k = 0; k < 16; ++k) y[k] = par == 0 ? Mg[hi * 16 + k] : 0.0;
-        } else {
-          // N = Q_i C, then from the column layout to rows: lane (l, t) takes N[l][(t, k)] = X[2l + t][k]
-          double X[16];
-          apply_q(X, 32, Q + i * TQ, Csh);
-          cols_to_rows(X, Xsh, y);
-        }
-        logs += svd_step(y, chi, Xsh, Csh, sig, A + i * TS, i == kp + 1);
+        // N = Q_i C, then from the column layout to rows: lane (l, t) takes N[l][(t, k)] = X[2l + t][k]
+        double X[16];
+        apply_q(X, 32, Q + i * TQ, Csh);
+        cols_to_rows(X, Xsh, y);
       }
+      logs += svd_step(y, chi, Xsh, Csh, sig, A + i * TS, i == kp + 1);
     }
     // top cap: S_0[q'][j] = sum_m Q_0[q'][m] C[m][j], unit Frobenius norm
     {
@@ -616,7 +345,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void tr
       }
       logs += log(fro);
     }
-    __syncthreads();
+    wave_sync();
   }
 
   // ---------------- the dense message: left chain x right chain ----------------
@@ -626,7 +355,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void tr
     pool[e] = A[e];                              // top cap row q' = 0
     pool[512 + e] = A[(kp + 1) * TS + e * 16];   // bottom cap column q' = 0
   }
-  __syncthreads();
+  wave_sync();
   int lc = 0, rc = 0;
   for (int i = 1; i <= hl; ++i) {   // L_i[(pre, h)][b] = sum_a L_{i-1}[pre][a] S_i[a][h][b]
     const int n = (1 << i) * 16;
@@ -636,7 +365,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void tr
       for (int aa = 0; aa < 16; ++aa) acc += pool[lc * 256 + pre * 16 + aa] * A[i * TS + aa * 32 + h * 16 + b];
       pool[(lc ^ 1) * 256 + e] = acc;
     }
-    __syncthreads();
+    wave_sync();
     lc ^= 1;
   }
   for (int i = kp; i > hl; --i) {   // R_i[(h, suf)][a] = sum_b S_i[a][h][b] R_{i+1}[suf][b]
@@ -647,7 +376,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void tr
       for (int b = 0; b < 16; ++b) acc += A[i * TS + aa * 32 + h * 16 + b] * pool[512 + rc * 256 + suf * 16 + b];
       pool[512 + (rc ^ 1) * 256 + e] = acc;
     }
-    __syncthreads();
+    wave_sync();
     rc ^= 1;
   }
   double out[4];
@@ -713,7 +442,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void tr
 
 }  // namespace
 
-size_t trunc_slot_bytes() { return (size_t)W_SLOT * sizeof(double); }
+size_t trunc_slot_bytes() { return std::max((size_t)W_SLOT * sizeof(double), trunc_narrow_slot_bytes()); }
 
 hipError_t launch_trunc_sweeps(hipStream_t st, const SweepArgs& a, bool narrow) {
   if (a.items <= 0) return hipSuccess;
@@ -723,9 +452,9 @@ hipError_t launch_trunc_sweeps(hipStream_t st, const SweepArgs& a, bool narrow) 
     b.item_base = base;
     const int64_t n = std::min<int64_t>(a.tws_slots, a.items - base);
     if (narrow)
-      trunc_sweep_kernel<true><<<dim3((unsigned)n), dim3(64), 0, st>>>(b);
+      launch_trunc_narrow((unsigned)n, st, b);
     else
-      trunc_sweep_kernel<false><<<dim3((unsigned)n), dim3(64), 0, st>>>(b);
+      trunc_sweep_kernel<<<dim3((unsigned)n), dim3(64), 0, st>>>(b);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

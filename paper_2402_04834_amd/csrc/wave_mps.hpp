@@ -26,6 +26,14 @@ constexpr int TQ = 32 * 64 + 32;  // one factor slot: reflection vectors [j][row
 constexpr double JAC = 1e-13, RANKTOL = 1e-13;
 constexpr int SWEEPS = 16;
 
+// Orders the memory accesses of the lanes of a one-wavefront workgroup: they complete in issue order, so only the
+// compiler has to keep them (__syncthreads also waits for every outstanding LDS access).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 __device__ __forceinline__ double wsum(double v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
@@ -50,7 +58,7 @@ __device__ __forceinline__ void qr64(double (&x)[32], double& rd, int jmax, doub
 #pragma unroll
       for (int k = 0; k < 32; ++k) v[2 * k + par] = (2 * k + par >= j) ? x[k] : 0.0;
     }
-    __syncthreads();
+    wave_sync();
     double hv[32], pn = 0.0;
 #pragma unroll
     for (int k = 0; k < 32; ++k) {
@@ -85,7 +93,7 @@ __device__ __forceinline__ void qr64(double (&x)[32], double& rd, int jmax, doub
     }
     if (ln == 0) Hb[j] = beta;
   }
-  __syncthreads();
+  wave_sync();
 }
 
 // qr64 with the reflections unrolled (JMAX = jmax): reflection j touches rows >= j only, i.e. registers
@@ -107,7 +115,7 @@ __device__ __forceinline__ void qr64u(double (&x)[32], double& rd, double* vb, d
 #pragma unroll
       for (int k = k0; k < KR; ++k) v[2 * k + par] = x[k];
     }
-    __syncthreads();
+    wave_sync();
     double hv[32], pn = 0.0;
 #pragma unroll
     for (int k = k0; k < KR; ++k) {
@@ -139,7 +147,7 @@ __device__ __forceinline__ void qr64u(double (&x)[32], double& rd, double* vb, d
     }
     if (ln == 0) Hb[j] = beta;
   }
-  __syncthreads();
+  wave_sync();
 }
 
 // The reflection vectors left in x by qr64 (rows >= j of column j, zero above) and their coefficients into a
@@ -201,10 +209,10 @@ __device__ __forceinline__ void cols_to_rows(const double (&X)[16], double* Xsh,
   const int ln = threadIdx.x;
 #pragma unroll
   for (int r = 0; r < 16; ++r) Xsh[((ln >> 4) * 16 + r) * XS + (ln & 15)] = X[r];
-  __syncthreads();
+  wave_sync();
 #pragma unroll
   for (int k = 0; k < 16; ++k) y[k] = Xsh[ln * XS + k];
-  __syncthreads();
+  wave_sync();
 }
 
 // The carry R (rows 0..31 of the factored matrix) into Rsh [row][col], unit Frobenius norm; returns ln |R|_F.
@@ -224,7 +232,7 @@ __device__ __forceinline__ double store_r(const double (&x)[32], double rd, doub
     const int row = 2 * k + par;
     Rsh[row * 32 + hi] = (row < hi ? x[k] : (row == hi ? rd : 0.0)) * inv;
   }
-  __syncthreads();
+  wave_sync();
   return log(fro);
 }
 
@@ -256,7 +264,7 @@ __device__ __forceinline__ double svd_step(double (&y)[16], int chi, double* Xsh
 #pragma unroll
       for (int k = 0; k < 16; ++k) Xsh[ln * XS + k] = y[k];
       Xsh[ln * XS + 16] = own;
-      __syncthreads();
+      wave_sync();
       double z[16], gg = 0.0;
 #pragma unroll
       for (int k = 0; k < 16; ++k) {
@@ -264,7 +272,7 @@ __device__ __forceinline__ double svd_step(double (&y)[16], int chi, double* Xsh
         gg += y[k] * z[k];
       }
       const double other = Xsh[(2 * pl + par) * XS + 16];
-      __syncthreads();
+      wave_sync();
       gg += __shfl_xor(gg, 1);
       const bool lower = hi < pl;
       const double al = lower ? own : other, be = lower ? other : own;
@@ -305,7 +313,7 @@ __device__ __forceinline__ double svd_step(double (&y)[16], int chi, double* Xsh
   const double sv = (s2r > thr2) ? sqrt(s2r) : 0.0;
   const double key = (sv == sv) ? sv : -1.0;
   if (par == 0) sig[hi] = key;
-  __syncthreads();
+  wave_sync();
   int rank = 0;
   for (int i = 0; i < 32; ++i) {
     const double o = sig[i];
@@ -326,7 +334,7 @@ __device__ __forceinline__ double svd_step(double (&y)[16], int chi, double* Xsh
     }
   }
   const double fro = sqrt(wsum((par == 0 && kept) ? sv * sv : 0.0));
-  __syncthreads();
+  wave_sync();
   const double finv = (fro > 0.0) ? 1.0 / fro : 0.0;
 #pragma unroll
   for (int j = 0; j < 16; ++j) {
@@ -336,7 +344,7 @@ __device__ __forceinline__ double svd_step(double (&y)[16], int chi, double* Xsh
     acc += __shfl_xor(acc, 1);
     if ((j >> 3) == par) Csh[hi * 16 + j] = acc * finv;
   }
-  __syncthreads();
+  wave_sync();
   return log(fro);
 }
 

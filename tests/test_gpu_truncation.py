@@ -217,3 +217,23 @@ def test_full_size_d17_truncating_against_oracle_fixture(dev, fixture, k, chi, b
     np.testing.assert_array_less(err, 2e-5 + 2e-7 * np.abs(ref_ll[ok]))
     _decisions_agree(got["coset"][idx], ref_ll, ref_cs, ref_dl, meta["delta1"], margin=1e-3)
     assert np.all(got["coset"] < 4)
+
+
+@pytest.mark.parametrize("d,p,k,chi,count", [
+    (4, 0.10, 3, 2, 2),     # 3x3 blocks: the narrowest state and the shortest sweeps
+    (5, 0.10, 3, 3, 3),     # odd chi
+    (7, 0.03, 7, 8, 1),     # one 7-wide block beside remainders, low noise: bonds of very different weight
+    (9, 0.12, 5, 5, 3),     # odd chi and block
+    (8, 0.10, 7, 8, 2),     # even distance, a remainder of 1
+])
+def test_narrow_sweeps_at_shape_edges(dev, d, p, k, chi, count):
+    # the form for bonds within 8 leaves out rows, columns and Jacobi rounds beyond a bond's actual size: smallest
+    # and largest chi and block, a size in between, odd and even sizes, single jobs. Bounds as above.
+    import paper_2402_04834_amd as bbp
+    _say(f"[trunc-narrow] d={d} p={p} k={k} chi={chi} count={count}")
+    assert bbp.plan_query(d, bbp.default_opts(block=k, chi=chi)).truncating_sweeps > 0
+    _, syn = workload.make_batch(d, p, count, workload="test", p_index=2 * d + k + chi)
+    ref = blockbp.decode(d, p, syn, block=(k, k), chi=chi, max_iter=3, eta=0.1, fixed_iters=True, return_messages=True)
+    got = _decode(dev, d, p, syn, block=k, chi=chi, max_iter=3, damping=0.1, fixed_iters=1)
+    _check_messages(got["messages"], ref, ref["plan"])
+    _check_loglik(got["loglik"], ref["loglik"])
