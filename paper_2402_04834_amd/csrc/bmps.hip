@@ -27,6 +27,9 @@
 // 15-30 nats below the best and returned non-positive values within 8 nats of the best (d=5, chi 16), so
 // every matrix is FP64; only rotation angles (below) are formed in FP32.
 //
+// Bound by the latency of one wavefront's chain of reflections and Jacobi rounds. Bonds are tracked at the number of
+// values kept, and what is zero beyond them is left out (d = 13, chi 16, 32 syndromes: 92.6 -> 67.1 ms).
+//
 // Layout (wave_mps.hpp): every lane owns matrix columns in registers. Pass 1: lane (col, par) holds the 32
 // entries of column col of M_r in the rows of parity par; a Householder vector is broadcast through LDS from
 // the two lanes that own it, and the vectors reach the workspace once, when the row is factored. Pass 2:
@@ -36,6 +39,8 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "bmps_launch.hpp"
 #include "wave_mps.hpp"
@@ -91,6 +96,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
   const int L = 2 * a.d - 1, chi = a.chi;
   __shared__ T pool[POOL];
   __shared__ T vch[32];                 // last-column chain vector
+  __shared__ uint8_t left[64], refl[64];   // per grid row (L <= 63): left bond, reflections of its factor
   // pass 1
   T* Rsh = pool;                        // carry R [k][li]
   T* vb = Rsh + 32 * 32;                // Householder vector buffers
@@ -118,6 +124,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     p0 = (T)pp; p1 = (T)pe; p2 = (T)pe; p3 = (T)pe;
   }
   double logs = 0.0;
+  left[ln] = 1;
 
   for (int c = 0; c < L; ++c) {
     const bool last = (c == L - 1);
@@ -126,6 +133,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     wave_sync();
 
     // ---------------- pass 1 (or the chain of the last column) ----------------
+    int nrow = 1;   // rows of R that can be nonzero
     for (int r = 0; r < L; ++r) {
       for (int i = ln; i < SITE_A; i += 64) Ash[i] = (c == 0) ? (i == 0 ? T(1) : T(0)) : Aj[(int64_t)r * SITE_A + i];
       wave_sync();
@@ -151,23 +159,30 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
         continue;
       }
       // lane (col, par): column col = (b, dn) of M_r = R B_r in the rows (k, t = par)
-      T x[32];
-      {
-        const int b = hi >> 1, dn = hi & 1;
-        const T t00 = tentry(r, c, L, lb, 0, 0, dn, par, p0, p1, p2, p3), t01 = tentry(r, c, L, lb, 0, 1, dn, par, p0, p1, p2, p3);
-        const T t10 = tentry(r, c, L, lb, 1, 0, dn, par, p0, p1, p2, p3), t11 = tentry(r, c, L, lb, 1, 1, dn, par, p0, p1, p2, p3);
+      T x[32], rd;
+      const int na = __builtin_amdgcn_readfirstlane(left[r]);
+      const int jmax = r < L - 1 ? min(2 * nrow, 2 * __builtin_amdgcn_readfirstlane((int)left[r + 1])) : 0;
+      const int b = hi >> 1, dn = hi & 1;
+      const T t00 = tentry(r, c, L, lb, 0, 0, dn, par, p0, p1, p2, p3), t01 = tentry(r, c, L, lb, 0, 1, dn, par, p0, p1, p2, p3);
+      const T t10 = tentry(r, c, L, lb, 1, 0, dn, par, p0, p1, p2, p3), t11 = tentry(r, c, L, lb, 1, 1, dn, par, p0, p1, p2, p3);
 #pragma unroll
-        for (int k = 0; k < 32; ++k) x[k] = T(0);
+      for (int k = 0; k < 32; ++k) x[k] = T(0);
+      // x[k] belongs to R's row k
+      auto site = [&](auto rows) __attribute__((always_inline)) {
+        constexpr int KR = decltype(rows)::value;
         // B[li][par][col] for li = (aa, u), formed as it is used
 #pragma unroll 1
-        for (int aa = 0; aa < 16; ++aa) {
+        for (int aa = 0; aa < na; ++aa) {
           const T a0 = Ash[(aa * 2 + 0) * 16 + b], a1 = Ash[(aa * 2 + 1) * 16 + b];
           const T b0 = a0 * t00 + a1 * t01, b1 = a0 * t10 + a1 * t11;
 #pragma unroll
-          for (int k = 0; k < 32; ++k) x[k] += Rsh[k * 32 + aa * 2] * b0 + Rsh[k * 32 + aa * 2 + 1] * b1;
+          for (int k = 0; k < KR; ++k) x[k] += Rsh[k * 32 + aa * 2] * b0 + Rsh[k * 32 + aa * 2 + 1] * b1;
         }
-      }
-      wave_sync();   // every lane has read R
+        wave_sync();   // every lane has read R
+        qr64u<32, KR>(x, rd, jmax, vb, Hb);
+      };
+      if (nrow <= 16) site(std::integral_constant<int, 16>());
+      else site(std::integral_constant<int, 32>());
       T* Qr = Qj + (int64_t)r * SITE_Q;
       if (r == L - 1) {
         // the bottom row's right bond has one value: M has the single column (0, 0), kept as is
@@ -177,15 +192,16 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
         }
         continue;
       }
-      T rd;
-      qr64u<32>(x, rd, vb, Hb);
       logs += store_r(x, rd, Rsh);
-      store_v(x, 32, Hb, Qr);
+      store_v(x, jmax, Hb, Qr);
+      if (ln == 0) refl[r] = jmax;
+      nrow = jmax;
     }
     wave_sync();
     if (last) break;
 
     // ---------------- pass 2: truncating SVD sweep, bottom row to top row ----------------
+    int nk = 1;   // the right bond
     for (int r = L - 1; r >= 0; --r) {
       // lane (l, t) = ln: y[k] = N[l][(t, k)], N = Q_r C_{r+1} (the bottom row: its own matrix)
       T y[16];
@@ -195,10 +211,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
         for (int k = 0; k < 16; ++k) y[k] = (k == 0) ? Qr[ln] : T(0);
       } else {
         T X[16];
-        apply_q(X, 32, Qr, Csh);
+        apply_q(X, __builtin_amdgcn_readfirstlane(refl[r]), Qr, Csh);
         cols_to_rows(X, Xsh, y);
       }
-      logs += svd_step(y, chi, Xsh, Csh, sig, Aj + (int64_t)r * SITE_A, false);
+      const int n = r > 0 ? __builtin_amdgcn_readfirstlane(refl[r - 1]) : 1;   // the rows of the R above
+      logs += svd_step(y, n, nk, chi, Xsh, Csh, sig, Aj + (int64_t)r * SITE_A, false, nk);
+      if (ln == 0) left[r] = nk;
     }
   }
   if (ln == 0) {

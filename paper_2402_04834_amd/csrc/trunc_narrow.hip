@@ -4,7 +4,7 @@
 //
 // What it is bound by: FP64 instruction issue and the serial chains of reflections and Jacobi rounds. Against the
 // general kernel on these shapes:
-//   * the state is held at the bonds' sizes: 165 registers and 10.3 KB of LDS, three wavefronts per SIMD instead of two
+//   * the state is held at the bonds' sizes: 167 registers and 10.3 KB of LDS, three wavefronts per SIMD instead of two
 //     (four, at 128 registers, spill 31 of them);
 //   * a bond's size is the number of singular values kept at it (those above 1e-13 of the norm: 5 on average for a 6 x 6
 //     block at chi 8), and absorptions, factorisations, reflections and Jacobi rounds leave out the rows and columns
@@ -13,7 +13,7 @@
 //     decomposed, sites a step ahead, and the column tensors are formed without their 16-entry tables.
 // Every sum keeps the order and the fusing of the general kernel's: the distance terms subtract an FP32 message from its
 // FP64 successor, so one last bit of a message is 1e-8 of a distance near convergence.
-// d = 17, 6 x 6 blocks at chi 8, 32 syndromes: 298 -> 139 ms; d = 9, 3 x 3 at chi 2, 20 syndromes: 49.4 -> 11.8 ms. (A
+// d = 17, 6 x 6 blocks at chi 8, 32 syndromes: 298 -> 124 ms; d = 9, 3 x 3 at chi 2, 20 syndromes: 49.4 -> 11.8 ms. (A
 // pivoted Householder factorisation that reveals the rank in place of the Jacobi rounds where the bond does not bind
 // took 84 ms, with distances off by up to 1e-7.)
 //
@@ -31,10 +31,7 @@
 namespace bbp {
 namespace {
 
-using wmps::JAC;
-using wmps::RANKTOL;
-using wmps::SWEEPS;
-using wmps::wave_sync;
+using namespace wmps;
 
 constexpr int B = 8, KN = 7;            // largest bond; longest sweep and widest state
 constexpr int SITE = B * 2 * B;         // one site [a][h][b], or one cap operator [P][v][Q]
@@ -54,66 +51,6 @@ constexpr int L_END = L_X + 64 * 6;
 constexpr int L_P = L_END;              // Pauli probabilities
 constexpr int L_N = L_P + 4;            // bond sizes (int)
 constexpr int L_TOTAL = L_N + 16;
-
-template <int CTRL>
-__device__ __forceinline__ double dpp(double v) {
-  const uint64_t x = __builtin_bit_cast(uint64_t, v);
-  const unsigned lo = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)x, CTRL, 0xF, 0xF, true);
-  const unsigned hi = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)(x >> 32), CTRL, 0xF, 0xF, true);
-  return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
-}
-// the two halves of an exchange of 16-lane (W = 16) or 32-lane groups: {own group's, other group's} values
-template <int W>
-__device__ __forceinline__ void halves(double v, double& a, double& b) {
-  const uint64_t x = __builtin_bit_cast(uint64_t, v);
-  const unsigned lo = (unsigned)x, hi = (unsigned)(x >> 32);
-  unsigned l0, l1, h0, h1;
-  if constexpr (W == 16) {
-    const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
-    const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
-    l0 = l[0], l1 = l[1], h0 = h[0], h1 = h[1];
-  } else {
-    const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
-    const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
-    l0 = l[0], l1 = l[1], h0 = h[0], h1 = h[1];
-  }
-  a = __builtin_bit_cast(double, (uint64_t)l0 | ((uint64_t)h0 << 32));
-  b = __builtin_bit_cast(double, (uint64_t)l1 | ((uint64_t)h1 << 32));
-}
-__device__ __forceinline__ double sum4(double v) {   // over a quad: lane ^ 1, then ^ 2
-  v += dpp<0xB1>(v);
-  return v + dpp<0x4E>(v);
-}
-__device__ __forceinline__ double sum8(double v) {   // over 8 lanes: ^ 1, ^ 2, then the other quad
-  v = sum4(v);
-  return v + dpp<0x141>(v);
-}
-// over the wavefront in the order of wmps::wsum: lane ^ 32, ^ 16, ^ 8, ^ 4, ^ 2, ^ 1 (a rotation by 4 of 16 lanes brings
-// the value of lane ^ 4 once lanes 8 apart agree)
-__device__ __forceinline__ double sum64(double v) {
-  double a, b;
-  halves<32>(v, a, b);
-  v = a + b;
-  halves<16>(v, a, b);
-  v = a + b;
-  v += dpp<0x128>(v);
-  v += dpp<0x124>(v);
-  v += dpp<0x4E>(v);
-  return v + dpp<0xB1>(v);
-}
-
-// Sum of x[k0 .. N)^2 as the general kernel forms it: the first square is added unrounded to the second, rounded one,
-// the others unrounded in turn.
-template <int N>
-__device__ __forceinline__ double squares(const double (&x)[N], int k0 = 0) {
-#pragma clang fp contract(off)
-  const double second = k0 + 1 < N ? x[k0 + 1 < N ? k0 + 1 : k0] * x[k0 + 1 < N ? k0 + 1 : k0] : 0.0;
-  double s = fma(x[k0], x[k0], second);
-#pragma unroll
-  for (int k = 0; k < N; ++k)
-    if (k >= k0 + 2) s = fma(x[k], x[k], s);
-  return s;
-}
 
 // product of the split-off norms as mantissa and exponent
 struct Scale {
@@ -139,7 +76,7 @@ __device__ __forceinline__ void chain(double* W, double* Hv, double* Hb, int K, 
     for (int c = 0; c < k; ++c) {
       const double xr = (ln < m && ln >= c) ? W[ln * n + c] : 0.0;
       const double alpha = W[c * n + c];
-      const double n2 = sum64(xr * xr);
+      const double n2 = wsum(xr * xr);
       double beta = 0.0, vj = alpha, diag = alpha;
       const double nrm = sqrt(n2);
       if (nrm > 0.0) {
@@ -205,10 +142,9 @@ __device__ __forceinline__ double factor(double (&x)[8], int jmax, double* lds, 
   const int ln = threadIdx.x, c = ln >> 2, q = ln & 3;
   double* vb = lds + L_V;
   double rd = 0.0;
-#pragma unroll
-  for (int j = 0; j < 16; ++j) {
-    if (j >= jmax) break;
-    const int kj = j >> 2, qj = j & 3;   // pivot row j = 4 kj + qj
+  for_each(std::make_integer_sequence<int, 16>(), [&](auto J) __attribute__((always_inline)) {
+    constexpr int j = decltype(J)::value, kj = j >> 2, qj = j & 3;   // pivot row j = 4 kj + qj
+    if (j >= jmax) return;
     double* v = vb + (j & 1) * 32;
     if (c == j) {
 #pragma unroll
@@ -223,13 +159,10 @@ __device__ __forceinline__ double factor(double (&x)[8], int jmax, double* lds, 
     }
     const double nrm = sqrt(sum4(squares(hv, kj)));
     const double alpha = v[j];
-    double beta = 0.0, vj = alpha, diag = alpha;
-    if (nrm > 0.0) {
-      const double sg = (alpha >= 0.0) ? 1.0 : -1.0;
-      vj = alpha + sg * nrm;
-      beta = 1.0 / (nrm * (nrm + fabs(alpha)));
-      diag = -sg * nrm;
-    }
+    const bool live = nrm > 0.0;
+    const double sg = (alpha >= 0.0) ? 1.0 : -1.0;
+    const double vj = live ? alpha + sg * nrm : alpha, diag = live ? -sg * nrm : alpha;
+    const double rec = 1.0 / (nrm * (nrm + fabs(alpha))), beta = live ? rec : 0.0;
     hv[kj] = (q == qj) ? vj : hv[kj];   // the pivot entry of the vector is v_j, not alpha
     double pw = 0.0;
 #pragma unroll
@@ -243,14 +176,14 @@ __device__ __forceinline__ double factor(double (&x)[8], int jmax, double* lds, 
       if (q == qj) x[kj] = vj;
       if (q == 0) Vg[512 + j] = beta;
     }
-  }
+  });
   double r[4];   // R's rows: the first 16
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     const int row = 4 * k + q;
     r[k] = row < c ? x[k] : (row == c ? rd : 0.0);
   }
-  const double fro = sqrt(sum64(squares(r)));
+  const double fro = sqrt(wsum(squares(r)));
   const double inv = (fro > 0.0) ? 1.0 / fro : 0.0;
   wave_sync();   // every lane has read the previous carry
 #pragma unroll
@@ -269,10 +202,9 @@ __device__ __forceinline__ double factor_top(double (&x)[8], int jmax, double* l
   const int ln = threadIdx.x, hi = ln >> 1, par = ln & 1;
   double* vb = lds + L_V;
   double rd = 0.0;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    if (j >= jmax) break;
-    const int k0 = j >> 1, jp = j & 1;
+  for_each(std::make_integer_sequence<int, 8>(), [&](auto J) __attribute__((always_inline)) {
+    constexpr int j = decltype(J)::value, k0 = j >> 1, jp = j & 1;
+    if (j >= jmax) return;
     double* v = vb + (j & 1) * 32;
     if (hi == j) {
 #pragma unroll
@@ -288,13 +220,10 @@ __device__ __forceinline__ double factor_top(double (&x)[8], int jmax, double* l
     const double pn = squares(hv, k0);
     const double nrm = sqrt(pn + dpp<0xB1>(pn));
     const double alpha = v[j];
-    double beta = 0.0, vj = alpha, diag = alpha;
-    if (nrm > 0.0) {
-      const double sg = (alpha >= 0.0) ? 1.0 : -1.0;
-      vj = alpha + sg * nrm;
-      beta = 1.0 / (nrm * (nrm + fabs(alpha)));
-      diag = -sg * nrm;
-    }
+    const bool live = nrm > 0.0;
+    const double sg = (alpha >= 0.0) ? 1.0 : -1.0;
+    const double vj = live ? alpha + sg * nrm : alpha, diag = live ? -sg * nrm : alpha;
+    const double rec = 1.0 / (nrm * (nrm + fabs(alpha))), beta = live ? rec : 0.0;
     hv[k0] = (par == jp) ? vj : hv[k0];
     double pw = 0.0;
 #pragma unroll
@@ -308,14 +237,14 @@ __device__ __forceinline__ double factor_top(double (&x)[8], int jmax, double* l
       if (par == jp) x[k0] = vj;
       if (par == 0) Vg[512 + j] = beta;
     }
-  }
+  });
   double r[8];
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
     const int row = 2 * k + par;
     r[k] = row < hi ? x[k] : (row == hi ? rd : 0.0);
   }
-  const double fro = sqrt(sum64(squares(r)));
+  const double fro = sqrt(wsum(squares(r)));
   const double inv = (fro > 0.0) ? 1.0 / fro : 0.0;
   wave_sync();
 #pragma unroll
@@ -377,10 +306,15 @@ __device__ __forceinline__ int bond(double (&y)[4], int n, int chi, double* lds,
   double y0[4];
 #pragma unroll
   for (int e = 0; e < 4; ++e) y0[e] = y[e];
-  const double thr2 = sum64(squares(y)) * (RANKTOL * RANKTOL);
+  const double thr2 = wsum(squares(y)) * (RANKTOL * RANKTOL);
+  double* own_row = Xsh + ln * XN;
+  *(d2*)own_row = d2{y[0], y[1]};
+  *(d2*)(own_row + 2) = d2{y[2], y[3]};
   for (int sw = 0; sw < SWEEPS; ++sw) {
     int rotated = 0;
     double c2max = 0.0, own = sum4(squares(y));
+    own_row[4] = own;
+    wave_sync();
     // round rd pairs rows l and pl: 15 and rd, the others (2 rd - l) mod 15, stepped by 2 each round. With n < 16 rows,
     // rounds none of whose pairs lie within them -- their row numbers add up to 2 rd mod 15, or 15 more -- do nothing.
     int cyc = (30 - l) % 15;
@@ -388,10 +322,6 @@ __device__ __forceinline__ int bond(double (&y)[4], int n, int chi, double* lds,
       const int sum = 2 * rd >= 15 ? 2 * rd - 15 : 2 * rd;
       if (n < 16 && !(sum >= 1 && sum <= 2 * n - 3) && sum + 15 > 2 * n - 3) continue;
       const int pl = (l == 15) ? rd : (l == rd) ? 15 : cyc;
-      *(d2*)&Xsh[ln * XN] = d2{y[0], y[1]};
-      *(d2*)&Xsh[ln * XN + 2] = d2{y[2], y[3]};
-      Xsh[ln * XN + 4] = own;
-      wave_sync();
       const double* P = Xsh + (4 * pl + u) * XN;
       const d2 z01 = *(const d2*)P, z23 = *(const d2*)(P + 2);
       const double z[4] = {z01[0], z01[1], z23[0], z23[1]};
@@ -403,25 +333,19 @@ __device__ __forceinline__ int bond(double (&y)[4], int n, int chi, double* lds,
       gg = sum4(gg);
       const bool lower = l < pl;
       const double al = lower ? own : other, be = lower ? other : own;
-      const double c2 = (al > thr2 && be > thr2) ? gg * gg * __builtin_amdgcn_rcp(al * be) : 0.0;
-      c2max = c2 > c2max ? c2 : c2max;
-      if (c2 > JAC * JAC) {
-        // the angle as in svd_step: tan in FP32, cos and sin in FP64 from it
-        const float zf = (float)(be - al) * __builtin_amdgcn_rcpf(2.0f * (float)gg), azf = fabsf(zf);
-        const float denf = azf + (azf < 1e18f ? __builtin_amdgcn_sqrtf(fmaf(zf, zf, 1.0f)) : azf);
-        const double tt = (double)copysignf(__builtin_amdgcn_rcpf(denf), zf);
-        const double xx = tt * tt + 1.0;
-        double cs = __builtin_amdgcn_rsq(xx);
-        cs = cs * (1.5 - 0.5 * xx * cs * cs);
-        cs = cs * (1.5 - 0.5 * xx * cs * cs);
-        const double sn = cs * tt;
-        const double sz = lower ? -sn : sn;
+      const Rotation t(al, be, gg, thr2);
+      c2max = t.c2 > c2max ? t.c2 : c2max;
+      if (t.c2 > JAC * JAC) {
+        const double sz = lower ? -t.sn : t.sn;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) y[e] = fma(sz, z[e], cs * y[e]);
-        const double cc = cs * cs;
-        own = lower ? cc * (al - 2.0 * tt * gg + tt * tt * be) : cc * (be + 2.0 * tt * gg + tt * tt * al);
+        for (int e = 0; e < 4; ++e) y[e] = fma(sz, z[e], t.cs * y[e]);
+        own = t.norm2(lower, al, be, gg);
+        *(d2*)own_row = d2{y[0], y[1]};
+        *(d2*)(own_row + 2) = d2{y[2], y[3]};
+        own_row[4] = own;
         rotated = 1;
       }
+      wave_sync();
     }
     if (!__any(rotated) || !__any(c2max >= 1e-12)) break;
   }
@@ -447,7 +371,7 @@ __device__ __forceinline__ int bond(double (&y)[4], int n, int chi, double* lds,
       else if (t == 0) site[rank * B + k0 + e] = y[e] * inv;
     }
   }
-  norm = sqrt(sum64((u == 0 && kept) ? sv * sv : 0.0));
+  norm = sqrt(wsum((u == 0 && kept) ? sv * sv : 0.0));
   const int size = __builtin_popcountll(__ballot(u == 0 && kept));
   wave_sync();
 #pragma unroll
@@ -718,7 +642,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void tr
       }
 #pragma unroll
       for (int r = 0; r < B; ++r) f += (ln < B) ? X[r] * X[r] : 0.0;
-      const double fro = sqrt(sum64(f));
+      const double fro = sqrt(wsum(f));
       const double inv = (fro > 0.0) ? 1.0 / fro : 0.0;
       if (ln < B) {
 #pragma unroll
@@ -787,13 +711,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void tr
     } else if (ln == 0) {
       w = out[0];
     }
-    w = sum64(w);
+    w = wsum(w);
     if (ln == 0) G.lnW[job * G.nblocks + s.block] = (w > 0.0) ? scale.log_value() + log(w) : NAN;
     return;
   }
   // normalised new message, damping against the old one (unit norm), distance term
   float* mo = G.msgs + (job * G.M + s.msg_out) * (int64_t)ms;
-  const double inv = 1.0 / sqrt(sum64(squares(out)));
+  const double inv = 1.0 / sqrt(wsum(squares(out)));
   double old[2], dm[2];
 #pragma unroll
   for (int r = 0; r < 2; ++r) {
@@ -801,7 +725,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void tr
     old[r] = (e < H) ? (double)mo[e] : 0.0;
     dm[r] = fma((double)a.eta, old[r], (1.0 - (double)a.eta) * out[r] * inv);
   }
-  const double ginv = 1.0 / sqrt(sum64(squares(dm)));
+  const double ginv = 1.0 / sqrt(wsum(squares(dm)));
   double df[2], sf[2];
 #pragma unroll
   for (int r = 0; r < 2; ++r) {
@@ -809,7 +733,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void tr
     sf[r] = fma(dm[r], ginv, old[r]);
     dm[r] = dm[r] * ginv;
   }
-  const double dd = sum64(squares(df)), ss = sum64(squares(sf));
+  const double dd = wsum(squares(df)), ss = wsum(squares(sf));
 #pragma unroll
   for (int r = 0; r < 2; ++r) {
     const int e = ln + 64 * r;

@@ -21,6 +21,10 @@
 //            singular vectors are the new site, N V (unit norm) the carry; the top cap takes Q C.
 //   end      the chain contracted to the dense 2^kp message; normalisation (remark 3), damping (remark 7) and
 //            distance term (remark 4) as in the dense kernels, or the closing overlap of Lemma 3.1.
+// Bound by the latency of one wavefront's chain of reflections and Jacobi rounds (few jobs) or by FP64 issue (many).
+// Bonds are tracked at the number of values kept: rows, columns, reflections and Jacobi rounds beyond them are left out
+// (they are zero and would change nothing), half the registers where a carry has at most 16 rows or a bond at most 8
+// values. d = 13, 8 x 8 blocks at chi 16, 16 syndromes: 475 -> 271 ms; d = 9, 6 x 6 at chi 12, 4: 184 -> 72 ms.
 // Sweeps whose every bond stays within 8 (trunc_shape.hpp) have a kernel of their own, trunc_narrow.hip.
 // Keeping the chi largest values at every bond is the textbook QR + truncated-SVD compression: the part left
 // of a bond is an isometry when it is truncated, so each cut keeps the chi largest Schmidt values of the
@@ -30,6 +34,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "geom.hpp"
 #include "sweep_launch.hpp"
@@ -183,6 +188,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void tr
   double* CT = ws + W_CT;
 
   __shared__ double pool[POOL];
+  __shared__ int left[KM + 2], refl[KM + 1];   // left bond of site i (1 .. kp + 1), reflections of site i (0 .. kp)
   const bool top = s.msg_top >= 0, bot = s.msg_bot >= 0, fwd = (s.frame == FRAME_E || s.frame == FRAME_S);
 
   // ---- caps and the initial state ----
@@ -208,7 +214,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void tr
       for (int w = ln; w < (1 << kp); w += 64) W[w] = (double)mbase[s.msg_init * (int64_t)ms + w];
       wave_sync();
       chain(W, Hv, Hb, kp, A + TS, false);
+      if (ln >= 1 && ln <= kp + 1) left[ln] = 1 << std::min(ln - 1, kp + 1 - ln);
     } else {
+      if (ln >= 1 && ln <= kp + 1) left[ln] = 1;
       for (int i = 1; i <= kp; ++i)
         if (ln == 0) A[i * TS] = 1.0;   // every in-leg at its only value 0
     }
@@ -221,6 +229,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void tr
 
   double logs = 0.0;
   for (int t = 0; t < kt; ++t) {
+    // cap bonds before and after this column (1 without a side message)
+    const int pq0 = 1 << std::min(t, kt - t), pq1 = 1 << std::min(t + 1, kt - t - 1);
     // ---------------- pass 1: absorb and factor, top to bottom ----------------
     double* Rsh = pool;
     double* vb = Rsh + 32 * 32;
@@ -239,7 +249,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void tr
 #pragma unroll
       for (int k = 0; k < 32; ++k) x[k] = 0.0;
       if (top) {
-        for (int P = 0; P < 16; ++P) {
+        for (int P = 0; P < pq0; ++P) {
           const double sp = Ash[P * 16 + d];
 #pragma unroll
           for (int k = 0; k < 8; ++k) x[k] += sp * CTs[P * 32 + v * 16 + 2 * k + par];
@@ -248,32 +258,43 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void tr
         x[0] = Ash[d];
       }
     }
-    qr64u<16, 8>(x, rd, vb, Hb);   // rows q' < 16: registers k < 8
+    // rows q' < 16: registers k < 8. nrow: the rows of R that can be nonzero
+    int nrow = __builtin_amdgcn_readfirstlane(std::min(top ? pq1 : 1, 2 * left[1]));
+    qr64u<16, 8>(x, rd, nrow, vb, Hb);
     logs += store_r(x, rd, Rsh);
-    store_v(x, 16, Hb, Q);
+    store_v(x, nrow, Hb, Q);
+    if (ln == 0) refl[0] = nrow;
     // crossing sites: M [(k, h)][(b, dn)] = sum_(a, u) R[k][(a, u)] (A_i T)[(a, u)][(h, b, dn)], factored
     for (int i = 1; i <= kp; ++i) {
       for (int e = ln; e < TS; e += 64) Ash[e] = A[i * TS + e];
       wave_sync();
-      {
-        const int b = hi >> 1, dn = hi & 1;
-        const double t00 = tab(s, L, lab, pq, t, i - 1, 0 * 8 + 0 * 4 + dn * 2 + par);
-        const double t01 = tab(s, L, lab, pq, t, i - 1, 0 * 8 + 1 * 4 + dn * 2 + par);
-        const double t10 = tab(s, L, lab, pq, t, i - 1, 1 * 8 + 0 * 4 + dn * 2 + par);
-        const double t11 = tab(s, L, lab, pq, t, i - 1, 1 * 8 + 1 * 4 + dn * 2 + par);
+      const int na = __builtin_amdgcn_readfirstlane(left[i]), nb = __builtin_amdgcn_readfirstlane(left[i + 1]);
+      const int jmax = std::min(2 * nrow, 2 * nb);
+      const int b = hi >> 1, dn = hi & 1;
+      const double t00 = tab(s, L, lab, pq, t, i - 1, 0 * 8 + 0 * 4 + dn * 2 + par);
+      const double t01 = tab(s, L, lab, pq, t, i - 1, 0 * 8 + 1 * 4 + dn * 2 + par);
+      const double t10 = tab(s, L, lab, pq, t, i - 1, 1 * 8 + 0 * 4 + dn * 2 + par);
+      const double t11 = tab(s, L, lab, pq, t, i - 1, 1 * 8 + 1 * 4 + dn * 2 + par);
 #pragma unroll
-        for (int k = 0; k < 32; ++k) x[k] = 0.0;
-        for (int aa = 0; aa < 16; ++aa) {
+      for (int k = 0; k < 32; ++k) x[k] = 0.0;
+      // x[k] belongs to R's row k
+      auto site = [&](auto rows) __attribute__((always_inline)) {
+        constexpr int KR = decltype(rows)::value;
+        for (int aa = 0; aa < na; ++aa) {
           const double a0 = Ash[(aa * 2 + 0) * 16 + b], a1 = Ash[(aa * 2 + 1) * 16 + b];
           const double b0 = a0 * t00 + a1 * t01, b1 = a0 * t10 + a1 * t11;
 #pragma unroll
-          for (int k = 0; k < 32; ++k) x[k] += Rsh[k * 32 + aa * 2] * b0 + Rsh[k * 32 + aa * 2 + 1] * b1;
+          for (int k = 0; k < KR; ++k) x[k] += Rsh[k * 32 + aa * 2] * b0 + Rsh[k * 32 + aa * 2 + 1] * b1;
         }
-      }
-      wave_sync();   // every lane has read R
-      qr64u<32>(x, rd, vb, Hb);
+        wave_sync();   // every lane has read R
+        qr64u<32, KR>(x, rd, jmax, vb, Hb);
+      };
+      if (nrow <= 16) site(std::integral_constant<int, 16>());
+      else site(std::integral_constant<int, 32>());
       logs += store_r(x, rd, Rsh);
-      store_v(x, 32, Hb, Q + i * TQ);
+      store_v(x, jmax, Hb, Q + i * TQ);
+      if (ln == 0) refl[i] = jmax;
+      nrow = jmax;
     }
     // bottom cap: Bb[(d, v)][q'] = sum_P S[d][P] CT[P][v][q'], then M[l][q'] = sum R[l][(d, v)] Bb[(d, v)][q']
     for (int e = ln; e < 256; e += 64) Ash[e] = A[(kp + 1) * TS + e];
@@ -287,7 +308,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void tr
         const int e = ln + 64 * u, dv = e >> 4, q = e & 15, d = dv >> 1, v = dv & 1;
         double acc = 0.0;
         if (bot) {
-          for (int P = 0; P < 16; ++P) acc += Ash[d * 16 + P] * CTs[P * 32 + v * 16 + q];
+          for (int P = 0; P < pq0; ++P) acc += Ash[d * 16 + P] * CTs[P * 32 + v * 16 + q];
         } else if (v == 0 && q == 0) {
           acc = Ash[d * 16];
         }
@@ -300,12 +321,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void tr
     wave_sync();
     {
       double* Mg = Q + (kp + 1) * TQ;
+      const int nd = __builtin_amdgcn_readfirstlane(left[kp + 1]);
 #pragma unroll 1
       for (int qq = 0; qq < 8; ++qq) {
         const int q = 8 * par + qq;
         double acc = 0.0;
-#pragma unroll 8
-        for (int dv = 0; dv < 32; ++dv) acc += Rsh[hi * 32 + dv] * Bb[dv * 16 + q];
+#pragma unroll 4
+        for (int dv = 0; dv < 2 * nd; ++dv) acc += Rsh[hi * 32 + dv] * Bb[dv * 16 + q];
         Mg[hi * 16 + q] = acc;
       }
     }
@@ -315,6 +337,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void tr
     double* Xsh = pool;
     double* Csh = Xsh + 64 * XS;
     double* sig = Csh + 32 * 16;
+    int nk = bot ? pq1 : 1;   // the right bond
     for (int i = kp + 1; i >= 1; --i) {
       const double* Mg = Q + (kp + 1) * TQ;   // the bottom cap's M [l][q']
       double y[16];
@@ -324,16 +347,18 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void tr
       } else {
         // N = Q_i C, then from the column layout to rows: lane (l, t) takes N[l][(t, k)] = X[2l + t][k]
         double X[16];
-        apply_q(X, 32, Q + i * TQ, Csh);
+        apply_q(X, __builtin_amdgcn_readfirstlane(refl[i]), Q + i * TQ, Csh);
         cols_to_rows(X, Xsh, y);
       }
-      logs += svd_step(y, chi, Xsh, Csh, sig, A + i * TS, i == kp + 1);
+      // (N has the rows of site i - 1's R)
+      logs += svd_step(y, __builtin_amdgcn_readfirstlane(refl[i - 1]), nk, chi, Xsh, Csh, sig, A + i * TS, i == kp + 1, nk);
+      if (ln == 0) left[i] = nk;
     }
     // top cap: S_0[q'][j] = sum_m Q_0[q'][m] C[m][j], unit Frobenius norm
     {
       // rows q' < 16 of Q_0 C sit in the lanes of quarter 0: S_0[q'][kc] = X[q']
       double X[16];
-      apply_q(X, 16, Q, Csh);
+      apply_q(X, __builtin_amdgcn_readfirstlane(refl[0]), Q, Csh);
       double f = 0.0;
 #pragma unroll
       for (int r = 0; r < 16; ++r) f += (ln < 16) ? X[r] * X[r] : 0.0;

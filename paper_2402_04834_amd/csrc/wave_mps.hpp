@@ -16,6 +16,9 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 
+#include <type_traits>
+#include <utility>
+
 namespace bbp {
 namespace wmps {
 
@@ -34,10 +37,64 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Lane exchanges by DPP and lane swaps: no LDS round trip as a shuffle takes.
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+  const uint64_t x = __builtin_bit_cast(uint64_t, v);
+  const unsigned lo = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)x, CTRL, 0xF, 0xF, true);
+  const unsigned hi = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)(x >> 32), CTRL, 0xF, 0xF, true);
+  return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
+}
+// the two halves of an exchange of 16-lane (W = 16) or 32-lane groups: {own group's, other group's} values
+template <int W>
+__device__ __forceinline__ void halves(double v, double& a, double& b) {
+  const uint64_t x = __builtin_bit_cast(uint64_t, v);
+  const unsigned lo = (unsigned)x, hi = (unsigned)(x >> 32);
+  unsigned l0, l1, h0, h1;
+  if constexpr (W == 16) {
+    const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    l0 = l[0], l1 = l[1], h0 = h[0], h1 = h[1];
+  } else {
+    const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    l0 = l[0], l1 = l[1], h0 = h[0], h1 = h[1];
+  }
+  a = __builtin_bit_cast(double, (uint64_t)l0 | ((uint64_t)h0 << 32));
+  b = __builtin_bit_cast(double, (uint64_t)l1 | ((uint64_t)h1 << 32));
+}
+__device__ __forceinline__ double sum4(double v) {   // over a quad: lane ^ 1, then ^ 2
+  v += dpp<0xB1>(v);
+  return v + dpp<0x4E>(v);
+}
+__device__ __forceinline__ double sum8(double v) {   // over 8 lanes: ^ 1, ^ 2, then the other quad
+  v = sum4(v);
+  return v + dpp<0x141>(v);
+}
+// over the wavefront: lane ^ 32, ^ 16, ^ 8, ^ 4, ^ 2, ^ 1 (a rotation by 4 of 16 lanes brings the value of lane ^ 4 once
+// lanes 8 apart agree)
 __device__ __forceinline__ double wsum(double v) {
+  double a, b;
+  halves<32>(v, a, b);
+  v = a + b;
+  halves<16>(v, a, b);
+  v = a + b;
+  v += dpp<0x128>(v);
+  v += dpp<0x124>(v);
+  v += dpp<0x4E>(v);
+  return v + dpp<0xB1>(v);
+}
+
+// Sum of x[k0 .. N)^2: the first square is added unrounded to the second, rounded one, the others unrounded in turn.
+template <int N>
+__device__ __forceinline__ double squares(const double (&x)[N], int k0 = 0) {
+#pragma clang fp contract(off)
+  const double second = k0 + 1 < N ? x[k0 + 1 < N ? k0 + 1 : k0] * x[k0 + 1 < N ? k0 + 1 : k0] : 0.0;
+  double s = fma(x[k0], x[k0], second);
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  return v;
+  for (int k = 0; k < N; ++k)
+    if (k >= k0 + 2) s = fma(x[k], x[k], s);
+  return s;
 }
 
 __device__ __forceinline__ double wmax(double v) {
@@ -46,98 +103,53 @@ __device__ __forceinline__ double wmax(double v) {
   return v;
 }
 
-// Householder QR of the 64 x 32 matrix held as x[k] = M[2k + par][hi] by lane (hi, par), reflections j < jmax.
-// On return x holds R above the diagonal and reflection vector j (pivot entry v_j) from the diagonal down in
-// lanes hi = j, rd the diagonal entry of R of the lane's column, Hb[j] the coefficients.
-__device__ __forceinline__ void qr64(double (&x)[32], double& rd, int jmax, double* vb, double* Hb) {
-  const int ln = threadIdx.x, hi = ln >> 1, par = ln & 1;
-  rd = 0.0;
-  for (int j = 0; j < jmax; ++j) {
-    double* v = vb + (j & 1) * 64;
-    if (hi == j) {
-#pragma unroll
-      for (int k = 0; k < 32; ++k) v[2 * k + par] = (2 * k + par >= j) ? x[k] : 0.0;
-    }
-    wave_sync();
-    double hv[32], pn = 0.0;
-#pragma unroll
-    for (int k = 0; k < 32; ++k) {
-      hv[k] = v[2 * k + par];
-      pn += hv[k] * hv[k];
-    }
-    const double nrm = sqrt(pn + __shfl_xor(pn, 1));
-    const double alpha = v[j];
-    double beta = 0.0, vj = alpha, diag = alpha;
-    if (nrm > 0.0) {
-      const double sg = (alpha >= 0.0) ? 1.0 : -1.0;
-      vj = alpha + sg * nrm;
-      beta = 1.0 / (nrm * (nrm + fabs(alpha)));
-      diag = -sg * nrm;
-    }
-    // the pivot entry of the vector is v_j, not alpha: one select per entry, then plain products
-    double pw = 0.0;
-#pragma unroll
-    for (int k = 0; k < 32; ++k) {
-      hv[k] = (2 * k + par == j) ? vj : hv[k];
-      pw += hv[k] * x[k];
-    }
-    const double w = (pw + __shfl_xor(pw, 1)) * beta;
-    if (hi > j) {
-#pragma unroll
-      for (int k = 0; k < 32; ++k) x[k] -= w * hv[k];
-    } else if (hi == j) {
-      rd = diag;
-#pragma unroll
-      for (int k = 0; k < 32; ++k)
-        if (2 * k + par == j) x[k] = vj;
-    }
-    if (ln == 0) Hb[j] = beta;
-  }
-  wave_sync();
+// f(0), f(1), ... with compile-time arguments (a loop that may end early is not unrolled fully by the compiler, and its
+// registers would be indexed in scratch memory)
+template <class F, int... J>
+__device__ __forceinline__ void for_each(std::integer_sequence<int, J...>, F&& f) {
+  (f(std::integral_constant<int, J>()), ...);
 }
 
-// qr64 with the reflections unrolled (JMAX = jmax): reflection j touches rows >= j only, i.e. registers
-// k >= j / 2, and its pivot row is a compile-time register, so the vector's rows above the pivot are neither
-// stored, read nor multiplied, and the pivot takes one select instead of one per register. KR: only rows
-// below 2 KR can be nonzero (x[k] = 0 for k >= KR, left untouched), as in a cap's 16-row matrix; the
-// rolled form with 64 rows kept x in scratch memory there. (An unrolled instance with 16 reflections over
-// all 32 registers beside the 32-reflection one took the compiler beyond 40 minutes.)
+// Householder QR of the 64 x 32 matrix held as x[k] = M[2k + par][hi] by lane (hi, par), reflections j < jmax <= JMAX
+// (uniform; those beyond the matrix's nonzero rows or columns would do nothing). On return x holds R above the diagonal
+// and reflection vector j (pivot entry v_j) from the diagonal down in lanes hi = j, rd the diagonal entry of R of the
+// lane's column, Hb[j] the coefficients. The reflections are unrolled: reflection j touches registers k >= j / 2 only,
+// and its pivot is a compile-time register. KR: only rows below 2 KR can be nonzero (x[k] = 0 for k >= KR, untouched), as
+// in a cap's 16-row matrix, or a site's when the carry has at most 16 rows.
 template <int JMAX, int KR = 32>
-__device__ __forceinline__ void qr64u(double (&x)[32], double& rd, double* vb, double* Hb) {
+__device__ __forceinline__ void qr64u(double (&x)[32], double& rd, int jmax, double* vb, double* Hb) {
   static_assert(KR <= 32 && JMAX <= 2 * KR, "reflections within the nonzero rows");
   const int ln = threadIdx.x, hi = ln >> 1, par = ln & 1;
   rd = 0.0;
-#pragma unroll
-  for (int j = 0; j < JMAX; ++j) {
-    const int k0 = j >> 1, jp = j & 1;   // pivot row j = 2 k0 + jp
+  for_each(std::make_integer_sequence<int, JMAX>(), [&](auto J) __attribute__((always_inline)) {
+    constexpr int j = decltype(J)::value, k0 = j >> 1, jp = j & 1;   // pivot row j = 2 k0 + jp
+    if (j >= jmax) return;
     double* v = vb + (j & 1) * 64;
     if (hi == j) {
 #pragma unroll
       for (int k = k0; k < KR; ++k) v[2 * k + par] = x[k];
     }
     wave_sync();
-    double hv[32], pn = 0.0;
+    double hv[KR];
 #pragma unroll
     for (int k = k0; k < KR; ++k) {
       hv[k] = v[2 * k + par];
       if (k == k0 && jp == 1) hv[k] = par ? hv[k] : 0.0;   // row 2 k0 < j is not part of the vector
-      pn += hv[k] * hv[k];
     }
-    const double nrm = sqrt(pn + __shfl_xor(pn, 1));
-    const double alpha = v[j];
-    double beta = 0.0, vj = alpha, diag = alpha;
-    if (nrm > 0.0) {
-      const double sg = (alpha >= 0.0) ? 1.0 : -1.0;
-      vj = alpha + sg * nrm;
-      beta = 1.0 / (nrm * (nrm + fabs(alpha)));
-      diag = -sg * nrm;
-    }
+    const double pn = squares<KR>(hv, k0);
+    // (a cap's last row: its own square is added unrounded)
+    const double n2 = (KR == 8 && k0 == KR - 1) ? fma(hv[k0], hv[k0], dpp<0xB1>(pn)) : pn + dpp<0xB1>(pn);
+    const double nrm = sqrt(n2), alpha = v[j];
+    const bool live = nrm > 0.0;
+    const double sg = (alpha >= 0.0) ? 1.0 : -1.0;
+    const double vj = live ? alpha + sg * nrm : alpha, diag = live ? -sg * nrm : alpha;
+    const double rec = 1.0 / (nrm * (nrm + fabs(alpha))), beta = live ? rec : 0.0;
     // the pivot entry of the vector is v_j, not alpha
     hv[k0] = (par == jp) ? vj : hv[k0];
     double pw = 0.0;
 #pragma unroll
     for (int k = k0; k < KR; ++k) pw += hv[k] * x[k];
-    const double w = (pw + __shfl_xor(pw, 1)) * beta;
+    const double w = (pw + dpp<0xB1>(pw)) * beta;
     if (hi > j) {
 #pragma unroll
       for (int k = k0; k < KR; ++k) x[k] -= w * hv[k];
@@ -146,11 +158,11 @@ __device__ __forceinline__ void qr64u(double (&x)[32], double& rd, double* vb, d
       if (par == jp) x[k0] = vj;
     }
     if (ln == 0) Hb[j] = beta;
-  }
+  });
   wave_sync();
 }
 
-// The reflection vectors left in x by qr64 (rows >= j of column j, zero above) and their coefficients into a
+// The reflection vectors left in x by qr64u (rows >= j of column j, zero above) and their coefficients into a
 // pass-1 factor slot: Vg[j * 64 + row], Vg[2048 + j].
 __device__ __forceinline__ void store_v(const double (&x)[32], int jmax, const double* Hb, double* Vg) {
   const int ln = threadIdx.x, hi = ln >> 1, par = ln & 1;
@@ -175,32 +187,37 @@ __device__ __forceinline__ void apply_q(double (&X)[16], int jmax, const double*
     const int row = qt * 16 + r;
     X[r] = (row < 32) ? Csh[row * 16 + kc] : 0.0;
   }
-  // the next reflection's vector quarter and coefficient are loaded while this one is applied (the loads
-  // come from the workspace, through L2: one reflection's latency each, otherwise)
-  double vn[16], bn = 0.0;
-  if (jmax > 0) {
+  // the vector quarters and coefficients of the next two reflections are loaded while one is applied (the loads come
+  // from the workspace, through L2: one reflection's latency each, otherwise)
+  double vn[3][16], bn[3];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) vn[r] = Vg[(jmax - 1) * 64 + qt * 16 + r];
-    bn = Vg[2048 + jmax - 1];
+  for (int u = 0; u < 3; ++u) {
+    const int j = jmax - 1 - u > 0 ? jmax - 1 - u : 0;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) vn[u][r] = Vg[j * 64 + qt * 16 + r];
+    bn[u] = Vg[2048 + j];
   }
-  for (int j = jmax - 1; j >= 0; --j) {
-    double v[16];
+  for (int j0 = jmax - 1; j0 >= 0; j0 -= 3) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) v[r] = vn[r];
-    const double beta = bn;
-    if (j > 0) {
+    for (int u = 0; u < 3; ++u) {
+      const int j = j0 - u;
+      if (j < 0) break;
+      double p = 0.0, a, b;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) vn[r] = Vg[(j - 1) * 64 + qt * 16 + r];
-      bn = Vg[2048 + j - 1];
+      for (int r = 0; r < 16; ++r) p += vn[u][r] * X[r];
+      halves<16>(p, a, b);
+      p = a + b;
+      halves<32>(p, a, b);
+      p = a + b;
+      const double w = p * bn[u];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) X[r] -= w * vn[u][r];
+      if (j >= 3) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) vn[u][r] = Vg[(j - 3) * 64 + qt * 16 + r];
+        bn[u] = Vg[2048 + j - 3];
+      }
     }
-    double p = 0.0;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) p += v[r] * X[r];
-    p += __shfl_xor(p, 16);
-    p += __shfl_xor(p, 32);
-    const double w = p * beta;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) X[r] -= w * v[r];
   }
 }
 
@@ -218,98 +235,110 @@ __device__ __forceinline__ void cols_to_rows(const double (&X)[16], double* Xsh,
 // The carry R (rows 0..31 of the factored matrix) into Rsh [row][col], unit Frobenius norm; returns ln |R|_F.
 __device__ __forceinline__ double store_r(const double (&x)[32], double rd, double* Rsh) {
   const int ln = threadIdx.x, hi = ln >> 1, par = ln & 1;
-  double f = 0.0;
+  double r[16];
 #pragma unroll
   for (int k = 0; k < 16; ++k) {
     const int row = 2 * k + par;
-    const double r = row < hi ? x[k] : (row == hi ? rd : 0.0);
-    f += r * r;
+    r[k] = row < hi ? x[k] : (row == hi ? rd : 0.0);
   }
-  const double fro = sqrt(wsum(f));
+  const double fro = sqrt(wsum(squares(r)));
   const double inv = (fro > 0.0) ? 1.0 / fro : 0.0;
 #pragma unroll
   for (int k = 0; k < 16; ++k) {
     const int row = 2 * k + par;
-    Rsh[row * 32 + hi] = (row < hi ? x[k] : (row == hi ? rd : 0.0)) * inv;
+    Rsh[row * 32 + hi] = r[k] * inv;
   }
   wave_sync();
   return log(fro);
 }
 
-// One-sided Jacobi SVD of the 32 x 32 matrix N held as y[k] = N[l][(par, k)] by lane (l = hi, par), the chi
-// largest singular values kept. Writes the kept right singular vectors (rows j < 16 of V, zero beyond chi) as
-// site [j][par][k] (or, bottom cap, [j][k] from the par = 0 half) and the carry C = N V / |.|_F into Csh
-// [l][j]; returns the log of that norm.
-__device__ __forceinline__ double svd_step(double (&y)[16], int chi, double* Xsh, double* Csh, double* sig,
-                                           double* site, bool bottom) {
+// Rotation of two rows with squared norms al, be and product gg.
+struct Rotation {
+  double c2, cs, sn, tt;
+  __device__ __forceinline__ Rotation(double al, double be, double gg, double thr2) {
+    // squared cosine of the pair (approximate reciprocal: it only decides whether to rotate)
+    c2 = (al > thr2 && be > thr2) ? gg * gg * __builtin_amdgcn_rcp(al * be) : 0.0;
+    // The angle only has to bring the pair closer to orthogonal, so t = tan(theta) (the smaller root) is formed in FP32
+    // (the hardware's approximate reciprocal and square root, one instruction each; above the noise threshold zeta stays
+    // within 1e30); cos and sin are then formed in FP64 from that t, so that the rotation is orthogonal to FP64
+    // rounding. (Formed for every pair, used or not: the chain runs beside that of c2.)
+    const float zf = (float)(be - al) * __builtin_amdgcn_rcpf(2.0f * (float)gg), azf = fabsf(zf);
+    const float denf = azf + (azf < 1e18f ? __builtin_amdgcn_sqrtf(fmaf(zf, zf, 1.0f)) : azf);
+    tt = (double)copysignf(__builtin_amdgcn_rcpf(denf), zf);
+    const double xx = fma(tt, tt, 1.0);
+    cs = __builtin_amdgcn_rsq(xx);
+    cs = cs * (1.5 - 0.5 * xx * cs * cs);
+    cs = cs * (1.5 - 0.5 * xx * cs * cs);
+    sn = cs * tt;
+  }
+  // squared norm of the lower or the higher row afterwards
+  __device__ __forceinline__ double norm2(bool lower, double al, double be, double gg) const {
+    const double cc = cs * cs;
+    return lower ? cc * (al - 2.0 * tt * gg + tt * tt * be) : cc * (be + 2.0 * tt * gg + tt * tt * al);
+  }
+};
+
+// One-sided Jacobi SVD of the 32 x 32 matrix N held as y[k] = N[l][(par, k)] by lane (l = hi, par), its entries
+// k >= KE and rows l >= n zero, the chi largest singular values kept. Writes the kept right singular vectors (rows j < 16 of V, zero
+// beyond chi) as site [j][par][k] (or, bottom cap, [j][k] from the par = 0 half) and the carry C = N V / |.|_F into Csh
+// [l][j]; returns the log of that norm, and in size the number of values kept.
+template <int KE>
+__device__ __forceinline__ double svd_rows(const double (&yin)[16], int chi, double* Xsh, double* Csh, double* sig,
+                                           double* site, bool bottom, int n, int& size) {
   const int ln = threadIdx.x, hi = ln >> 1, par = ln & 1;
-  double y0[16];
+  double y[KE], y0[KE];
 #pragma unroll
-  for (int k = 0; k < 16; ++k) y0[k] = y[k];
-  double nf2 = 0.0;
+  for (int k = 0; k < KE; ++k) y[k] = y0[k] = yin[k];
+  const double thr2 = wsum(squares(y)) * (RANKTOL * RANKTOL);
+  double* own_row = Xsh + ln * XS;
 #pragma unroll
-  for (int k = 0; k < 16; ++k) nf2 += y[k] * y[k];
-  const double thr2 = wsum(nf2) * (RANKTOL * RANKTOL);
+  for (int k = 0; k < KE; ++k) own_row[k] = y[k];
   for (int sw = 0; sw < SWEEPS; ++sw) {
     int rotated = 0;
     double c2max = 0.0;
-    double own = 0.0;
-#pragma unroll
-    for (int k = 0; k < 16; ++k) own += y[k] * y[k];
-    own += __shfl_xor(own, 1);
-    // round rd pairs rows hi and pl: 31 and rd, the others (2 rd - hi) mod 31, stepped by 2 each round
+    double own = squares(y);
+    own += dpp<0xB1>(own);
+    own_row[16] = own;
+    wave_sync();
+    // round rd pairs rows hi and pl: 31 and rd, the others (2 rd - hi) mod 31, stepped by 2 each round. With n <= 16
+    // rows only sums 1 .. 2 n - 3 of two row numbers occur: the other rounds would do nothing.
     int cyc = (62 - hi) % 31;
     for (int rd = 0; rd < 31; ++rd, cyc = (cyc + 2 >= 31) ? cyc + 2 - 31 : cyc + 2) {
+      const int sum = 2 * rd >= 31 ? 2 * rd - 31 : 2 * rd;
+      if (n <= 16 && (sum < 1 || sum > 2 * n - 3)) continue;
       const int pl = (hi == 31) ? rd : (hi == rd) ? 31 : cyc;
+      double z[KE], gg = 0.0;
 #pragma unroll
-      for (int k = 0; k < 16; ++k) Xsh[ln * XS + k] = y[k];
-      Xsh[ln * XS + 16] = own;
-      wave_sync();
-      double z[16], gg = 0.0;
-#pragma unroll
-      for (int k = 0; k < 16; ++k) {
+      for (int k = 0; k < KE; ++k) {
         z[k] = Xsh[(2 * pl + par) * XS + k];
         gg += y[k] * z[k];
       }
       const double other = Xsh[(2 * pl + par) * XS + 16];
       wave_sync();
-      gg += __shfl_xor(gg, 1);
+      gg += dpp<0xB1>(gg);
       const bool lower = hi < pl;
       const double al = lower ? own : other, be = lower ? other : own;
-      // squared cosine of the pair (approximate reciprocal: it only decides whether to rotate)
-      const double c2 = (al > thr2 && be > thr2) ? gg * gg * __builtin_amdgcn_rcp(al * be) : 0.0;
-      c2max = c2 > c2max ? c2 : c2max;
-      if (c2 > JAC * JAC) {
-        // The angle only has to bring the pair closer to orthogonal, so t = tan(theta) (the smaller root) is
-        // formed in FP32 (the hardware's approximate reciprocal and square root, one instruction each; above the
-        // noise threshold zeta stays within 1e30);
-        // cos and sin are then formed in FP64 from that t, so that the rotation is orthogonal to FP64
-        // rounding.
-        const float zf = (float)(be - al) * __builtin_amdgcn_rcpf(2.0f * (float)gg), azf = fabsf(zf);
-        const float denf = azf + (azf < 1e18f ? __builtin_amdgcn_sqrtf(fmaf(zf, zf, 1.0f)) : azf);
-        const double tt = (double)copysignf(__builtin_amdgcn_rcpf(denf), zf);
-        const double xx = tt * tt + 1.0;
-        double cs = __builtin_amdgcn_rsq(xx);
-        cs = cs * (1.5 - 0.5 * xx * cs * cs);
-        cs = cs * (1.5 - 0.5 * xx * cs * cs);
-        const double sn = cs * tt;
-        // lower row p: c p - s q; higher row q: c q + s p -- one multiply and one fused multiply-add each
-        const double sz = lower ? -sn : sn;
+      const Rotation t(al, be, gg, thr2);
+      c2max = t.c2 > c2max ? t.c2 : c2max;
+      if (t.c2 > JAC * JAC) {
+        // lower row p: c p - s q; higher row q: c q + s p -- one multiply and one fused multiply-add each. Only rows
+        // that turn are written again.
+        const double sz = lower ? -t.sn : t.sn;
 #pragma unroll
-        for (int k = 0; k < 16; ++k) y[k] = fma(sz, z[k], cs * y[k]);
-        const double cc = cs * cs;
-        own = lower ? cc * (al - 2.0 * tt * gg + tt * tt * be) : cc * (be + 2.0 * tt * gg + tt * tt * al);
+        for (int k = 0; k < KE; ++k) y[k] = fma(sz, z[k], t.cs * y[k]);
+        own = t.norm2(lower, al, be, gg);
+#pragma unroll
+        for (int k = 0; k < KE; ++k) own_row[k] = y[k];
+        own_row[16] = own;
         rotated = 1;
       }
+      wave_sync();
     }
     // a sweep whose pairs all started within cos 1e-6 of orthogonal leaves them within about 1e-12
     // (quadratic convergence): far below the FP32 messages the singular vectors end up in
-    if (!__any(rotated) || wmax(c2max) < 1e-12) break;
+    if (!__any(rotated) || !__any(c2max >= 1e-12)) break;
   }
-  double s2 = 0.0;
-#pragma unroll
-  for (int k = 0; k < 16; ++k) s2 += y[k] * y[k];
-  const double s2r = s2 + __shfl_xor(s2, 1);
+  const double s2 = squares(y), s2r = s2 + dpp<0xB1>(s2);
   const double sv = (s2r > thr2) ? sqrt(s2r) : 0.0;
   const double key = (sv == sv) ? sv : -1.0;
   if (par == 0) sig[hi] = key;
@@ -325,27 +354,38 @@ __device__ __forceinline__ double svd_step(double (&y)[16], int chi, double* Xsh
   if (rank < 16) {
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
+      const double v = k < KE ? y[k < KE ? k : 0] * inv : 0.0;
       if (bottom) {
-        if (par == 0) site[rank * 16 + k] = y[k] * inv;
+        if (par == 0) site[rank * 16 + k] = v;
       } else {
-        site[(rank * 2 + par) * 16 + k] = y[k] * inv;
+        site[(rank * 2 + par) * 16 + k] = v;
       }
-      Vsh[rank * 32 + par * 16 + k] = y[k] * inv;
+      if (k < KE) Vsh[rank * 32 + par * 16 + k] = v;
     }
   }
+  size = __builtin_popcountll(__ballot(par == 0 && kept));
   const double fro = sqrt(wsum((par == 0 && kept) ? sv * sv : 0.0));
   wave_sync();
   const double finv = (fro > 0.0) ? 1.0 / fro : 0.0;
 #pragma unroll
   for (int j = 0; j < 16; ++j) {
     double acc = 0.0;
+    if (j < size) {
 #pragma unroll
-    for (int k = 0; k < 16; ++k) acc += y0[k] * Vsh[j * 32 + par * 16 + k];
-    acc += __shfl_xor(acc, 1);
+      for (int k = 0; k < KE; ++k) acc += y0[k] * Vsh[j * 32 + par * 16 + k];
+      acc += dpp<0xB1>(acc);
+    }
     if ((j >> 3) == par) Csh[hi * 16 + j] = acc * finv;
   }
   wave_sync();
   return log(fro);
+}
+
+// (nk: the size of the right bond)
+__device__ __forceinline__ double svd_step(const double (&y)[16], int n, int nk, int chi, double* Xsh, double* Csh,
+                                           double* sig, double* site, bool bottom, int& size) {
+  if (nk <= 8) return svd_rows<8>(y, chi, Xsh, Csh, sig, site, bottom, n, size);
+  return svd_rows<16>(y, chi, Xsh, Csh, sig, site, bottom, n, size);
 }
 
 }  // namespace wmps
