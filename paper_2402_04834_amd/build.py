@@ -29,7 +29,7 @@ FLAGS = [
 FUSED_SHAPES = [(6, 1), (6, 3), (6, 5), (5, 0), (5, 1), (5, 2), (5, 3), (5, 4), (4, 1), (4, 3), (3, 0), (3, 1), (3, 2)]
 
 # (source, extra flags, object name), the longest compiles first
-UNITS = [(f"{n}.hip", [], f"{n}.o") for n in ("trunc_sweep", "trunc_narrow", "bmps", "warm")] + [
+UNITS = [(f"{n}.hip", [], f"{n}.o") for n in ("trunc_sweep", "trunc_narrow", "bmps", "warm", "small_loop")] + [
     ("sweep_kernel.hip", [f"-DBBP_KT={t}", f"-DBBP_KP={p}"], f"sweep_{t}x{p}.o")
     for t in range(6, 0, -1) for p in range(6, 0, -1)
 ] + [

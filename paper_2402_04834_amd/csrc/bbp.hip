@@ -344,10 +344,46 @@ int fused_shape(const bbp::Plan& p) {
   return -1;
 }
 
+// A list of sweeps of blocks of at most 2x2 for small_loop.hip, equal kinds together, those at the grid's edge last;
+// apart: filled up with empty entries so that no wavefront holds two kinds.
+std::vector<bbp::SmallSweep> small_list(const std::vector<SweepDesc>& v, bool apart) {
+  std::vector<bbp::SmallSweep> w;
+  for (const SweepDesc& s : v) {
+    bbp::SmallSweep x;
+    std::memset(&x, 0, sizeof(x));
+    x.r0 = (int16_t)s.r0;
+    x.c0 = (int16_t)s.c0;
+    const int q00 = ((s.r0 + s.c0) & 1) == 0;
+    x.kind = (s.kr == 2) << 4 | (s.kc == 2) << 3 | q00 << 2 | s.frame;
+    x.m[s.frame] = s.msg_close;   // (-1 for an update)
+    x.m[s.frame ^ 1] = s.msg_init;
+    x.m[s.frame <= bbp::FRAME_W ? bbp::FRAME_N : bbp::FRAME_W] = s.msg_top;
+    x.m[s.frame <= bbp::FRAME_W ? bbp::FRAME_S : bbp::FRAME_E] = s.msg_bot;
+    x.out = s.msg_out >= 0 ? s.msg_out : s.block;
+    w.push_back(x);
+  }
+  auto edges = [](const bbp::SmallSweep& x) { return (x.m[0] < 0) + (x.m[1] < 0) + (x.m[2] < 0) + (x.m[3] < 0); };
+  std::stable_sort(w.begin(), w.end(), [&](const bbp::SmallSweep& a, const bbp::SmallSweep& b) {
+    return a.kind != b.kind ? a.kind > b.kind : edges(a) < edges(b);
+  });
+  if (!apart) return w;
+  std::vector<bbp::SmallSweep> x;
+  for (size_t i = 0; i < w.size(); ++i) {
+    bbp::SmallSweep none = w[i];
+    none.kind = -1;
+    if (i > 0 && w[i].kind != w[i - 1].kind) x.resize((x.size() + 63) / 64 * 64, none);
+    x.push_back(w[i]);
+  }
+  return x;
+}
+
 struct DevPlan {
   bbp::Plan plan;
   SweepDesc* round[2] = {nullptr, nullptr};
   SweepDesc* bethe = nullptr;
+  // the lists for small_loop.hip (blocks of at most 2x2), dense and with every kind in wavefronts of its own
+  bbp::SmallSweep* small[2][3] = {{nullptr, nullptr, nullptr}, {nullptr, nullptr, nullptr}};
+  int small_count[2][3] = {{0, 0, 0}, {0, 0, 0}};
   std::vector<ClassRun> runs[3];   // rounds 0, 1 and the closing sweeps
   int32_t* edge_len = nullptr;
   int32_t* pairs = nullptr;
@@ -391,6 +427,13 @@ int device_plan(int d, const bbp_opts* o, DevPlan** out) {
     SweepDesc*& dst = (c < 2) ? dp->round[c] : dp->bethe;
     HIP_TRY(hipMalloc(&dst, sizeof(SweepDesc) * std::max<size_t>(1, v.size())));
     if (!v.empty()) HIP_TRY(hipMemcpy(dst, v.data(), sizeof(SweepDesc) * v.size(), hipMemcpyHostToDevice));
+    if (p.kr > 2 || p.kc > 2 || v.empty()) continue;
+    for (int k = 0; k < 2; ++k) {
+      const std::vector<bbp::SmallSweep> w = small_list(v, k == 1);
+      HIP_TRY(hipMalloc(&dp->small[k][c], sizeof(bbp::SmallSweep) * w.size()));
+      HIP_TRY(hipMemcpy(dp->small[k][c], w.data(), sizeof(bbp::SmallSweep) * w.size(), hipMemcpyHostToDevice));
+      dp->small_count[k][c] = (int)w.size();
+    }
   }
   std::vector<int32_t> el(p.edge_len.begin(), p.edge_len.end());
   if (el.empty()) el.push_back(0);
@@ -569,7 +612,10 @@ struct Mark {
 
 // How the sweeps of a decode are launched: per class and round (sweep_kernel.hip and the others), all classes of a
 // round at once, or everything of a job in one workgroup (fused_sweep.hip). Results do not depend on it.
-enum class Route { classes, rounds, loop };
+enum class Route { classes, rounds, loop, small };
+
+// Blocks of at most 2x2 in FP32 (small_sweep.hip and small_loop.hip).
+bool small_blocks(const bbp_opts* o) { return o->block_rows <= 2 && o->block_cols <= 2 && o->precision == 0; }
 
 // The route with the smallest estimated time. The estimates (microseconds for a decode of up to 20 iterations, whose
 // number scales all three) are straight lines through decodes timed at d = 3 .. 25, blocks 3 .. 6, 1 to 400 syndromes:
@@ -586,7 +632,14 @@ enum class Route { classes, rounds, loop };
 // syndrome: 634 / 235 / 76 us (classes / rounds / loop); d = 17, 6 x 6, BF16: 1647 / 502 / 1325 for 1 syndrome,
 // 1750 / 972 / 1350 for 16, 2163 / 2310 / 1505 for 64, 2738 / 3986 / 2942 for 128.
 Route choose_route(const std::vector<GroupRun>& gr, const bbp_opts* opts) {
-  if (opts->block_rows <= 2 && opts->block_cols <= 2 && opts->precision == 0) return Route::classes;   // small_sweep.hip
+  if (small_blocks(opts)) {
+    // a workgroup per job wherever its messages fit the LDS (d <= 32 for 2x2 blocks, d <= 21 for single tensors): faster
+    // than a launch per class and round at every size tried (2x2 blocks, d = 5, 1 syndrome: 4452 -> 141 us; d = 17, 16:
+    // 7376 -> 361, 2048: 32.9 -> 4.0 ms; d = 9, 4096: 17.4 -> 3.2 ms; single tensors, d = 17, 1024: 52.0 -> 6.3 ms)
+    for (const GroupRun& g : gr)
+      if (g.in.batch > 0 && bbp::small_loop_lds(g.dp->plan.M) > bbp::SMALL_LOOP_LDS_MAX) return Route::classes;
+    return Route::small;
+  }
   static const double round_start[7] = {0, 0, 0, 280.0, 300.0, 330.0, 420.0};
   static const double round_slope[7] = {0, 0, 0, 0.027, 0.031, 0.040, 0.125};
   static const double loop_slope[7] = {0, 0, 0, 6.4, 8.1, 12.0, 23.0};
@@ -730,7 +783,7 @@ int enqueue(std::vector<GroupRun>& gr, const bbp_opts* opts, const Tune& tn, hip
       sa.bf16 = opts->precision == 1 ? 1 : 0;
       sa.eta = (float)opts->damping;
       sa.gate = opts->gate;
-      sa.small = (opts->block_rows <= 2 && opts->block_cols <= 2 && opts->precision == 0) ? 1 : 0;
+      sa.small = small_blocks(opts) ? 1 : 0;
       int64_t items = 0;
       for (int k = 0; k < sa.ngroups; ++k) {
         const GroupRun& g = gr[members[k].first];
@@ -770,7 +823,7 @@ int enqueue(std::vector<GroupRun>& gr, const bbp_opts* opts, const Tune& tn, hip
   // small decodes: the fused kernels, one launch per set of groups with the same block sizes
   const Route route = marks ? Route::classes : choose_route(gr, opts);
   std::map<int, std::vector<int>> sets;
-  if (route != Route::classes)
+  if (route == Route::rounds || route == Route::loop)
     for (int g = 0; g < ng; ++g)
       if (gr[g].in.batch > 0) sets[fused_shape(gr[g].dp->plan)].push_back(g);
   auto fused = [&](int list) -> int {
@@ -811,7 +864,63 @@ int enqueue(std::vector<GroupRun>& gr, const bbp_opts* opts, const Tune& tn, hip
     return BBP_OK;
   };
   if (route == Route::loop && (rc = fused(0))) return rc;
-  for (int it = 0; it < opts->max_iter && route != Route::loop; ++it) {
+  if (route == Route::small) {
+    bbp::SmallArgs sa;
+    std::memset(&sa, 0, sizeof(sa));
+    sa.max_iter = opts->max_iter;
+    sa.fixed = opts->fixed_iters;
+    sa.delta0 = opts->delta0;
+    sa.s.eta = (float)opts->damping;
+    sa.s.gate = opts->gate;
+    size_t lds = 0;
+    int most = 1;
+    // A wavefront with several kinds takes them one after the other, and the round waits for it; lists with a kind per
+    // wavefront leave lanes empty. The latter are faster until the chip is full (d = 9, 2x2, 64 syndromes: 176 us against
+    // 266; 256: 375 against 363; 1024: 1221 against 989) and where at most about half the lanes stay empty (d = 17,
+    // 1.8 entries a block, 2048 syndromes: 3.97 ms against 4.07; d = 13, 3.1 entries, 1024: 1.95 against 1.68).
+    int64_t jobs = 0, dense = 0, padded = 0;
+    for (const GroupRun& g : gr) {
+      jobs += g.jobs;
+      for (int c = 0; c < 2; ++c) {
+        dense += g.jobs * g.dp->small_count[0][c];
+        padded += g.jobs * g.dp->small_count[1][c];
+      }
+    }
+    const int apart = jobs <= 512 || 5 * padded <= 11 * dense ? 1 : 0;
+    for (const GroupRun& g : gr) {
+      if (g.in.batch == 0) continue;
+      bbp::SweepGroup& G = sa.s.g[sa.s.ngroups];
+      fill(G, g, sa.s.items);
+      bbp::SmallGroup& F = sa.f[sa.s.ngroups++];
+      const bbp::Plan& p = g.dp->plan;
+      for (int c = 0; c < 3; ++c) {
+        F.sweeps[c] = g.dp->small[apart][c];
+        F.count[c] = g.dp->small_count[apart][c];
+        if (c < 2) most = std::max(most, F.count[c]);
+      }
+      F.iters = g.iters;
+      F.delta = g.delta;
+      lds = std::max(lds, bbp::small_loop_lds(p.M));
+      sa.s.items += g.jobs;
+    }
+    // wavefronts of a workgroup: enough for 16 on a CU with the workgroups that its LDS holds and the jobs supply, up
+    // to twice that, the number that leaves the fewest lanes idle in the last pass over a round's blocks
+    const int64_t held = std::max<int64_t>(1, std::min<int64_t>((int64_t)(bbp::SMALL_LOOP_LDS_MAX / std::max<size_t>(lds, 1)),
+                                                                (sa.s.items + 255) / 256));
+    const int all = std::min(16, (most + 63) / 64), least = std::min<int>(all, (int)((16 + held - 1) / held));
+    int waves = least;
+    double best = 0.0;
+    for (int w = least; w <= std::min(all, 2 * least); ++w) {
+      const double used = (double)most / (double)((most + 64 * w - 1) / (64 * w) * 64 * w);
+      if (used > best + 1e-9) {
+        best = used;
+        waves = w;
+      }
+    }
+    HIP_TRY(bbp::launch_small_loop(st, sa, 64 * waves, lds));
+  }
+  const bool whole = route == Route::loop || route == Route::small;   // the closing sweeps are done
+  for (int it = 0; it < opts->max_iter && !whole; ++it) {
     for (int c = 0; c < 2; ++c)
       if ((rc = route == Route::rounds ? fused(c) : round(c, it))) return rc;
     for (auto& g : gr) {
@@ -823,7 +932,7 @@ int enqueue(std::vector<GroupRun>& gr, const bbp_opts* opts, const Tune& tn, hip
       if ((rc = end_mark(st))) return rc;
     }
   }
-  if (route != Route::loop && (rc = route == Route::rounds ? fused(2) : round(2, opts->max_iter))) return rc;
+  if (!whole && (rc = route == Route::rounds ? fused(2) : round(2, opts->max_iter))) return rc;
   for (auto& g : gr) {
     if (g.in.batch == 0) continue;
     const bbp::Plan& P = g.dp->plan;

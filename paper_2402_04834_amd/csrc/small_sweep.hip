@@ -1,7 +1,8 @@
 // small_sweep.hip -- block updates for blocks of at most 2x2 tensors (block size 1 is plain BP between single
 // tensors, the paper's naive limit of blockBP): one lane per (job, sweep) instead of one wavefront, since a
 // sweep of such a block has at most four crossing configurations and a wavefront would leave 60 of its 64
-// lanes idle.
+// lanes idle. Serves plans whose messages exceed a workgroup's LDS, and decodes timed class by class; the others run in
+// small_loop.hip.
 //
 // A lane contracts its block directly. Every bond joins a qubit and a check and carries the check's
 // variable (checks are COPY tensors), so the block's variables are its own checks and the outside checks

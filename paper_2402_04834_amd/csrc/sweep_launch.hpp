@@ -74,6 +74,32 @@ struct SweepArgs {
   int64_t item_base;         // first item of the current chunk
 };
 
+// A block update (or closing sum) of small_loop.hip.
+struct alignas(16) SmallSweep {
+  int16_t r0, c0;   // first site
+  int32_t kind;     // (rows == 2, columns == 2, first site a qubit, receiver side): bits 4, 3, 2, 1-0
+  int32_t m[4];     // messages entering from E, W, S, N, -1 where there is none
+  int32_t out;      // outgoing message (closing: the block)
+  int32_t pad;
+};
+static_assert(sizeof(SmallSweep) == 32, "SmallSweep layout");
+struct SmallGroup {
+  const SmallSweep* sweeps[3];   // the two colour rounds and the closing sums
+  int32_t count[3];
+  int32_t* iters;                // [job] results
+  double* delta;
+};
+struct SmallArgs {
+  SweepArgs s;                   // group state; items = jobs, one workgroup each
+  SmallGroup f[MAX_GROUPS];
+  int32_t max_iter, fixed;
+  double delta0;
+};
+// LDS of a job's messages and distance terms; the most that a workgroup may have
+constexpr size_t small_loop_lds(int M) { return (size_t)M * 24; }
+constexpr size_t SMALL_LOOP_LDS_MAX = 160 * 1024 - 256;
+hipError_t launch_small_loop(hipStream_t st, const SmallArgs& a, int threads, size_t lds);
+
 // Sweep classes of the truncating kernel (any length; sweeps with SweepDesc::trunc set): TRUNC_CLASS, and
 // TRUNC_CLASS | 1 for the narrow form (trunc_shape.hpp).
 constexpr int TRUNC_CLASS = 1 << 12;

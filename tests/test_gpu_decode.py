@@ -456,3 +456,34 @@ def test_fused_routes_mixed_groups_and_graph(dev, ds, b):
                 assert torch.equal(eager[g][key].view(torch.uint8), r), (g, key)
                 outs[g][key].zero_()
         torch.cuda.synchronize()
+
+
+# blocks of at most 2x2 in FP32 run a whole job per workgroup wherever its messages fit the LDS
+@pytest.mark.parametrize("d,rows,cols,b,extra", [
+    (2, 1, 1, 1, {}), (2, 2, 2, 3, {}), (3, 2, 2, 1, {}), (4, 1, 2, 5, {}), (5, 2, 1, 2, {}),   # every shape and parity
+    (9, 2, 2, 70, {}), (7, 1, 1, 300, {}), (17, 2, 2, 4, {}),
+    (32, 2, 2, 1, {"max_iter": 3}), (21, 1, 1, 1, {"max_iter": 2}), (22, 1, 1, 1, {"max_iter": 2}),   # LDS: 95 KB, 157 KB, too much
+    (5, 2, 2, 9, {"fixed_iters": 1, "max_iter": 1}), (6, 1, 1, 3, {"fixed_iters": 1, "max_iter": 4}),
+    (9, 2, 2, 3, {"gate": 1e-4}), (8, 1, 1, 2, {"gate": 1e-3, "damping": 0.0}),
+])
+def test_small_block_loop_equals_class_launches(dev, d, rows, cols, b, extra):
+    """Every output, for one rate, rates per syndrome with given start messages, and biased noise, alone and together,
+    equals the class launches' bitwise."""
+    import torch
+    import paper_2402_04834_amd as bbp
+    _, syn = workload.make_batch(d, 0.12, b, workload="test", p_index=990 + 10 * d + rows)
+    s = torch.from_numpy(syn).to(dev)
+    ps = torch.linspace(0.06, 0.16, b, dtype=torch.float64, device=dev)
+    opts = bbp.default_opts(block=rows, chi=4, precision=0, **extra)
+    opts.block_cols = cols
+    info = bbp.plan_query(d, opts)
+    init = torch.rand((b, 4, max(info.num_messages, 1), 64), generator=torch.Generator().manual_seed(d * 31 + rows)).to(dev) + 0.1
+    biased = (d, (0.85, 0.02, 0.1, 0.03), s)
+    _say(f"[small blocks] d={d} {rows}x{cols} batch {b} {extra}")
+    for groups in ([(d, 0.1, s)], [(d, ps, s, 0, init)], [biased], [(d, 0.1, s), biased, (3, 0.1, s[:1, :12].contiguous())]):
+        loop, _, _ = bbp.decode_groups(groups, opts, messages=True)
+        classes, _, _ = bbp.decode_groups(groups, opts, messages=True, timing=True)
+        for g in range(len(groups)):
+            for key in ("loglik", "delta", "iters", "coset", "correction", "messages"):
+                x, y = loop[g][key], classes[g][key]
+                assert torch.equal(x.contiguous().view(torch.uint8), y.contiguous().view(torch.uint8)), (g, key)
