@@ -761,24 +761,33 @@ __global__ __launch_bounds__(128 * WM) __attribute__((amdgpu_waves_per_eu(3))) v
 // workgroup, so that every weight stage and halo row loaded serves twice the outputs of a 128-row tile (the
 // composed layer 8.8 % faster, the first layer 7 %, the second unchanged: its 256 registers then spill a few).
 // Needs 2 L + 2 <= HALO_ROWS - HALO_MT (L <= 49, d <= 25); larger grids take the gather kernel.
+// LIST > 0: only the n sites of every job's grid listed in `sites` are computed (bits 0-11 the site, 12-15 the
+// directions whose projections of it some message reads); the tile's rows are then MT consecutive entries, whose sites
+// span at most LIST - 2 L - 2 rows of the input, staged in one buffer of LIST halo rows (two would leave one workgroup
+// per CU). With 6 x 6 blocks a message's legs touch half of
+// the sites: the forward takes 1374 us instead of 1610 (d = 21, 512 syndromes), 1301 instead of 1485 (d = 17, 700).
 constexpr int HALO_MT = 256, HALO_ROWS = HALO_MT + 100;   // rows per tile, halo rows
+constexpr int LIST_ROWS = 768;                            // halo rows of the listed form
 
-template <int CIN, int NT, int RELU, bool OUT_BF, int PN>
+template <int CIN, int NT, int RELU, bool OUT_BF, int PN, int LIST = 0>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void conv_halo_bf16(int L, int64_t rows, const unsigned short* __restrict__ X,
                                                        const unsigned short* __restrict__ Wt,
-                                                       const float* __restrict__ bias, void* __restrict__ Y) {
+                                                       const float* __restrict__ bias, void* __restrict__ Y,
+                                                       const uint16_t* __restrict__ sites, int n, int64_t listed) {
   constexpr int KS = CONV_KS, KP = kpad(CIN);                // k per step, weight row
   constexpr int CH = CIN < KS ? CIN : KS, NC = CIN / CH;     // channels per chunk, chunks
   constexpr int NS = CIN < KS ? KP / KS : 9 * NC;            // steps
   constexpr int RE = CH + 8, RP = CH / 8;                    // elements and 16-byte pieces per halo row
   constexpr int TH = 256, MT = HALO_MT, MI = MT / 64, NJ = NT / 16;   // 16-row and 16-channel blocks per wave
   constexpr int UB = (NT * 4 + TH - 1) / TH;                 // 16-byte weight chunks per thread and step
-  constexpr int UH = (HALO_ROWS * RP + TH - 1) / TH;         // 16-byte halo pieces per thread and chunk
-  constexpr int NH = NC > 1 ? 2 : 1, HALO = HALO_ROWS * RE;  // halo buffers, elements of one
+  constexpr int HR = LIST > 0 ? LIST : HALO_ROWS;            // halo rows
+  constexpr int UH = (HR * RP + TH - 1) / TH;         // 16-byte halo pieces per thread and chunk
+  constexpr int NH = NC > 1 && LIST == 0 ? 2 : 1, HALO = HR * RE;  // halo buffers, elements of one
   constexpr int BST = NT * KS;                               // elements of one weight stage
   constexpr int TILE = OUT_BF ? MT * (NT + 16) : 0;          // BF16 output tile (padded rows)
   constexpr int MAIN = NH * HALO + 2 * BST + 32;             // halo buffers, two weight stages, a zero row
   static_assert((CIN == 16 || CIN % 32 == 0) && NT % 16 == 0 && NT <= 128, "tile shape");
+  static_assert(LIST == 0 || (!OUT_BF && CIN >= KS), "listed form: FP32 outputs");
   __shared__ __align__(16) unsigned short lds[MAIN > TILE ? MAIN : TILE];
   unsigned short* const Bsm = lds + NH * HALO;
   unsigned short* const zrow = Bsm + 2 * BST;
@@ -792,9 +801,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void c
   const int fr = lane & 15, fc = lane >> 4;
   const unsigned xbytes = (unsigned)(rows * CIN * 2);   // the host keeps this + 512 below 2^32
   const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc((void*)X, (short)0, (int)xbytes, 0x00020000);
-  const int hr = MT + 2 * L + 2;                         // halo rows in use
   // (rows < 2^31: 32-bit row arithmetic)
-  const int g0 = (int)m0 - L - 1;                        // input row of halo row 0
+  const int LL = L * L;
+  // first and last input row of the tile. Listed form: entry m0 + r is entry rem0 + r of job job0 on, past the job's n
+  // entries of the next one
+  const int job0 = LIST > 0 ? (int)((unsigned)m0 / (unsigned)n) : 0;
+  const int rem0 = LIST > 0 ? (int)m0 - job0 * n : (int)((unsigned)m0 % (unsigned)LL);
+  int first = (int)m0, last = (int)m0 + MT - 1;
+  if constexpr (LIST > 0) {
+    const int end = (int)(m0 + MT < listed ? m0 + MT : listed) - 1, jl = (int)((unsigned)end / (unsigned)n);
+    first = job0 * LL + (sites[rem0] & 4095);
+    last = jl * LL + (sites[end - jl * n] & 4095);
+  }
+  const int hr = last - first + 1 + 2 * L + 2;           // halo rows in use
+  const int g0 = first - L - 1;                          // input row of halo row 0
   // halo pieces of this thread: row h = p / RP, 16-byte group p % RP; byte offset of channel 0 of the group
   // (chunk c adds 2 CH c), xbytes for rows outside the input or the halo
   unsigned hoff[UH];
@@ -808,9 +828,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void c
   // bit 4 always set: the padding tap reads the zero row for every row). The row's place in its job's grid
   // comes from the tile's (uniform) and small quotients by L^2 and by L per lane: x < L^2 + MT, so the FP32
   // quotient is off by at most one, which the remainder tests correct.
-  const int LL = L * L;
-  const int rem0 = (int)((unsigned)m0 % (unsigned)LL);
-  const float rl = 1.0f / (float)L, rll = 1.0f / (float)LL;
+  const float rl = 1.0f / (float)L, rll = 1.0f / (float)(LIST > 0 ? n : LL);
   auto quot = [](const int x, const int n, const float rn, int& rem) {
     int q = (int)((float)x * rn);
     rem = x - q * n;
@@ -823,14 +841,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void c
     }
     return q;
   };
-  int abase[MI];
-  unsigned edge[MI];
+  int abase[MI], orow[MI];   // (orow: the output row of this lane's row, listed form)
+  unsigned edge[MI], dirs[MI];
 #pragma unroll
   for (int i = 0; i < MI; ++i) {
-    const int r = wm + 16 * i + fr;
-    abase[i] = (r + L + 1) * RE + 8 * (CIN < KS ? (fc & 1) : fc);
+    int r = wm + 16 * i + fr;
     int site, col;
-    quot(rem0 + r, LL, rll, site);
+    orow[i] = 0;
+    dirs[i] = 0;
+    if constexpr (LIST > 0) {
+      int k;
+      const int job = job0 + quot(min(rem0 + r, (int)(listed - 1) - job0 * n), n, rll, k);   // (past the list: its last)
+      const unsigned v = sites[k];
+      site = (int)(v & 4095u);
+      orow[i] = job * LL + site;
+      dirs[i] = m0 + r < listed ? v >> 12 : 0u;
+      r = orow[i] - first;
+    } else {
+      quot(rem0 + r, LL, rll, site);
+    }
+    abase[i] = (r + L + 1) * RE + 8 * (CIN < KS ? (fc & 1) : fc);
     const int gr = quot(site, L, rl, col);
     edge[i] = 16u | (gr == 0 ? 1u : 0u) | (gr == L - 1 ? 2u : 0u) | (col == 0 ? 4u : 0u) | (col == L - 1 ? 8u : 0u);
   }
@@ -843,7 +873,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void c
 #pragma unroll
     for (int u = 0; u < UH; ++u) {
       const int p = tid + TH * u, h = p / RP;
-      if ((UH * TH <= HALO_ROWS * RP) || h < HALO_ROWS) *(u32x4*)&lds[buf * HALO + h * RE + 8 * (p % RP)] = rh[u];
+      if ((UH * TH <= HR * RP) || h < HR) *(u32x4*)&lds[buf * HALO + h * RE + 8 * (p % RP)] = rh[u];
     }
   };
   auto loadB = [&](const int s, u32x4 (&rb)[UB]) {
@@ -886,8 +916,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void c
   auto step = [&](const int s, u32x4 (&rb_next)[UB], const u32x4 (&rb_due)[UB]) {
     const int c = CIN < KS ? 0 : s / 9, t = CIN < KS ? 2 * s : s % 9;
     if (s + 2 < NS) loadB(s + 2, rb_next);
-    if (t == 0 && c + 1 < NC) loadH(c + 1, rh);
-    const unsigned short* Hs = lds + (c & 1) * HALO;
+    if (t == (NH > 1 ? 0 : 3) && c + 1 < NC) loadH(c + 1, rh);
+    const unsigned short* Hs = lds + (NH > 1 ? (c & 1) : 0) * HALO;
     // the fragment addresses are formed anew each step: kept from the step two chunks back (same buffer, same
     // tap) they would hold 72 registers for the whole kernel
 #pragma unroll
@@ -909,9 +939,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void c
     for (int i = 0; i < MI; ++i)
 #pragma unroll
       for (int j = 0; j < NJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j], a[i], acc[i][j], 0, 0, 0);
-    if (t == 2 && c + 1 < NC) storeH((c + 1) & 1, rh);
+    if (NH > 1 && t == 2 && c + 1 < NC) storeH((c + 1) & 1, rh);
     if (s + 1 < NS) storeB((s + 1) & 1, rb_due);
     __syncthreads();
+    if (NH == 1 && CIN >= KS && t == 8 && c + 1 < NC) {   // every wave has read the chunk
+      storeH(0, rh);
+      __syncthreads();
+    }
   };
 #pragma unroll
   for (int s = 0; s < NS; s += 2) {
@@ -966,7 +1000,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void c
       const int dir = ch / PD, cd = ch - dir * PD;
 #pragma unroll
       for (int i = 0; i < MI; ++i) {
-        const int64_t row = m0 + wm + 16 * i + fr;
+        const int64_t row = LIST > 0 ? (int64_t)orow[i] : m0 + wm + 16 * i + fr;
         float4 v{acc[i][j][0] + b0, acc[i][j][1] + b1, acc[i][j][2] + b2, acc[i][j][3] + b3};
         if (RELU) {
           v.x = fmaxf(v.x, 0.0f);
@@ -975,7 +1009,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void c
           v.w = fmaxf(v.w, 0.0f);
         }
         float* dst = PN > 0 ? (float*)Y + (dir * rows + row) * PN + cd : (float*)Y + row * NT + ch;
-        if (full || row < rows) *(float4*)dst = v;
+        if (LIST > 0 ? (dirs[i] >> dir & 1u) != 0 : full || row < rows) *(float4*)dst = v;
       }
     }
   }
@@ -1318,9 +1352,16 @@ __global__ void fallback_scatter_kernel(const int64_t* __restrict__ list, int64_
 // ------------------------------------------------------------------------------------------ host side
 unsigned grid1(int64_t n) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, 65536)); }
 
+// the haloed-tile kernel serves grids whose halo fits its LDS rows
+bool halo_fits(int L) { return HALO_MT + 2 * L + 2 <= HALO_ROWS; }
+
 struct Legs {
   int32_t* dev = nullptr;
   int M = 0;
+  // the sites whose projections some message reads, ascending, with the directions it reads them of (bits 12-15), for
+  // the listed form of the composed layer; 0 where that form does not serve the plan
+  uint16_t* sites = nullptr;
+  int used = 0;
 };
 std::mutex l_mu;
 std::map<std::tuple<int, int, int, int, int>, Legs> l_cache;
@@ -1362,6 +1403,24 @@ int legs_for(int d, const bbp_opts* o, Legs* out) {
   }
   Legs lg;
   lg.M = P.M;
+  std::vector<uint16_t> need((size_t)L * L, 0), sites;
+  for (int e = 0; e < P.M; ++e)
+    for (int i = 0; i < 2 * MAXK; ++i) {
+      const int32_t site = t[(size_t)e * 14 + 2 + i];
+      if (site >= 0) need[site] |= (uint16_t)(1 << t[(size_t)e * 14 + 1]);
+    }
+  for (int i = 0; i < L * L; ++i)
+    if (need[i]) sites.push_back((uint16_t)(i | need[i] << 12));
+  const int n = (int)sites.size();
+  // input rows that a tile's consecutive entries span, from every entry
+  int64_t span = 0;
+  auto at = [&](int k) { return (int64_t)(k / n) * L * L + (sites[k % n] & 4095); };
+  for (int k = 0; k < n; ++k) span = std::max(span, at(k + HALO_MT - 1) - at(k) + 1);
+  if (n > 0 && 10 * n <= 9 * L * L && halo_fits(L) && span + 2 * L + 2 <= LIST_ROWS) {
+    lg.used = n;
+    W_TRY(hipMalloc(&lg.sites, sites.size() * sizeof(uint16_t)));
+    W_TRY(hipMemcpy(lg.sites, sites.data(), sites.size() * sizeof(uint16_t), hipMemcpyHostToDevice));
+  }
   W_TRY(hipMalloc(&lg.dev, t.size() * sizeof(int32_t)));
   W_TRY(hipMemcpy(lg.dev, t.data(), t.size() * sizeof(int32_t), hipMemcpyHostToDevice));
   l_cache[key] = lg;
@@ -1453,15 +1512,12 @@ struct Args {
   hipStream_t st;
 };
 
-// forward trunk of `jobs` coset jobs starting at syndrome syn / noise rates pdev: features F [rows][C3]
-// the haloed-tile kernel serves grids whose halo fits its LDS rows
-bool halo_fits(int L) { return HALO_MT + 2 * L + 2 <= HALO_ROWS; }
 
 // PN > 0 (the composed last layer): with the haloed-tile kernel the projections are stored direction-major,
 // [4][rows][PN]; the gather kernel of larger grids stores them [rows][NT]
 template <int CIN, int NT, int WM, int RELU, bool OUT_BF, int PN = 0>
 int conv_bf16(int L, int64_t rows, const unsigned short* X, const unsigned short* Wt, const float* bias, void* Y,
-              hipStream_t st) {
+              hipStream_t st, const uint16_t* sites = nullptr, int n = 0) {
   // the kernel addresses the activations through one buffer descriptor with 32-bit byte offsets, the
   // out-of-grid sentinel (the buffer's size) plus a channel offset included
   if (rows * CIN > (int64_t)INT32_MAX - 512) return wfail(BBP_EINVAL, "too many sites for one BF16 convolution");
@@ -1470,8 +1526,19 @@ int conv_bf16(int L, int64_t rows, const unsigned short* X, const unsigned short
       // the haloed-tile kernel computes only the 4 PN projection channels of the composed layer (the weight
       // rows beyond them are the padding of the gather kernel's tile)
       constexpr int NTH = PN > 0 ? 4 * PN : NT;
+      if constexpr (PN > 0) {
+        // (while every tile of the plain form runs at once, two per CU, only a tile's own time counts, and a listed
+        // tile's is longer: d = 13, 1 syndrome, 71.9 us the plain forward, 74.5 the listed)
+        if (n > 0 && rows > 512 * HALO_MT) {
+          const int64_t listed = rows / ((int64_t)L * L) * n;
+          conv_halo_bf16<CIN, NTH, RELU, OUT_BF, PN, LIST_ROWS><<<dim3((unsigned)((listed + HALO_MT - 1) / HALO_MT)), dim3(256), 0, st>>>(
+              L, rows, X, Wt, bias, Y, sites, n, listed);
+          W_TRY(hipGetLastError());
+          return BBP_OK;
+        }
+      }
       conv_halo_bf16<CIN, NTH, RELU, OUT_BF, PN><<<dim3((unsigned)((rows + HALO_MT - 1) / HALO_MT)), dim3(256), 0, st>>>(
-          L, rows, X, Wt, bias, Y);
+          L, rows, X, Wt, bias, Y, nullptr, 0, 0);
       W_TRY(hipGetLastError());
       return BBP_OK;
     }
@@ -1496,7 +1563,7 @@ int weights_bf16(const float* prm, const WLayout& w, char* ws, hipStream_t st) {
 // forward trunk in BF16 storage with FP32 accumulation: input channels, A1 and A2 in BF16; the last layer
 // composed with the head gives the projections [rows][PROJ_CH] in FP32 (in the features' slot)
 int trunk_bf16(int d, const uint8_t* syn, const double* pdev, double p, int64_t jobs, char* ws, const WLayout& w,
-               const float* prm, hipStream_t st) {
+               const float* prm, const Legs& lg, hipStream_t st) {
   const int L = 2 * d - 1;
   const int64_t rows = jobs * L * L;
   unsigned short *X0 = (unsigned short*)(ws + w.X0), *A1 = (unsigned short*)(ws + w.A1),
@@ -1508,7 +1575,7 @@ int trunk_bf16(int d, const uint8_t* syn, const double* pdev, double p, int64_t 
   if ((rc = conv_bf16<CS0, C1, CONV_WM, 1, true>(L, rows, X0, Wb, prm + OFF.b1, A1, st))) return rc;
   if ((rc = conv_bf16<C1, C2, CONV_WM, 1, true>(L, rows, A1, Wb + WB1, prm + OFF.b2, A2, st))) return rc;
   if ((rc = conv_bf16<C2, PROJ_CH, CONV_WM, 0, false, NPROJ>(L, rows, A2, Wb + WB1 + WB2,
-                                                              (const float*)(Wb + WB_TOTAL), F, st)))
+                                                              (const float*)(Wb + WB_TOTAL), F, st, lg.sites, lg.used)))
     return rc;
   return BBP_OK;
 }
@@ -1580,7 +1647,7 @@ int bbp_warm_predict(int32_t d, double p, const double* p_dev, const uint8_t* sy
     const int64_t nb = std::min(chunk, batch - b0), jobs = 4 * nb;
     const uint8_t* sb = syndromes_dev + b0 * m;
     const double* pb = p_dev ? p_dev + b0 : nullptr;
-    rc = (precision == 1) ? trunk_bf16(d, sb, pb, p, jobs, (char*)workspace, w, params_dev, a.st)
+    rc = (precision == 1) ? trunk_bf16(d, sb, pb, p, jobs, (char*)workspace, w, params_dev, lg, a.st)
                           : trunk(d, sb, pb, p, jobs, params_dev, (char*)workspace, w, a.st);
     if (rc) return rc;
     if (lg.M > 0) {

@@ -414,3 +414,23 @@ def test_loss_gradient_tile_edges(dev, d, k, b):
     for n in rp:
         err = np.abs(gp[n] - rp[n]).max()
         assert err <= 2e-4 * np.abs(rp[n]).max(), (n, err)
+
+
+@pytest.mark.parametrize("d,k,b", [(5, 3, 410), (9, 6, 120), (13, 4, 55), (17, 5, 31), (21, 6, 20), (25, 6, 14)])
+def test_bf16_forward_at_listed_sites_equals_plain(dev, d, k, b):
+    """A batch large enough for the composed layer to run at the sites the messages read equals its syndromes in
+    batches that run it everywhere, bitwise: sites a fraction of the grid apart, tiles that end inside a grid, one
+    that spans several (a site's sums do not depend on the tile)."""
+    import torch
+    import paper_2402_04834_amd as bbp
+    from paper_2402_04834_amd import warm
+    opts = bbp.default_opts(block=k, chi=32)
+    prm = torch.from_numpy(warm.init_params(3)).to(dev)
+    _, syn = workload.make_batch(d, 0.1, b, workload="test", p_index=700 + d)
+    s = torch.from_numpy(syn).to(dev)
+    _say(f"[warm listed] d={d} k={k} batch {b}")
+    whole = warm.predict(d, 0.1, s, opts, prm)
+    n = 131072 // (4 * (2 * d - 1) ** 2)
+    assert b > n
+    parts = torch.cat([warm.predict(d, 0.1, s[i:i + n].contiguous(), opts, prm) for i in range(0, b, n)])
+    assert torch.equal(whole.view(torch.int32), parts.view(torch.int32))
