@@ -45,23 +45,23 @@ def traffic(kernel, path=TRAFFIC):
 
 
 TRAFFIC_SOURCES = ["paper_2402_04834_amd/csrc/geom.hpp", "paper_2402_04834_amd/csrc/sweep_launch.hpp",
-                   "paper_2402_04834_amd/csrc/wave_sweep.hpp", "paper_2402_04834_amd/csrc/sweep_kernel.hip"]
+                   "paper_2402_04834_amd/csrc/wave_sweep.hpp", "paper_2402_04834_amd/csrc/sweep_item.hpp",
+                   "paper_2402_04834_amd/csrc/sweep_kernel.hip"]
 BMPS_TRAFFIC_SOURCES = ["paper_2402_04834_amd/csrc/bmps_launch.hpp", "paper_2402_04834_amd/csrc/bmps.hip",
                         "paper_2402_04834_amd/csrc/wave_mps.hpp"]
 
 
 def _short_kernel_name(name):
-    """'void bbp::(anonymous namespace)::sweep_kernel<false, 6, true, true, false, true, false>(...)' ->
-    'sweep_kernel<6, true, true, false, true>' (FP32 depolarizing kernels; the first template argument true
-    gives 'sweep_kernel_bf16<...>', as _lib.sweep_kernel_name names them); 'bmps_kernel'; other kernels
+    """'void bbp::(anonymous namespace)::sweep_kernel<false, 6, 6, true, true, true, false>(...)' (precision, steps,
+    positions, top cap, bottom cap, first site a qubit, biased) -> 'sweep_kernel<6, true, true, false, true>' (FP32
+    depolarizing kernels; the first template argument true gives 'sweep_kernel_bf16<...>', as
+    _lib.sweep_kernel_name names them: one position across instead of their number); 'bmps_kernel'; other kernels
     keep their name."""
     import re
-    m = re.search(r"sweep_kernel<(true|false), (\d+(?:, (?:true|false)){4}), false>", name)
+    m = re.search(r"sweep_kernel<(true|false), (\d+), (\d+), (true|false), (true|false), (true|false), false>", name)
     if m:
-        return f"sweep_kernel{'_bf16' if m.group(1) == 'true' else ''}<{m.group(2)}>"
-    m = re.search(r"trunc_sweep_kernel<(true|false)>", name)
-    if m:
-        return f"trunc_sweep_kernel<{m.group(1)}>"
+        bf, kt, kp, top, bot, q00 = m.groups()
+        return f"sweep_kernel{'_bf16' if bf == 'true' else ''}<{kt}, {top}, {bot}, {'true' if kp == '1' else 'false'}, {q00}>"
     return "bmps_kernel" if re.search(r"bmps_kernel\b", name) and "decide" not in name else name
 
 
@@ -96,7 +96,8 @@ def write_traffic_summary(fetch_csv, write_csv, copy_mib=1024, target="sweep"):
     kernels = {}
     for k, (v, n) in fetch.items():
         short = _short_kernel_name(k)
-        if short.startswith(prefix) and k in write:
+        # (of the widths that share a name, the one that moves most)
+        if short.startswith(prefix) and k in write and v > kernels.get(short, dict(fetch_kib=-1.0))["fetch_kib"]:
             kernels[short] = dict(fetch_kib=v, write_kib=write[k][0], dispatches=n)
     out = dict(source_sha256=h.hexdigest(), sources=sources, fetch_scale=round(size_kib / cf, 4),
                write_scale=round(size_kib / cw, 4),

@@ -66,8 +66,10 @@ __device__ __forceinline__ void sweep_item(const SweepArgs& a, int mode, const S
     c.p00 = G.p00;
     c.pe = G.pe;
   }
-  c.biased = BIASED ? G.biased : 0;
-  for (int k = 0; k < 4; ++k) c.pib[k] = __float_as_int(G.pi[k]);
+  for (int k = 0; k < 4; ++k) {
+    c.pib[k] = BIASED ? __float_as_int(G.biased ? G.pi[k] : k == 0 ? c.p00 : c.pe) : 0;
+    if constexpr (BIASED && SUBS == 1) c.pib[k] = __builtin_amdgcn_readfirstlane(c.pib[k]);   // (one job: to the scalar unit)
+  }
   c.exp2 = 0;
 
   // labels

@@ -487,3 +487,28 @@ def test_small_block_loop_equals_class_launches(dev, d, rows, cols, b, extra):
             for key in ("loglik", "delta", "iters", "coset", "correction", "messages"):
                 x, y = loop[g][key], classes[g][key]
                 assert torch.equal(x.contiguous().view(torch.uint8), y.contiguous().view(torch.uint8)), (g, key)
+
+
+@pytest.mark.parametrize("k", [3, 4, 5, 6])
+def test_depolarizing_group_in_a_biased_launch(dev, k):
+    """A launch with a biased group takes every group's entries from its four probabilities. Depolarizing groups beside
+    one, with one rate and with rates per syndrome, packed and whole-wavefront widths, agree with their own launches:
+    the same products and sums but for the rounding order of the end sites, so each message within a few FP32 roundings
+    per iteration (1e-6) and ln Z within 2e-5 + 2e-7 |ln Z| as against the oracle."""
+    import torch
+    import paper_2402_04834_amd as bbp
+    d, b = 2 * k + 1, 5
+    _, syn = workload.make_batch(d, 0.1, b, workload="test", p_index=60 + k)
+    s = torch.from_numpy(syn).to(dev)
+    ps = torch.linspace(0.05, 0.15, b, dtype=torch.float64, device=dev)
+    opts = bbp.default_opts(block=k, chi=32, max_iter=3, fixed_iters=1)
+    groups = [(d, 0.1, s), (d, (0.85, 0.02, 0.1, 0.03), s), (d, ps, s)]
+    _say(f"[biased launch] d={d} k={k}")
+    mixed, _, _ = bbp.decode_groups(groups, opts, messages=True)
+    for g, one in zip((0, 2), (groups[0], groups[2])):
+        own, _, _ = bbp.decode_groups([one], opts, messages=True)
+        M = bbp.plan_query(d, opts).num_messages
+        x, y = (o["messages"][:, :, :M].cpu().numpy() for o in (mixed[g], own[0]))
+        np.testing.assert_allclose(x, y, rtol=0, atol=1e-6)
+        ll = own[0]["loglik"].cpu().numpy()
+        np.testing.assert_allclose(mixed[g]["loglik"].cpu().numpy(), ll, rtol=0, atol=2e-5 + 2e-7 * np.abs(ll).max())
