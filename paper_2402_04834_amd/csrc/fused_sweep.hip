@@ -40,7 +40,7 @@ __device__ __forceinline__ void shape_sweep(const SweepArgs& a, int mode, const 
                                             int64_t job, float* lds) {
   const bool active = ((int)__lane_id() >> sweep_lane_bits(KP)) == 0;   // one job: the first lanes
   auto run = [&](auto top, auto bot, auto q00) {
-    sweep_item<BF, KT, KP, decltype(top)::value, decltype(bot)::value, KP == 1, decltype(q00)::value, false>(
+    sweep_item<BF, KT, KP, decltype(top)::value, decltype(bot)::value, KP == 1, decltype(q00)::value, false, true>(
         a, mode, G, s, job, active, lds);
   };
   auto run2 = [&](auto top, auto bot) {

@@ -31,13 +31,17 @@ constexpr int sweep_lds_floats() { return LB == 6 ? 1 : (64 >> LB) * (2 * (1 << 
 // biased Pauli noise (otherwise the depolarizing entries are compiled in and the biased selection is removed).
 // KP: positions across, 0 where only s.kp tells. job: the lane's job (wave-uniform with LB = 6); active: it takes part
 // (inactive lanes follow along on a valid job and write nothing). mode as in sweep_kernel.hip.
-template <bool BF, int KT, int KP, bool TOP, bool BOT, bool SINGLE, bool Q00, bool BIASED>
+// FRESH: the call sits in a loop over sweeps of several shapes: what derives from the lane is formed anew for each (hoisted
+// out of the loop, the values of all shapes together spill).
+template <bool BF, int KT, int KP, bool TOP, bool BOT, bool SINGLE, bool Q00, bool BIASED, bool FRESH = false>
 __device__ __forceinline__ void sweep_item(const SweepArgs& a, int mode, const SweepGroup& G, const SweepDesc& s,
                                            int64_t job, bool active, float* lds) {
   using V = float;
   constexpr int LB = sweep_lane_bits(KP), LANES = 1 << LB, SUBS = 64 / LANES;
   using C = wave::Ctx<V, LB, KP, BIASED>;
-  const int lane = (int)__lane_id(), h = lane & (LANES - 1), sub = lane >> LB;
+  int lane = (int)__lane_id();
+  if constexpr (FRESH) asm volatile("" : "+v"(lane));
+  const int h = lane & (LANES - 1), sub = lane >> LB;
   if (mode == 0) {
     active = active && !(G.conv && G.conv[job]);
     if (a.gate > 0.0) {
