@@ -625,12 +625,13 @@ bool small_blocks(const bbp_opts* o) { return o->block_rows <= 2 && o->block_col
 //            the waves of one launch run different code, one job each, so they use the chip worse;
 //   loop     60 plus, for every 256 jobs (one workgroup per CU) of a set, a cost per sweep of a round: 16 wavefronts
 //            share them.
-// The slopes grow with the block width; plans with a remainder of one site at width 6 run twice as long in the fused
-// kernels (their one-position sweeps of six steps spill at 128 registers). For a graph, whose replays on several
-// streams overlap, only a third of the waiting counts (d = 7 and 13 mixed, 32 syndromes, three graphs in turn: 744 us
-// a decode by classes, 1297 by rounds, against 1870 and 1441 eager). Measured around the lines: d = 5, 3 x 3, 1
-// syndrome: 634 / 235 / 76 us (classes / rounds / loop); d = 17, 6 x 6, BF16: 1647 / 502 / 1325 for 1 syndrome,
-// 1750 / 972 / 1350 for 16, 2163 / 2310 / 1505 for 64, 2738 / 3986 / 2942 for 128.
+// The slopes grow with the block width; plans with a remainder of one site at width 6 run 1.7 (loop) to 2.6 times
+// (rounds) as long in the fused kernels: their one-position sweeps of six steps spill at 128 registers. For a graph,
+// whose replays on several streams overlap, only a third of the waiting counts (d = 7 and 13 mixed, 32 syndromes, three
+// graphs in turn, before the fused kernels' spills were reduced: 744 us a decode by classes, 1297 by rounds, against
+// 1870 and 1441 eager). Measured around the lines: d = 5, 3 x 3, 1 syndrome: 634 / 235 / 76 us (classes / rounds /
+// loop); d = 17, 6 x 6, BF16: 1666 / 539 / 1267 for 1 syndrome, 1779 / 743 / 1287 for 16, 2207 / 1500 / 1302 for 64,
+// 2509 / 1985 / 2491 for 100; d = 21, FP32, 40: 2724 / 1828 / 2521; d = 13 (a remainder of one), 64: 2097 / 2482 / 1764.
 Route choose_route(const std::vector<GroupRun>& gr, const bbp_opts* opts) {
   if (small_blocks(opts)) {
     // a workgroup per job wherever its messages fit the LDS (d <= 32 for 2x2 blocks, d <= 21 for single tensors): faster
@@ -640,9 +641,9 @@ Route choose_route(const std::vector<GroupRun>& gr, const bbp_opts* opts) {
       if (g.in.batch > 0 && bbp::small_loop_lds(g.dp->plan.M) > bbp::SMALL_LOOP_LDS_MAX) return Route::classes;
     return Route::small;
   }
-  static const double round_start[7] = {0, 0, 0, 280.0, 300.0, 330.0, 420.0};
-  static const double round_slope[7] = {0, 0, 0, 0.027, 0.031, 0.040, 0.125};
-  static const double loop_slope[7] = {0, 0, 0, 6.4, 8.1, 12.0, 23.0};
+  static const double round_start[7] = {0, 0, 0, 280.0, 300.0, 310.0, 520.0};
+  static const double round_slope[7] = {0, 0, 0, 0.027, 0.031, 0.040, 0.065};
+  static const double loop_slope[7] = {0, 0, 0, 6.4, 8.1, 10.0, 23.0};
   static const double class_slope[7] = {0, 0, 0, 0.004, 0.006, 0.013, 0.040};
   struct Set {
     double waves = 0, jobs = 0, sweeps = 0;
@@ -673,7 +674,7 @@ Route choose_route(const std::vector<GroupRun>& gr, const bbp_opts* opts) {
     const Set& s = kv.second;
     const double per = loop_slope[s.wide] * (s.odd ? 1.7 : 1.0) * s.sweeps;
     t_classes += class_slope[s.wide] * s.waves;
-    t_rounds += alone * round_start[s.wide] + round_slope[s.wide] * (s.odd ? 2.0 : 1.0) * s.waves;
+    t_rounds += alone * round_start[s.wide] + round_slope[s.wide] * (s.odd ? 2.6 : 1.0) * s.waves;
     t_loop += std::max(alone * (60.0 + per * std::ceil(s.jobs / 256.0)), per * s.jobs / 256.0);
   }
   if (t_loop <= t_rounds && t_loop <= t_classes) return Route::loop;
