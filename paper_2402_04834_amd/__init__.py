@@ -73,6 +73,19 @@ def _outputs(batch, n, dev):
     )
 
 
+def _contiguous(t, stream):
+    """t, or a contiguous copy of it for work on `stream` (None: the current one). The copy is made on that stream, after
+    what the current one holds, so that its memory is reused in the order of the stream that reads it: a copy made on
+    another stream could be read before it is written, and be another call's once this one has returned."""
+    import torch
+    if stream is None or t.is_contiguous():
+        return t.contiguous()
+    stream.wait_stream(torch.cuda.current_stream(t.device))
+    t.record_stream(stream)
+    with torch.cuda.stream(stream):
+        return t.contiguous()
+
+
 def decode_device(d: int, p: float, syndromes, opts: bbp_opts, *, workspace=None, messages: bool = False,
                   timing: bool = False, stream=None, out=None):
     """Decode a batch of syndromes held in a torch uint8 CUDA tensor [batch, m].
@@ -83,7 +96,7 @@ def decode_device(d: int, p: float, syndromes, opts: bbp_opts, *, workspace=None
     import torch
 
     assert syndromes.is_cuda and syndromes.dtype == torch.uint8 and syndromes.dim() == 2
-    syndromes = syndromes.contiguous()
+    syndromes = _contiguous(syndromes, stream)
     batch = syndromes.shape[0]
     dev = syndromes.device
     n = d * d + (d - 1) * (d - 1)
@@ -127,7 +140,7 @@ def decode_device_noalloc(d: int, p: float, syndromes, opts: bbp_opts, *, stream
     import torch
 
     assert syndromes.is_cuda and syndromes.dtype == torch.uint8 and syndromes.dim() == 2
-    syndromes = syndromes.contiguous()
+    syndromes = _contiguous(syndromes, stream)
     batch = syndromes.shape[0]
     dev = syndromes.device
     n = d * d + (d - 1) * (d - 1)
@@ -156,7 +169,7 @@ def bmps_decode(d: int, p, syndromes, chi: int = 16, *, workspace=None, correcti
     import torch
 
     assert syndromes.is_cuda and syndromes.dtype == torch.uint8 and syndromes.dim() == 2
-    syndromes = syndromes.contiguous()
+    syndromes = _contiguous(syndromes, stream)
     batch = syndromes.shape[0]
     dev = syndromes.device
     n = d * d + (d - 1) * (d - 1)
@@ -165,7 +178,11 @@ def bmps_decode(d: int, p, syndromes, chi: int = 16, *, workspace=None, correcti
         workspace = torch.empty(max(ws_bytes, 1), dtype=torch.uint8, device=dev)
     pval, p_ptr, noise, keep = 0.0, None, None, None
     if isinstance(p, torch.Tensor):
-        keep = p.to(device=dev, dtype=torch.float64).contiguous()
+        keep = p.to(device=dev, dtype=torch.float64)
+        if keep is not p and stream is not None:   # (made on the current stream)
+            stream.wait_stream(torch.cuda.current_stream(dev))
+            keep.record_stream(stream)
+        keep = _contiguous(keep, stream)
         p_ptr = keep.data_ptr()
     elif isinstance(p, (tuple, list)):
         noise = (C.c_double * 4)(*[float(v) for v in p])
@@ -209,7 +226,7 @@ def decode_groups(groups, opts: bbp_opts, *, workspace=None, timing: bool = Fals
         chi = grp[3] if len(grp) > 3 else 0
         init = grp[4] if len(grp) > 4 else None
         assert syn.is_cuda and syn.dtype == torch.uint8 and syn.dim() == 2
-        syn = syn.contiguous()
+        syn = _contiguous(syn, stream)
         keep.append(syn)
         dev = syn.device
         b = syn.shape[0]
@@ -219,7 +236,7 @@ def decode_groups(groups, opts: bbp_opts, *, workspace=None, timing: bool = Fals
             noise, p_val = tuple(float(v) for v in p), 0.0
         elif torch.is_tensor(p):
             assert p.is_cuda and p.dtype == torch.float64 and p.shape == (b,)
-            p = p.contiguous()
+            p = _contiguous(p, stream)
             keep.append(p)
             p_ptr, p_val = p.data_ptr(), 0.0
         o = outs_in[k] if outs_in is not None else _outputs(b, d * d + (d - 1) * (d - 1), dev)
@@ -227,7 +244,7 @@ def decode_groups(groups, opts: bbp_opts, *, workspace=None, timing: bool = Fals
         init_ptr = None
         if init is not None:
             assert init.is_cuda and init.dtype == torch.float32 and init.shape[0] == b and init.shape[1] == 4
-            init = init.contiguous()
+            init = _contiguous(init, stream)
             keep.append(init)
             init_ptr = init.data_ptr()
         msg_ptr = None
@@ -262,7 +279,7 @@ def autotune(d: int, p: float, syndromes, opts: bbp_opts, *, workspace=None, str
     """Time the launch variants of the block sweeps on this batch and keep the fastest for (d, opts)."""
     import torch
 
-    syndromes = syndromes.contiguous()
+    syndromes = _contiguous(syndromes, stream)
     ws_bytes = workspace_size(d, syndromes.shape[0], opts)
     if workspace is None or workspace.numel() < ws_bytes:
         workspace = torch.empty(max(ws_bytes, 1), dtype=torch.uint8, device=syndromes.device)

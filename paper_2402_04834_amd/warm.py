@@ -67,11 +67,12 @@ def _stream(stream, dev):
     return (stream if stream is not None else torch.cuda.current_stream(dev)).cuda_stream
 
 
-def _p_args(p, b):
+def _p_args(p, b, stream=None):
     import torch
+    from . import _contiguous
     if torch.is_tensor(p):
         assert p.is_cuda and p.dtype == torch.float64 and p.shape == (b,)
-        return 0.0, p.contiguous()
+        return 0.0, _contiguous(p, stream)
     return float(p), None
 
 
@@ -85,14 +86,15 @@ def predict(d: int, p, syndromes, opts: bbp_opts, params, *, precision: int = 1,
     """Start messages [batch, 4, M, 64] (float32, unit norm) for syndromes [batch, m] (uint8 CUDA).
     precision 1: BF16 weights and activations, FP32 accumulation (inference); 0: FP32 throughout."""
     import torch
-    syndromes = syndromes.contiguous()
+    from . import _contiguous
+    syndromes = _contiguous(syndromes, stream)
     b, dev = syndromes.shape[0], syndromes.device
     M = max(_plan_messages(d, opts), 1)
     out = torch.empty((b, 4, M, 64), dtype=torch.float32, device=dev)
     ws_bytes = workspace_size(d, b, opts, False)
     if workspace is None or workspace.numel() < ws_bytes:
         workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=dev)
-    pv, pt = _p_args(p, b)
+    pv, pt = _p_args(p, b, stream)
     _lib.check_warm(_lib.lib().bbp_warm_predict(
         d, pv, pt.data_ptr() if pt is not None else None, syndromes.data_ptr(), b, C.byref(opts),
         params.data_ptr(), precision, out.data_ptr(), workspace.data_ptr(), workspace.numel(), _stream(stream, dev)))
@@ -109,7 +111,8 @@ def loss_grad(d: int, p, syndromes, opts: bbp_opts, params, targets, use, *, wor
     KL(q || softmax(s)), q the target message normalised to sum 1 and s the network's scores (the loss of
     bbp_warm_loss_grad); targets [batch, 4, M, 64] float32, use [batch * 4] uint8 (CUDA tensors)."""
     import torch
-    syndromes = syndromes.contiguous()
+    from . import _contiguous
+    syndromes = _contiguous(syndromes, stream)
     b, dev = syndromes.shape[0], syndromes.device
     M = _plan_messages(d, opts)
     assert targets.shape == (b, 4, max(M, 1), 64) and targets.dtype == torch.float32
@@ -123,8 +126,8 @@ def loss_grad(d: int, p, syndromes, opts: bbp_opts, params, targets, use, *, wor
     ws_bytes = workspace_size(d, b, opts, True)
     if workspace is None or workspace.numel() < ws_bytes:
         workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=dev)
-    pv, pt = _p_args(p, b)
-    targets, use = targets.contiguous(), use.contiguous()
+    pv, pt = _p_args(p, b, stream)
+    targets, use = _contiguous(targets, stream), _contiguous(use, stream)
     _lib.check_warm(_lib.lib().bbp_warm_loss_grad(
         d, pv, pt.data_ptr() if pt is not None else None, syndromes.data_ptr(), b, C.byref(opts),
         params.data_ptr(), targets.data_ptr(), use.data_ptr(), n_used * M, grad.data_ptr(), loss.data_ptr(),
@@ -151,8 +154,8 @@ def decode(d: int, p, syndromes, opts: bbp_opts, params, *, precision: int = 1, 
     check): outside it the whole batch is decoded from the uniform start. Returns the output dict of
     decode_device plus 'fallback' (number of syndromes decoded from the uniform start)."""
     import torch
-    from . import _outputs
-    syndromes = syndromes.contiguous()
+    from . import _contiguous, _outputs
+    syndromes = _contiguous(syndromes, stream)
     b, dev = syndromes.shape[0], syndromes.device
     n = C.c_size_t()
     _lib.check_warm(_lib.lib().bbp_warm_decode_workspace_size(d, b, C.byref(opts), C.byref(n)))
@@ -160,7 +163,7 @@ def decode(d: int, p, syndromes, opts: bbp_opts, params, *, precision: int = 1, 
         workspace = torch.empty(n.value, dtype=torch.uint8, device=dev)
     if out is None:
         out = _outputs(b, d * d + (d - 1) * (d - 1), dev)
-    pv, pt = _p_args(p, b)
+    pv, pt = _p_args(p, b, stream)
     fb = C.c_int64()
     lo, hi = trained_range() if trained is None else trained
     _lib.check_warm(_lib.lib().bbp_warm_decode(

@@ -284,3 +284,37 @@ def test_concurrent_multistream_decodes_match_serial(dev):
                 _same(r, ref[k], f"thread {k}")
     finally:
         bbp.set_tuning(d, opts, 0, 1)
+
+
+def test_strided_inputs_on_a_busy_side_stream(dev):
+    """Syndromes, rates and start messages that are not contiguous are copied on the stream that decodes them: the
+    current stream is kept busy, so a copy made there would not have run when the decode starts, and its memory is
+    handed out again as soon as the call returns."""
+    import torch
+    import paper_2402_04834_amd as bbp
+    d, b = 9, 24
+    opts = bbp.default_opts(block=6, chi=32, max_iter=8)
+    _, syn = workload.make_batch(d, 0.1, 2 * b, workload="test", p_index=77)
+    s = torch.from_numpy(np.ascontiguousarray(syn)).to(dev)
+    ps = torch.linspace(0.05, 0.15, 2 * b, dtype=torch.float64, device=dev)
+    M = bbp.plan_query(d, opts).num_messages
+    init = torch.rand((2 * b, 4, M, 64), generator=torch.Generator().manual_seed(5)).to(dev) + 0.1
+    cut = [x[::2] for x in (s, ps, init)]
+    assert not any(x.is_contiguous() for x in cut)
+    whole = [x.contiguous() for x in cut]
+    ref_one = _np(bbp.decode_device(d, 0.1, whole[0], opts))
+    ref_all, _, _ = bbp.decode_groups([(d, whole[1], whole[0], 0, whole[2])], opts)
+    torch.cuda.synchronize()
+    st = torch.cuda.Stream(dev)
+    _say("[strided] side stream, current stream busy")
+    for _ in range(3):
+        ws = torch.empty(bbp.workspace_size(d, b, opts), dtype=torch.uint8, device=dev)
+        torch.cuda._sleep(20_000_000)
+        one = bbp.decode_device(d, 0.1, cut[0], opts, workspace=ws, stream=st)
+        torch.cuda._sleep(20_000_000)
+        many, _, _ = bbp.decode_groups([(d, cut[1], cut[0], 0, cut[2])], opts, stream=st)
+        junk = [torch.full_like(x, 1) for x in whole]
+        torch.cuda.synchronize()
+        _same(_np(one), ref_one, "one group")
+        _same(_np(many[0]), _np(ref_all[0]), "start messages")
+        del junk
