@@ -637,8 +637,10 @@ Route choose_route(const std::vector<GroupRun>& gr, const bbp_opts* opts) {
     // a workgroup per job wherever its messages fit the LDS (d <= 32 for 2x2 blocks, d <= 21 for single tensors): faster
     // than a launch per class and round at every size tried (2x2 blocks, d = 5, 1 syndrome: 4452 -> 141 us; d = 17, 16:
     // 7376 -> 361, 2048: 32.9 -> 4.0 ms; d = 9, 4096: 17.4 -> 3.2 ms; single tensors, d = 17, 1024: 52.0 -> 6.3 ms)
+    // (the allocation-free decode holds no lists for it)
     for (const GroupRun& g : gr)
-      if (g.in.batch > 0 && bbp::small_loop_lds(g.dp->plan.M) > bbp::SMALL_LOOP_LDS_MAX) return Route::classes;
+      if (g.in.batch > 0 && (g.dp->small_count[0][2] == 0 || bbp::small_loop_lds(g.dp->plan.M) > bbp::SMALL_LOOP_LDS_MAX))
+        return Route::classes;
     return Route::small;
   }
   static const double round_start[7] = {0, 0, 0, 280.0, 300.0, 310.0, 520.0};

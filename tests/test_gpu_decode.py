@@ -512,3 +512,18 @@ def test_depolarizing_group_in_a_biased_launch(dev, k):
         np.testing.assert_allclose(x, y, rtol=0, atol=1e-6)
         ll = own[0]["loglik"].cpu().numpy()
         np.testing.assert_allclose(mixed[g]["loglik"].cpu().numpy(), ll, rtol=0, atol=2e-5 + 2e-7 * np.abs(ll).max())
+
+
+@pytest.mark.parametrize("d,k,b", [(5, 2, 3), (9, 2, 40), (7, 1, 5), (9, 3, 2), (9, 6, 30)])
+def test_allocation_free_decode_equals_decode(dev, d, k, b):
+    """The allocation-free entry point, whose plan tables lie in its own scratch, on every launch route's sizes."""
+    import torch
+    import paper_2402_04834_amd as bbp
+    _, syn = workload.make_batch(d, 0.1, b, workload="test", p_index=40 + k)
+    s = torch.from_numpy(np.ascontiguousarray(syn)).to(dev)
+    opts = bbp.default_opts(block=k, chi=32, max_iter=12)
+    _say(f"[noalloc routes] d={d} k={k} batch {b}")
+    one, ref = bbp.decode_device_noalloc(d, 0.1, s, opts), bbp.decode_device(d, 0.1, s, opts)
+    torch.cuda.synchronize()
+    for key in ("loglik", "delta", "iters", "coset", "correction"):
+        assert torch.equal(one[key].view(torch.uint8), ref[key].view(torch.uint8)), key
