@@ -5,7 +5,8 @@
 //   init_kernel       uniform unit messages (remark 2) or given start messages, convergence flags cleared
 //   sweep_kernel      block message updates, one wavefront per (job, sweep), launched per sweep class
 //                     (sweep_kernel.hip, wave_sweep.hpp): Sec. III.D update, normalisation (remark 3),
-//                     damping (remark 7), distance term (remark 4)
+//                     damping (remark 7), distance term (remark 4); small decodes and small blocks in fewer launches
+//                     (fused_sweep.hip, small_loop.hip)
 //   delta_kernel      convergence distance per job and early exit (Alg. 1 BP loop)
 //   sweep_kernel      (closing mode) W_v of every block for the Bethe estimate (Lemma 3.1)
 //   finalize_kernel   ln Z = sum ln W_v - sum ln <m_uv, m_vu>, decision rule, correction f_s L*
