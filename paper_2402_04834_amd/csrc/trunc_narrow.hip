@@ -526,7 +526,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void tr
           for (int in = 0; in < 2; ++in) {
             const int pv = u ^ dn, ph = in ^ h;
             const int code = lb ^ (swap ? (ph | (pv << 1)) : (pv | (ph << 1)));
-            const double p = lds[L_P + ((code & 1) << 1 | code >> 1)];   // (x and z swapped, as in trunc_sweep.hip)
+            const double p = lds[L_P + code];
             tt[u][in] = (dead || (n_up && u) || (n_in && in)) ? 0.0 : p;
           }
       } else {

@@ -69,7 +69,8 @@ __device__ __forceinline__ double tab(const SweepDesc& s, int L, const uint8_t* 
                                       int e) {
   int r, c;
   frame_site(s.frame, s.r0, s.c0, s.kr, s.kc, t, i, r, c);
-  const float m = site_entry(s.frame, L, r, c, lab[r * L + c], 1.0f, 2.0f, 3.0f, 4.0f, e);
+  // (site_entry's noise arguments are I, Z, X, Y: each marks its place in pq)
+  const float m = site_entry(s.frame, L, r, c, lab[r * L + c], 1.0f, 3.0f, 2.0f, 4.0f, e);
   if ((r + c) & 1) return (double)m;
   const int k = (int)m;
   return k == 0 ? 0.0 : pq[k - 1];

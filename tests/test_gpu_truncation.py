@@ -237,3 +237,30 @@ def test_narrow_sweeps_at_shape_edges(dev, d, p, k, chi, count):
     got = _decode(dev, d, p, syn, block=k, chi=chi, max_iter=3, damping=0.1, fixed_iters=1)
     _check_messages(got["messages"], ref, ref["plan"])
     _check_loglik(got["loglik"], ref["loglik"])
+
+
+@pytest.mark.parametrize("d,k,chi,iters,count", [
+    (5, 3, 2, 3, 4), (9, 6, 8, 3, 3),       # narrow form: alone, and beside exact sweeps of the same blocks
+    (7, 6, 12, 3, 3), (9, 8, 16, 2, 2),     # wide form: message strides 64 and 256
+])
+def test_truncating_biased_noise_against_oracle(dev, d, k, chi, iters, count):
+    """Biased Pauli noise with X, Z and Y all different where chi binds: messages and ln Z against the oracle with the
+    same probabilities, bounds as for depolarizing noise. The group decodes beside a depolarizing one, whose results the
+    four-probability launch leaves within the same bounds."""
+    import torch
+    import paper_2402_04834_amd as bbp
+    probs = (0.88, 0.02, 0.085, 0.015)                          # I, X, Z, Y
+    pi = np.array([[probs[0], probs[2]], [probs[1], probs[3]]])   # [x][z]
+    opts = bbp.default_opts(block=k, chi=chi, max_iter=iters, fixed_iters=1)
+    assert bbp.plan_query(d, opts).truncating_sweeps > 0
+    _, syn = workload.make_batch_pauli(d, probs, count, workload="test", p_index=d + k + chi)
+    s = torch.from_numpy(np.ascontiguousarray(syn)).to(dev)
+    _say(f"[trunc-biased] d={d} k={k} chi={chi} count={count}")
+    outs, _, _ = bbp.decode_groups([(d, probs, s), (d, 0.1, s)], opts, messages=True)
+    torch.cuda.synchronize()
+    for out, noise in zip(outs, (pi, None)):
+        ref = blockbp.decode(d, 0.1, syn, block=(k, k), chi=chi, max_iter=iters, fixed_iters=True, noise=noise,
+                             return_messages=True)
+        _check_messages(out["messages"].cpu().numpy(), ref, ref["plan"])
+        _check_loglik(out["loglik"].cpu().numpy(), ref["loglik"])
+        _decisions_agree(out["coset"].cpu().numpy(), ref["loglik"], ref["coset"], ref["delta"], 1e-2)
