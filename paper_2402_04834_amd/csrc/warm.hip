@@ -385,8 +385,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void c
 
 // Weight gradient, K = rows split over grid.y: workgroup (x, y) sums the rows [y kchunk, (y + 1) kchunk) into the
 // 128 rows m = t CIN + ci from 128 x of its partial matrix P[y], workgroup (0, y) the column sums of dY (the bias
-// gradient) into its row 9 CIN; dw_reduce_kernel adds the partials in order (a
-// fixed order: the gradients of two calls are equal). Bound by the FP32 matrix rate like conv_f32, with the same wave
+// gradient) into its row 9 CIN; dw_reduce_kernel adds the partials in a fixed order (dY itself comes from the
+// features' gradient, which head_kernel accumulates atomically). Bound by the FP32 matrix rate like conv_f32, with the same wave
 // tiles, 16-row stages and two LDS buffers. The LDS tiles keep the activations' layout [row][channel]: MFMA
 // operands are 4-byte reads of 16 consecutive channels at 4 rows, a row stride of 16 modulo 64 floats putting the 64
 // lanes on distinct banks. The partials replace atomic adds of every split into the one gradient. Measured at d = 17,
@@ -1223,12 +1223,12 @@ __global__ __launch_bounds__(64) void head_proj_kernel(const float* __restrict__
 // derivatives, the first half of Wp with the pair it opens, the second half with the pair it closes -- so
 // workgroup (direction, x) walks the messages of its jobs x, x + gridDim.x, ... once: thread k holds the rows k of the
 // three blocks (10 sums, in registers) for input k of [F(a_i), F(b_i)], loads that feature of all legs of a message
-// together (the loads' latency bounds this kernel) and adds its sums to the gradient at the end (atomically: the
-// gradient is zeroed before). The derivatives are uniform over the workgroup. Measured at d = 17, 16 syndromes: 76 us;
-// 36 wavefronts that each walked every job and message one after the other took 3268 us.
+// together (the loads' latency bounds this kernel) and stores its sums as partial gradient x of all four directions,
+// which dw_reduce_kernel adds in the order of x. The derivatives are uniform over the workgroup. Measured at d = 17,
+// 16 syndromes: 75 us and 7 for the sum; 36 wavefronts that each walked every job and message one after the other took 3268 us.
 __global__ __launch_bounds__(2 * C3) void head_grad_kernel(const float* __restrict__ F, const int32_t* __restrict__ legs,
                                                            int M, int L, int64_t jobs, const uint8_t* __restrict__ use,
-                                                           const float* __restrict__ dout, float* __restrict__ grad) {
+                                                           const float* __restrict__ dout, float* __restrict__ P) {
   const int dir = blockIdx.y, k = threadIdx.x, ch = k < C3 ? k : k - C3, side = k < C3 ? 2 : 2 + MAXK;
   float u[2] = {0, 0}, open[4] = {0, 0, 0, 0}, close[4] = {0, 0, 0, 0};
   float bu[2] = {0, 0}, bp[4] = {0, 0, 0, 0};
@@ -1263,16 +1263,16 @@ __global__ __launch_bounds__(2 * C3) void head_grad_kernel(const float* __restri
       }
     }
   }
-  float* G = grad + OFF.head + (size_t)dir * HEAD;
+  float* G = P + ((size_t)blockIdx.x * 4 + dir) * HEAD;
   float* Wp = G + 2 * C3 * 2 + 2;
-  for (int c = 0; c < 2; ++c) atomicAdd(G + k * 2 + c, u[c]);
+  for (int c = 0; c < 2; ++c) G[k * 2 + c] = u[c];
   for (int q = 0; q < 4; ++q) {
-    atomicAdd(Wp + k * 4 + q, open[q]);
-    atomicAdd(Wp + (2 * C3 + k) * 4 + q, close[q]);
+    Wp[k * 4 + q] = open[q];
+    Wp[(2 * C3 + k) * 4 + q] = close[q];
   }
   if (k == 0) {
-    for (int c = 0; c < 2; ++c) atomicAdd(G + 2 * C3 * 2 + c, bu[c]);
-    for (int q = 0; q < 4; ++q) atomicAdd(Wp + 4 * C3 * 4 + q, bp[q]);
+    for (int c = 0; c < 2; ++c) G[2 * C3 * 2 + c] = bu[c];
+    for (int q = 0; q < 4; ++q) Wp[4 * C3 * 4 + q] = bp[q];
   }
 }
 
@@ -1499,6 +1499,19 @@ int conv_weights(int L, int64_t rows, const float* X, const float* dY, float* dW
   return BBP_OK;
 }
 
+// Gradient of the heads' weights: up to 128 workgroups per direction (two per CU), as far as their partials fit in
+// `scratch`; with no room for two the one writes the gradient itself.
+int head_weights(const float* F, const int32_t* legs, int M, int L, int64_t jobs, const uint8_t* use, const float* dout,
+                 float* grad, float* scratch, size_t scratch_bytes, hipStream_t st) {
+  constexpr int N = 4 * HEAD;
+  const int64_t groups = std::max<int64_t>(1, std::min({jobs, (int64_t)128, (int64_t)(scratch_bytes / (N * sizeof(float)))}));
+  head_grad_kernel<<<dim3((unsigned)groups, 4), dim3(2 * C3), 0, st>>>(F, legs, M, L, jobs, use, dout,
+                                                                     groups > 1 ? scratch : grad);
+  if (groups > 1) dw_reduce_kernel<<<dim3((N + 255) / 256), dim3(256), 0, st>>>(scratch, N, (int)groups, grad);
+  W_TRY(hipGetLastError());
+  return BBP_OK;
+}
+
 struct Args {
   int d;
   const bbp_opts* opts;
@@ -1697,13 +1710,12 @@ int bbp_warm_loss_grad(int32_t d, double p, const double* p_dev, const uint8_t* 
     head_kernel<true><<<dim3((unsigned)(jobs * M)), dim3(64), 0, st>>>(
         F, lg.dev, M, L, jobs, params_dev, targets_dev, use_dev, 1.0f / (float)trained_messages, nullptr, dout, dF,
         lossb);
-    // up to 128 workgroups per direction: two per CU, and no more adds into a gradient entry than that
-    head_grad_kernel<<<dim3((unsigned)std::min<int64_t>(jobs, 128), 4), dim3(2 * C3), 0, st>>>(F, lg.dev, M, L, jobs, use_dev,
-                                                                                         dout, grad_dev);
+    if ((rc = head_weights(F, lg.dev, M, L, jobs, use_dev, dout, grad_dev + OFF.head, dA2, w.dA1 - w.dA2, st))) return rc;
   }
   sum_kernel<<<1, 256, 0, st>>>(lossb, jobs * std::max(M, 1), loss_dev);
   W_TRY(hipGetLastError());
-  // conv3 (no activation); the weight gradients' partials go where the next gradient is still to be written
+  // conv3 (no activation); the weight gradients' partials, the heads' too, go where the next gradient is still to be
+  // written
   if ((rc = conv_weights<C2, C3>(L, rows, A2, dF, grad_dev + OFF.w3, dA2, w.dA1 - w.dA2, st))) return rc;
   if ((rc = conv<G_DX, C3, C2, 1>(L, rows, dF, params_dev + OFF.w3, dA2, A2, st))) return rc;
   // conv2 (ReLU: dA2 is already the gradient of its pre-activation); dF has been used

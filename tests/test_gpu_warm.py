@@ -434,3 +434,30 @@ def test_bf16_forward_at_listed_sites_equals_plain(dev, d, k, b):
     assert b > n
     parts = torch.cat([warm.predict(d, 0.1, s[i:i + n].contiguous(), opts, prm) for i in range(0, b, n)])
     assert torch.equal(whole.view(torch.int32), parts.view(torch.int32))
+
+
+@pytest.mark.parametrize("d,k,b", [(2, 2, 2), (3, 2, 3), (7, 3, 5), (11, 6, 40)])
+def test_head_gradient_is_the_same_in_every_call(dev, d, k, b):
+    """The heads' weight gradients depend on the features and the targets only, which a repeated call forms alike, and
+    are summed in a fixed order: equal bitwise over six calls. Grids with room for one, a few and all 128 partial
+    gradients in the workspace; a job without training among them."""
+    import torch
+    import paper_2402_04834_amd as bbp
+    from paper_2402_04834_amd import warm
+    _, syn = workload.make_batch(d, 0.1, b, workload="warm", p_index=360 + d)
+    opts = bbp.default_opts(block=k, chi=32)
+    M = bbp.plan_query(d, opts).num_messages
+    s = torch.from_numpy(syn).to(dev)
+    targets = (torch.rand((b, 4, M, 64), generator=torch.Generator().manual_seed(d)) + 0.05).to(dev)
+    use = torch.ones(4 * b, dtype=torch.uint8, device=dev)
+    use[1] = 0
+    th = torch.from_numpy(_theta(160 + d, head_scale=0.5)).to(dev)
+    head = sum(v.size for n, v in warmnet.unpack(np.zeros(th.numel())).items() if n.startswith("head"))
+    _say(f"[warm head grad] d={d} k={k} batch {b}")
+    first = None
+    for _ in range(6):
+        _, grad = warm.loss_grad(d, 0.1, s, opts, th, targets, use)
+        part = grad[-head:].view(torch.int32)
+        first = part if first is None else first
+        assert float(grad[-head:].abs().max()) > 0
+        assert torch.equal(part, first)
