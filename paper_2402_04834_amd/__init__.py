@@ -62,14 +62,29 @@ def workspace_size(d: int, batch: int, opts: bbp_opts) -> int:
     return n.value
 
 
-def _outputs(batch, n, dev):
+def _empty(shape, dtype, dev, stream):
+    """Memory for work on `stream` (None: the current one), allocated there. The current stream's memory may still be in
+    use by work that it holds, and would be handed out again, in that stream's order, once the call has dropped it. What
+    the call returns is for the current stream to use too: recorded on it."""
+    import torch
+    if stream is None:
+        return torch.empty(shape, dtype=dtype, device=dev)
+    current = torch.cuda.current_stream(dev)
+    with torch.cuda.stream(stream):
+        t = torch.empty(shape, dtype=dtype, device=dev)
+    if stream != current:
+        t.record_stream(current)
+    return t
+
+
+def _outputs(batch, n, dev, stream=None):
     import torch
     return dict(
-        loglik=torch.empty((batch, 4), dtype=torch.float64, device=dev),
-        delta=torch.empty((batch, 4), dtype=torch.float64, device=dev),
-        iters=torch.empty((batch, 4), dtype=torch.int32, device=dev),
-        coset=torch.empty((batch,), dtype=torch.uint8, device=dev),
-        correction=torch.empty((batch, n), dtype=torch.uint8, device=dev),
+        loglik=_empty((batch, 4), torch.float64, dev, stream),
+        delta=_empty((batch, 4), torch.float64, dev, stream),
+        iters=_empty((batch, 4), torch.int32, dev, stream),
+        coset=_empty((batch,), torch.uint8, dev, stream),
+        correction=_empty((batch, n), torch.uint8, dev, stream),
     )
 
 
@@ -102,17 +117,16 @@ def decode_device(d: int, p: float, syndromes, opts: bbp_opts, *, workspace=None
     n = d * d + (d - 1) * (d - 1)
     ws_bytes = workspace_size(d, batch, opts)
     if workspace is None or workspace.numel() < ws_bytes:
-        workspace = torch.empty(max(ws_bytes, 1), dtype=torch.uint8, device=dev)
+        workspace = _empty(max(ws_bytes, 1), torch.uint8, dev, stream)
     if out is None:
-        out = _outputs(batch, n, dev)
+        out = _outputs(batch, n, dev, stream)
     else:
         assert out["loglik"].shape == (batch, 4) and out["correction"].shape == (batch, n)
         out = {k: v for k, v in out.items() if k in ("loglik", "delta", "iters", "coset", "correction")}
     msg_ptr = None
     if messages:
         info = plan_query(d, opts)
-        out["messages"] = torch.empty((batch, 4, max(info.num_messages, 1), info.message_stride),
-                                      dtype=torch.float32, device=dev)
+        out["messages"] = _empty((batch, 4, max(info.num_messages, 1), info.message_stride), torch.float32, dev, stream)
         msg_ptr = out["messages"].data_ptr()
     st = (stream if stream is not None else torch.cuda.current_stream(dev)).cuda_stream
     tm = bbp_timing() if timing else None
@@ -145,7 +159,7 @@ def decode_device_noalloc(d: int, p: float, syndromes, opts: bbp_opts, *, stream
     dev = syndromes.device
     n = d * d + (d - 1) * (d - 1)
     if out is None:
-        out = _outputs(batch, n, dev)
+        out = _outputs(batch, n, dev, stream)
     st = (stream if stream is not None else torch.cuda.current_stream(dev)).cuda_stream
     _lib.check(_lib.lib().bbp_decode_device_noalloc(
         d, p, syndromes.data_ptr(), batch, C.byref(opts), out["loglik"].data_ptr(), out["delta"].data_ptr(),
@@ -175,7 +189,7 @@ def bmps_decode(d: int, p, syndromes, chi: int = 16, *, workspace=None, correcti
     n = d * d + (d - 1) * (d - 1)
     ws_bytes = bmps_workspace_size(d, batch, chi)
     if workspace is None or workspace.numel() < ws_bytes:
-        workspace = torch.empty(max(ws_bytes, 1), dtype=torch.uint8, device=dev)
+        workspace = _empty(max(ws_bytes, 1), torch.uint8, dev, stream)
     pval, p_ptr, noise, keep = 0.0, None, None, None
     if isinstance(p, torch.Tensor):
         keep = p.to(device=dev, dtype=torch.float64)
@@ -188,10 +202,9 @@ def bmps_decode(d: int, p, syndromes, chi: int = 16, *, workspace=None, correcti
         noise = (C.c_double * 4)(*[float(v) for v in p])
     else:
         pval = float(p)
-    out = dict(loglik=torch.empty((batch, 4), dtype=torch.float64, device=dev),
-               coset=torch.empty(batch, dtype=torch.uint8, device=dev))
+    out = dict(loglik=_empty((batch, 4), torch.float64, dev, stream), coset=_empty(batch, torch.uint8, dev, stream))
     if correction:
-        out["correction"] = torch.empty((batch, n), dtype=torch.uint8, device=dev)
+        out["correction"] = _empty((batch, n), torch.uint8, dev, stream)
     st = (stream if stream is not None else torch.cuda.current_stream(dev)).cuda_stream
     ms = C.c_float(0.0)
     _lib.check(_lib.lib().bbp_bmps_decode_device(
@@ -239,7 +252,7 @@ def decode_groups(groups, opts: bbp_opts, *, workspace=None, timing: bool = Fals
             p = _contiguous(p, stream)
             keep.append(p)
             p_ptr, p_val = p.data_ptr(), 0.0
-        o = outs_in[k] if outs_in is not None else _outputs(b, d * d + (d - 1) * (d - 1), dev)
+        o = outs_in[k] if outs_in is not None else _outputs(b, d * d + (d - 1) * (d - 1), dev, stream)
         outs.append(o)
         init_ptr = None
         if init is not None:
@@ -251,8 +264,7 @@ def decode_groups(groups, opts: bbp_opts, *, workspace=None, timing: bool = Fals
         if messages:
             if "messages" not in o:
                 info = plan_query(d, _with_chi(opts, chi))
-                o["messages"] = torch.empty((b, 4, max(info.num_messages, 1), info.message_stride),
-                                            dtype=torch.float32, device=dev)
+                o["messages"] = _empty((b, 4, max(info.num_messages, 1), info.message_stride), torch.float32, dev, stream)
             msg_ptr = o["messages"].data_ptr()
         gs[k] = bbp_group(d, chi, p_val, p_ptr, syn.data_ptr(), b, o["loglik"].data_ptr(), o["delta"].data_ptr(),
                           o["iters"].data_ptr(), o["coset"].data_ptr(), o["correction"].data_ptr(), init_ptr,
@@ -260,7 +272,7 @@ def decode_groups(groups, opts: bbp_opts, *, workspace=None, timing: bool = Fals
     n = C.c_size_t()
     _lib.check(_lib.lib().bbp_workspace_size_groups(gs, len(groups), C.byref(opts), C.byref(n)))
     if workspace is None or workspace.numel() < n.value:
-        workspace = torch.empty(max(n.value, 1), dtype=torch.uint8, device=dev)
+        workspace = _empty(max(n.value, 1), torch.uint8, dev, stream)
     st = (stream if stream is not None else torch.cuda.current_stream(dev)).cuda_stream
     tm = bbp_timing() if timing else None
     _lib.check(_lib.lib().bbp_decode_groups(gs, len(groups), C.byref(opts), workspace.data_ptr(),
@@ -282,7 +294,7 @@ def autotune(d: int, p: float, syndromes, opts: bbp_opts, *, workspace=None, str
     syndromes = _contiguous(syndromes, stream)
     ws_bytes = workspace_size(d, syndromes.shape[0], opts)
     if workspace is None or workspace.numel() < ws_bytes:
-        workspace = torch.empty(max(ws_bytes, 1), dtype=torch.uint8, device=syndromes.device)
+        workspace = _empty(max(ws_bytes, 1), torch.uint8, syndromes.device, stream)
     st = (stream if stream is not None else torch.cuda.current_stream(syndromes.device)).cuda_stream
     best = bbp_tuning()
     _lib.check(_lib.lib().bbp_autotune(d, p, syndromes.data_ptr(), syndromes.shape[0], C.byref(opts),

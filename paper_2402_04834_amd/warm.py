@@ -86,14 +86,14 @@ def predict(d: int, p, syndromes, opts: bbp_opts, params, *, precision: int = 1,
     """Start messages [batch, 4, M, 64] (float32, unit norm) for syndromes [batch, m] (uint8 CUDA).
     precision 1: BF16 weights and activations, FP32 accumulation (inference); 0: FP32 throughout."""
     import torch
-    from . import _contiguous
+    from . import _contiguous, _empty
     syndromes = _contiguous(syndromes, stream)
     b, dev = syndromes.shape[0], syndromes.device
     M = max(_plan_messages(d, opts), 1)
-    out = torch.empty((b, 4, M, 64), dtype=torch.float32, device=dev)
+    out = _empty((b, 4, M, 64), torch.float32, dev, stream)
     ws_bytes = workspace_size(d, b, opts, False)
     if workspace is None or workspace.numel() < ws_bytes:
-        workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=dev)
+        workspace = _empty(ws_bytes, torch.uint8, dev, stream)
     pv, pt = _p_args(p, b, stream)
     _lib.check_warm(_lib.lib().bbp_warm_predict(
         d, pv, pt.data_ptr() if pt is not None else None, syndromes.data_ptr(), b, C.byref(opts),
@@ -111,21 +111,25 @@ def loss_grad(d: int, p, syndromes, opts: bbp_opts, params, targets, use, *, wor
     KL(q || softmax(s)), q the target message normalised to sum 1 and s the network's scores (the loss of
     bbp_warm_loss_grad); targets [batch, 4, M, 64] float32, use [batch * 4] uint8 (CUDA tensors)."""
     import torch
-    from . import _contiguous
+    from . import _contiguous, _empty
     syndromes = _contiguous(syndromes, stream)
     b, dev = syndromes.shape[0], syndromes.device
     M = _plan_messages(d, opts)
     assert targets.shape == (b, 4, max(M, 1), 64) and targets.dtype == torch.float32
     assert use.shape == (4 * b,) and use.dtype == torch.uint8
-    n_used = int(use.sum().item())
-    loss = torch.zeros(1, dtype=torch.float32, device=dev)
-    grad = torch.empty_like(params)
+    if stream is not None:   # the host waits for the sum: inputs that the current stream forms are complete then too
+        stream.wait_stream(torch.cuda.current_stream(dev))
+    with torch.cuda.stream(stream):
+        n_used = int(use.sum().item())
+    loss, grad = _empty(1, torch.float32, dev, stream), _empty(params.shape, params.dtype, dev, stream)
     if n_used == 0 or M == 0:
-        grad.zero_()
+        with torch.cuda.stream(stream):
+            loss.zero_()
+            grad.zero_()
         return loss, grad
     ws_bytes = workspace_size(d, b, opts, True)
     if workspace is None or workspace.numel() < ws_bytes:
-        workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=dev)
+        workspace = _empty(ws_bytes, torch.uint8, dev, stream)
     pv, pt = _p_args(p, b, stream)
     targets, use = _contiguous(targets, stream), _contiguous(use, stream)
     _lib.check_warm(_lib.lib().bbp_warm_loss_grad(
@@ -154,15 +158,15 @@ def decode(d: int, p, syndromes, opts: bbp_opts, params, *, precision: int = 1, 
     check): outside it the whole batch is decoded from the uniform start. Returns the output dict of
     decode_device plus 'fallback' (number of syndromes decoded from the uniform start)."""
     import torch
-    from . import _contiguous, _outputs
+    from . import _contiguous, _empty, _outputs
     syndromes = _contiguous(syndromes, stream)
     b, dev = syndromes.shape[0], syndromes.device
     n = C.c_size_t()
     _lib.check_warm(_lib.lib().bbp_warm_decode_workspace_size(d, b, C.byref(opts), C.byref(n)))
     if workspace is None or workspace.numel() < n.value:
-        workspace = torch.empty(n.value, dtype=torch.uint8, device=dev)
+        workspace = _empty(n.value, torch.uint8, dev, stream)
     if out is None:
-        out = _outputs(b, d * d + (d - 1) * (d - 1), dev)
+        out = _outputs(b, d * d + (d - 1) * (d - 1), dev, stream)
     pv, pt = _p_args(p, b, stream)
     fb = C.c_int64()
     lo, hi = trained_range() if trained is None else trained

@@ -318,3 +318,44 @@ def test_strided_inputs_on_a_busy_side_stream(dev):
         _same(_np(one), ref_one, "one group")
         _same(_np(many[0]), _np(ref_all[0]), "start messages")
         del junk
+
+
+def test_buffers_of_a_side_stream_call_are_its_own(dev):
+    """Calls on a side stream that allocate their workspace and outputs, the current stream's allocator having just
+    got blocks of those sizes back: with the current stream behind (its last writes to those blocks are still to come)
+    and with the side stream behind (the call has dropped its workspace before running), results equal those of the
+    idle device and memory allocated afterwards keeps what is written to it."""
+    import torch
+    import paper_2402_04834_amd as bbp
+    from paper_2402_04834_amd import warm
+    d, b = 9, 24
+    opts = bbp.default_opts(block=6, chi=32, max_iter=8)
+    syn = torch.from_numpy(workload.make_batch(d, 0.1, b, workload="test", p_index=79)[1]).to(dev)
+    prm = torch.from_numpy(warm.init_params(5)).to(dev)
+    st = torch.cuda.Stream(dev)
+    predict = lambda **kw: dict(messages=warm.predict(d, 0.1, syn, opts, prm, **kw))
+    decode = lambda **kw: {k: v for k, v in bbp.decode_device(d, 0.1, syn, opts, **kw).items() if k in KEYS}
+    for name, call, ws_bytes in (("predict", predict, warm.workspace_size(d, b, opts, False)),
+                                 ("decode", decode, bbp.workspace_size(d, b, opts))):
+        ref = {k: v.clone() for k, v in call().items()}
+        torch.cuda.synchronize()
+        sizes = [ws_bytes] + [v.numel() * v.element_size() for v in ref.values()]
+        for behind in ("current", "side"):
+            _say(f"[side stream buffers] {name}, the {behind} stream behind")
+            blocks = [torch.empty(n, dtype=torch.uint8, device=dev) for n in sizes]
+            torch.cuda.synchronize()
+            if behind == "current":
+                torch.cuda._sleep(20_000_000)
+                for n in range(len(blocks)):
+                    blocks[n].fill_(255)
+            else:
+                with torch.cuda.stream(st):
+                    torch.cuda._sleep(20_000_000)
+            del blocks
+            got = call(stream=st)
+            after = [torch.full((n,), 85, dtype=torch.uint8, device=dev) for n in sizes]
+            torch.cuda.synchronize()
+            for key, v in ref.items():
+                assert torch.equal(got[key].view(torch.uint8), v.view(torch.uint8)), key
+            assert all(bool((x == 85).all()) for x in after)
+            del after
