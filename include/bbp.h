@@ -236,12 +236,14 @@ int bbp_decode_groups(const bbp_group* groups, int32_t ngroups, const bbp_opts* 
  * or job-major order, and spread over 1, 2 or 4 streams (a round's launches are independent). Results do
  * not depend on the choice. bbp_autotune times every variant on the given batch (a warm-up and two
  * timed decodes each, on `stream`; it allocates and frees a small device output buffer), keeps the
- * fastest for (d, block size, chi) on the current device, and returns it; later decodes of that key use
- * it. bbp_set_tuning sets it directly. Errors: BBP_EINVAL, BBP_ENOMEM, BBP_EHIP. */
+ * fastest for (d, block size, chi) on the current device, and returns it; later decodes of that key that run
+ * by class launches use it. Small batches and small blocks run in fewer launches without variants: there the
+ * tuning changes nothing, and bbp_autotune still times the class launches. bbp_set_tuning sets it directly. Errors: BBP_EINVAL, BBP_ENOMEM, BBP_EHIP. */
 typedef struct bbp_tuning {
   int32_t order;     /* 0 sweep-major, 1 job-major */
   int32_t streams;   /* 1, 2 or 4 */
-  double ms;         /* decode time of the chosen variant on the tuning batch (output of bbp_autotune) */
+  double ms;         /* decode time of the chosen variant, by class launches, on the tuning batch (output of
+                        bbp_autotune) */
 } bbp_tuning;
 int bbp_autotune(int32_t d, double p, const uint8_t* syndromes_dev, int64_t batch, const bbp_opts* opts,
                  void* workspace, size_t workspace_bytes, void* stream, bbp_tuning* best);

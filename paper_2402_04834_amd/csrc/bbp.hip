@@ -684,9 +684,10 @@ Route choose_route(const std::vector<GroupRun>& gr, const bbp_opts* opts) {
   return t_rounds <= t_classes ? Route::rounds : Route::classes;
 }
 
-// Enqueue the whole decode of the groups on st (and the auxiliary streams of the tune).
+// Enqueue the whole decode of the groups on st (and the auxiliary streams of the tune), with class launches whatever the
+// route if by_class is set, or if marks asks for a record of every launch.
 int enqueue(std::vector<GroupRun>& gr, const bbp_opts* opts, const Tune& tn, hipStream_t st,
-            Aux* aux, std::vector<Mark>* marks) {
+            Aux* aux, std::vector<Mark>* marks, bool by_class = false) {
   const int ng = (int)gr.size();
   // consecutive launches on one stream share their boundary event (an event record is a queue packet)
   int dev = 0;
@@ -825,7 +826,7 @@ int enqueue(std::vector<GroupRun>& gr, const bbp_opts* opts, const Tune& tn, hip
     return BBP_OK;
   };
   // small decodes: the fused kernels, one launch per set of groups with the same block sizes
-  const Route route = marks ? Route::classes : choose_route(gr, opts);
+  const Route route = marks || by_class ? Route::classes : choose_route(gr, opts);
   std::map<int, std::vector<int>> sets;
   if (route == Route::rounds || route == Route::loop)
     for (int g = 0; g < ng; ++g)
@@ -1015,6 +1016,8 @@ uint64_t u64(T v) {
   return r;
 }
 
+// force: time a launch variant -- of the class launches, the only ones that have variants (on the other routes every
+// variant would be the same work, and the pick, which later batches of any size use, noise)
 int decode_groups(const bbp_group* groups, int ng, const bbp_opts* opts, void* workspace, size_t workspace_bytes,
                   void* stream, bbp_timing* timing, const Tune* force) {
   std::vector<GroupRun> gr;
@@ -1077,7 +1080,7 @@ int decode_groups(const bbp_group* groups, int ng, const bbp_opts* opts, void* w
     }
     return rc;
   }
-  if (!opts->graph) return enqueue(gr, opts, tn, st, aux, nullptr);
+  if (!opts->graph) return enqueue(gr, opts, tn, st, aux, nullptr, force != nullptr);
 
   // graph mode: capture the decode once per argument set, replay it afterwards
   if (!st) return fail(BBP_EINVAL, "graph mode needs a stream other than the default stream");

@@ -359,3 +359,23 @@ def test_buffers_of_a_side_stream_call_are_its_own(dev):
                 assert torch.equal(got[key].view(torch.uint8), v.view(torch.uint8)), key
             assert all(bool((x == 85).all()) for x in after)
             del after
+
+
+@pytest.mark.parametrize("d,k", [(5, 2), (7, 1)])
+def test_autotune_times_class_launches(dev, d, k):
+    """The launch variants are variants of the class launches: tuning on a batch that decodes in one launch (5 to 20
+    times as fast here) times the class launches all the same, whose launches alone, timed one by one, take at most four
+    times as long as the decode that overlaps them."""
+    import torch
+    import paper_2402_04834_amd as bbp
+    _, syn = workload.make_batch(d, 0.1, 2, workload="test", p_index=180 + d)
+    s = torch.from_numpy(syn).to(dev)
+    opts = bbp.default_opts(block=k, chi=32, fixed_iters=1)
+    try:
+        for _ in range(2):
+            tm = bbp.decode_device(d, 0.1, s, opts, timing=True)["timing"]
+        best = bbp.autotune(d, 0.1, s, opts)
+        _say(f"[autotune] d={d} k={k}: launches {tm.update_ms + tm.bethe_ms + tm.other_ms:.3f} ms, tuned {best.ms:.3f} ms")
+        assert best.ms > 0.25 * (tm.update_ms + tm.bethe_ms + tm.other_ms)
+    finally:
+        bbp.set_tuning(d, opts, 0, 1)
