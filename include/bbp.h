@@ -369,6 +369,13 @@ int bbp_warm_decode(int32_t d, double p, const double* p_dev, const uint8_t* syn
 int bbp_reference_update_host(int32_t d, double p, const bbp_opts* opts, const uint8_t* labels, int32_t msg_id,
                               const double* msgs, double* out, double* logscale);
 
+/* Validation hook: how the kernels of bbp_decode_groups are launched for these groups without `timing` (results do
+ * not depend on it): 0 a launch per sweep class and colour round, the route that the launch tuning applies to; 1 one
+ * launch per round; 2 one workgroup per coset job runs everything; 3 the same for blocks of at most 2x2. Only the
+ * groups' d, chi, batch and noise are read. Used by the GPU tests to state which kernels they compare. Errors as
+ * bbp_workspace_size_groups, BBP_EUNSUPPORTED, BBP_EHIP. */
+int bbp_launch_route(const bbp_group* groups, int32_t ngroups, const bbp_opts* opts, int32_t* route);
+
 #ifdef __cplusplus
 }
 #endif

@@ -15,7 +15,7 @@ from ._lib import BbpError, bbp_group, bbp_opts, bbp_plan_info, bbp_timing, bbp_
 
 __all__ = ["default_opts", "plan_query", "build_network", "workspace_size", "decode_device", "decode_groups",
            "decode_device_noalloc", "noalloc_max_batch",
-           "autotune", "set_tuning", "blockbp_decode", "reference_update_host", "BbpError", "bbp_opts",
+           "autotune", "set_tuning", "blockbp_decode", "reference_update_host", "launch_route", "BbpError", "bbp_opts",
            "bbp_timing", "bbp_tuning"]
 
 
@@ -330,3 +330,14 @@ def reference_update_host(d: int, p: float, opts: bbp_opts, labels, msg_id: int,
     _lib.check(_lib.lib().bbp_reference_update_host(d, p, C.byref(opts), labels.ctypes.data, msg_id,
                                                     msgs.ctypes.data, out.ctypes.data, C.byref(ls)))
     return out, ls.value
+
+
+def launch_route(shapes, opts: bbp_opts) -> int:
+    """Validation hook of the C ABI: the launch route (0 class launches, 1 rounds, 2 and 3 a workgroup per job) of a
+    decode of groups (d, batch) of depolarizing noise without timing."""
+    gs = (bbp_group * len(shapes))()
+    for g, (d, batch) in zip(gs, shapes):
+        g.d, g.batch, g.p = d, batch, 0.1
+    route = C.c_int32()
+    _lib.check(_lib.lib().bbp_launch_route(gs, len(shapes), C.byref(opts), C.byref(route)))
+    return route.value

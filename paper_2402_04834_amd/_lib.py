@@ -107,6 +107,7 @@ SIGNATURES = {
                                      C.c_void_p, C.c_void_p, C.c_void_p]),
     "bbp_reference_update_host": (C.c_int, [C.c_int32, C.c_double, C.POINTER(bbp_opts), C.c_void_p, C.c_int32,
                                             C.c_void_p, C.c_void_p, C.POINTER(C.c_double)]),
+    "bbp_launch_route": (C.c_int, [C.POINTER(bbp_group), C.c_int32, C.POINTER(bbp_opts), C.POINTER(C.c_int32)]),
     "bbp_bmps_workspace_size": (C.c_int, [C.c_int32, C.c_int64, C.c_int32, C.POINTER(C.c_size_t)]),
     "bbp_bmps_decode_device": (C.c_int, [C.c_int32, C.c_double, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int64,
                                          C.c_int32, C.c_void_p, C.c_size_t, C.c_void_p, C.c_void_p, C.c_void_p,

@@ -1723,4 +1723,14 @@ int bbp_reference_update_host(int32_t d, double p, const bbp_opts* opts, const u
   return bbp::host_sweep(P, *found, labels, pi, msgs, out, logscale);
 }
 
+int bbp_launch_route(const bbp_group* groups, int32_t ngroups, const bbp_opts* opts, int32_t* route) {
+  if (!route) return fail(BBP_EINVAL, "route is NULL");
+  std::vector<GroupRun> gr;
+  size_t total = 0;
+  const int rc = resolve(groups, ngroups, opts, gr, &total, true);
+  if (rc) return rc;
+  *route = (int)choose_route(gr, opts);
+  return BBP_OK;
+}
+
 }  // extern "C"

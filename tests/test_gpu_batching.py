@@ -379,3 +379,84 @@ def test_autotune_times_class_launches(dev, d, k):
         assert best.ms > 0.25 * (tm.update_ms + tm.bethe_ms + tm.other_ms)
     finally:
         bbp.set_tuning(d, opts, 0, 1)
+
+
+# batches beyond the smaller routes' reach; packed widths (blocks 3 to 5) with a last job block that is partly filled
+CLASS_BATCHES = [(5, 3, 2501, 0), (5, 4, 3501, 1), (6, 5, 2501, 0), (9, 6, 1501, 1)]
+
+
+@pytest.mark.parametrize("d,k,b,precision", CLASS_BATCHES)
+def test_launch_variants_of_class_launches(dev, d, k, b, precision):
+    """Decodes by class launches, item order sweep-major and job-major, on 1, 2 and 4 streams, eager and as a graph
+    replayed with other work between, equal the first variant's bitwise, and its first syndromes decoded by themselves."""
+    import torch
+    import paper_2402_04834_amd as bbp
+    p = 0.10
+    opts = bbp.default_opts(block=k, chi=32, max_iter=6, precision=precision)
+    graph = bbp.default_opts(block=k, chi=32, max_iter=6, precision=precision, graph=1)
+    assert bbp.launch_route([(d, b)], opts) == 0 and bbp.launch_route([(d, b)], graph) == 0
+    _, syn = workload.make_batch(d, p, b, workload="mixed", p_index=130 + d)
+    s = torch.from_numpy(syn).to(dev)
+    st = torch.cuda.Stream(dev)
+    ws = torch.empty(bbp.workspace_size(d, b, opts), dtype=torch.uint8, device=dev)
+    ref, out = None, None
+    try:
+        for order in (0, 1):
+            for streams in (1, 2, 4):
+                _say(f"[class variants] d={d} k={k} batch {b} order={order} streams={streams}")
+                bbp.set_tuning(d, opts, order, streams)
+                got = _alone(dev, d, p, syn, opts)
+                ref = got if ref is None else ref
+                _same(got, ref, f"order {order} streams {streams}")
+                for replay in range(3 if streams > 1 else 0):
+                    out = bbp.decode_device(d, p, s, graph, workspace=ws, stream=st, out=out)
+                    st.synchronize()
+                    _same(_np(out), ref, f"graph {replay}, order {order} streams {streams}")
+                    for key in KEYS:
+                        out[key].zero_()
+                    torch.cuda.synchronize()
+    finally:
+        bbp.set_tuning(d, opts, 0, 1)
+    few = _alone(dev, d, p, syn[:3], opts)
+    _same(few, {key: ref[key][:3] for key in KEYS}, "first syndromes")
+
+
+def test_concurrent_multistream_class_launches(dev):
+    """Two host threads whose decodes spread class launches over the device's auxiliary streams, eagerly and through
+    captured graphs, each on its own stream: every result is bitwise the single-stream decode's."""
+    import threading
+    import torch
+    import paper_2402_04834_amd as bbp
+    d, p, b = 9, 0.10, 1501
+    opts, gopts = (bbp.default_opts(block=6, chi=32, max_iter=6, graph=g) for g in (0, 1))
+    assert bbp.launch_route([(d, b)], opts) == 0 and bbp.launch_route([(d, b)], gopts) == 0
+    syn = [torch.from_numpy(workload.make_batch(d, p, b, workload="mixed", p_index=140 + k)[1]).to(dev) for k in range(2)]
+    bbp.set_tuning(d, opts, 0, 1)
+    ref = [_np(bbp.decode_device(d, p, s, opts)) for s in syn]
+    bbp.set_tuning(d, opts, 1, 4)
+    errors, done = [], [0, 0]
+
+    def worker(k):
+        try:
+            st = torch.cuda.Stream(dev)
+            ws = torch.empty(bbp.workspace_size(d, b, opts), dtype=torch.uint8, device=dev)
+            out = None
+            for rep in range(6):
+                out = bbp.decode_device(d, p, syn[k], gopts if rep % 2 else opts, workspace=ws, stream=st, out=out)
+                st.synchronize()
+                _same(_np(out), ref[k], f"thread {k} decode {rep}")
+                done[k] += 1
+        except BaseException as e:   # reported by the main thread
+            errors.append(e)
+
+    _say("[concurrent class launches] two threads, 4-stream variant, eager and graph")
+    try:
+        th = [threading.Thread(target=worker, args=(k,)) for k in range(2)]
+        for t in th:
+            t.start()
+        for t in th:
+            t.join()
+        assert not errors, errors
+        assert done == [6, 6]
+    finally:
+        bbp.set_tuning(d, opts, 0, 1)

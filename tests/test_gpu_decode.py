@@ -527,3 +527,26 @@ def test_allocation_free_decode_equals_decode(dev, d, k, b):
     torch.cuda.synchronize()
     for key in ("loglik", "delta", "iters", "coset", "correction"):
         assert torch.equal(one[key].view(torch.uint8), ref[key].view(torch.uint8)), key
+
+
+@pytest.mark.parametrize("d,rows,cols,b,precision,route", [
+    (10, 6, 6, 40, 0, 2), (13, 6, 6, 64, 1, 2),                 # 16 wavefronts of one-position sweeps: 66,048 bytes of LDS
+    (8, 3, 6, 4, 1, 1), (8, 3, 6, 64, 1, 2), (8, 6, 3, 2, 0, 1), (8, 6, 3, 64, 0, 2), (5, 1, 4, 3, 0, 1), (5, 1, 4, 30, 0, 2),
+    (8, 3, 5, 2, 0, 2), (8, 5, 3, 70, 1, 2), (8, 4, 3, 5, 0, 2), (5, 3, 1, 6, 0, 1), (8, 1, 5, 2, 1, 1), (8, 1, 5, 60, 1, 2),
+    (17, 3, 6, 1, 0, 1),
+])
+def test_fused_routes_of_rectangular_blocks(dev, d, rows, cols, b, precision, route):
+    """Blocks whose height and width are a block and a remainder size of the fused kernels, and the largest workgroups:
+    bitwise the class launches' results."""
+    import torch
+    import paper_2402_04834_amd as bbp
+    opts = bbp.default_opts(block=(rows, cols), chi=32, precision=precision)
+    taken = bbp.launch_route([(d, b)], opts)
+    _say(f"[fused rectangular] d={d} {rows}x{cols} batch {b} precision {precision}: route {taken}")
+    assert taken == route
+    _, syn = workload.make_batch(d, 0.12, b, workload="test", p_index=900 + 10 * d + rows)
+    s = torch.from_numpy(syn).to(dev)
+    small, _, _ = bbp.decode_groups([(d, 0.1, s)], opts, messages=True)
+    classes, _, _ = bbp.decode_groups([(d, 0.1, s)], opts, messages=True, timing=True)
+    for key in ("loglik", "delta", "iters", "coset", "correction", "messages"):
+        assert torch.equal(small[0][key].view(torch.uint8), classes[0][key].view(torch.uint8)), key
