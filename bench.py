@@ -341,10 +341,11 @@ def main():
                                 other=r["other_ms"] / a.steps),
         mean_iterations_per_coset=r["out"]["iters"].double().mean().item(),
         launch_tuning=dict(order=("sweep-major", "job-major")[tune.order], timed_streams=tune.streams,
-                           timed_as=("eager launches" if r["events_in_timed"] else "one HIP graph per step"),
+                           timed_as=("eager launches" if tune.streams == 1 else "one HIP graph per step"),
+                           route=r["route"],
                            tuning_decode_ms=tune.ms,
                            roofline_measured_on=("the timed decodes" if r["events_in_timed"] else
-                                                 f"{a.steps} separate single-stream decodes")),
+                                                 f"{a.steps} separate single-stream decodes by class launches")),
         plan=dict(messages_per_coset=r["info"].num_messages, exact_sweeps=bool(r["info"].exact_sweeps),
                   max_cut_rank=r["info"].max_cut_rank),
         agreement=agreement(r["out"], a.batch, errors, d) if block == 6 else None,
@@ -365,8 +366,8 @@ def main():
 
 def d17_leg(a, d, p, block, chi, max_iter, syn_dev, precision):
     """Autotune, warm up and time a.steps decodes of the d17 batch at `precision`; kernel rates from HIP events
-    (in the timed decodes when the tuned variant is one stream, else from as many single-stream decodes after
-    the timed region)."""
+    (in the timed decodes when those run by class launches on one stream, else from as many single-stream decodes
+    by class launches after the timed region)."""
     import torch
 
     import paper_2402_04834_amd as bbp
@@ -379,17 +380,19 @@ def d17_leg(a, d, p, block, chi, max_iter, syn_dev, precision):
     # The library's autotuner picks the launch variant for (d, blocks, chi) on this batch (untimed set-up), and
     # the timed steps run that variant. Per-kernel rates need every launch timed alone, so the roofline
     # figure comes from separate single-stream decodes with HIP events after the timed region (with
-    # --no-autotune, or when the tuned variant is single-stream, the timed decodes carry the events).
+    # --no-autotune, or when the tuned variant is single-stream, the timed decodes carry the events). Events
+    # make a decode take the class launches, so a batch that decodes in fewer launches is timed without.
     if a.no_autotune:   # profiling runs: only the timed single-stream decodes, job-major items
         tune = bbp.bbp_tuning(1, 1, 0.0)
     else:
         tune = bbp.autotune(d, p, syn_dev, opts, workspace=ws)
     bbp.set_tuning(d, opts, tune.order, tune.streams)
-    events_in_timed = tune.streams == 1
+    route = bbp.launch_route([(d, a.batch)], opts)
+    events_in_timed = tune.streams == 1 and route == 0
     # With the tuned multi-stream variant the timed steps replay the decode as one HIP graph (captured by the
     # library on the first call, on a stream of its own): no host work per launch.
     timed_opts, timed_stream = opts, None
-    if not events_in_timed:
+    if tune.streams > 1:
         timed_opts = bbp.default_opts(block=block, chi=chi, max_iter=max_iter, delta0=1e-4, delta1=1e-2,
                                       damping=0.1, precision=precision, graph=1)
         timed_stream = torch.cuda.Stream()
@@ -398,7 +401,8 @@ def d17_leg(a, d, p, block, chi, max_iter, syn_dev, precision):
         out = bbp.decode_device(d, p, syn_dev, timed_opts, workspace=ws, stream=timed_stream, out=out)
     torch.cuda.synchronize()
     r = dict(upd_ms=0.0, upd_flops=0.0, bethe_ms=0.0, other_ms=0.0, launches=0, top={}, tune=tune, info=info,
-             events_in_timed=events_in_timed)
+             events_in_timed=events_in_timed,
+             route=("class launches", "one launch per round", "one workgroup per job", "one workgroup per job")[route])
 
     def account(tm):
         r["upd_ms"] += tm.update_ms

@@ -550,3 +550,35 @@ def test_fused_routes_of_rectangular_blocks(dev, d, rows, cols, b, precision, ro
     classes, _, _ = bbp.decode_groups([(d, 0.1, s)], opts, messages=True, timing=True)
     for key in ("loglik", "delta", "iters", "coset", "correction", "messages"):
         assert torch.equal(small[0][key].view(torch.uint8), classes[0][key].view(torch.uint8)), key
+
+
+@pytest.mark.parametrize("k,b", [(2, 64), (6, 4)])
+def test_benchmark_times_the_decode_that_a_caller_gets(dev, k, b):
+    """Asking for timing makes a decode take the class launches, several times as slow for a small batch: the benchmark's
+    timed steps of such a batch are decodes without it, at most twice as long as ones timed here."""
+    import argparse
+    import time
+    import torch
+    import bench
+    import paper_2402_04834_amd as bbp
+    _, syn = workload.make_batch(17, 0.1, b, workload="d17")
+    s = torch.from_numpy(np.ascontiguousarray(syn)).to(dev)
+    opts = bbp.default_opts(block=k, chi=32, precision=0)
+    assert bbp.launch_route([(17, b)], opts) != 0
+    args = argparse.Namespace(batch=b, steps=5, warmup=2, no_autotune=True)
+    try:
+        leg = bench.d17_leg(args, 17, 0.1, k, 32, 20, s, 0)
+    finally:
+        bbp.set_tuning(17, opts, 0, 1)
+    out = bbp.decode_device(17, 0.1, s, opts)
+    times = []
+    for _ in range(5):
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        out = bbp.decode_device(17, 0.1, s, opts, workspace=out["workspace"], out=out)
+        torch.cuda.synchronize()
+        times.append(time.perf_counter() - t0)
+    _say(f"[bench leg] k={k} batch {b}: {1e3 * leg['elapsed'] / 5:.3f} ms a step, {1e3 * min(times):.3f} ms a decode")
+    assert leg["elapsed"] / 5 < 2 * max(times)
+    assert leg["upd_ms"] > 0 and not leg["events_in_timed"]
+    assert torch.equal(leg["out"]["coset"], out["coset"])
