@@ -64,13 +64,12 @@ constexpr int POOL = std::max(std::max(P1, P2), std::max(PC, PE));
 __device__ __forceinline__ int bitrev(int w, int K) { return (int)(__brev((unsigned)w) >> (32 - K)); }
 
 // Entry e = up*8 + in*4 + down*2 + out of the frame table at sweep step t, position i, in FP64: checks are
-// COPY tensors (0 / 1), qubits one of the four Pauli probabilities pq (by code x + 2z).
+// COPY tensors (0 / 1), qubits one of the four Pauli probabilities pq (indexed x * 2 + z, as site_entry's).
 __device__ __forceinline__ double tab(const SweepDesc& s, int L, const uint8_t* lab, const double* pq, int t, int i,
                                       int e) {
   int r, c;
   frame_site(s.frame, s.r0, s.c0, s.kr, s.kc, t, i, r, c);
-  // (site_entry's noise arguments are I, Z, X, Y: each marks its place in pq)
-  const float m = site_entry(s.frame, L, r, c, lab[r * L + c], 1.0f, 3.0f, 2.0f, 4.0f, e);
+  const float m = site_entry(s.frame, L, r, c, lab[r * L + c], 1.0f, 2.0f, 3.0f, 4.0f, e);
   if ((r + c) & 1) return (double)m;
   const int k = (int)m;
   return k == 0 ? 0.0 : pq[k - 1];
@@ -180,7 +179,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void tr
     pq[0] = 1.0 - pj;
     pq[1] = pq[2] = pq[3] = pj / 3.0;
   } else {
-    for (int k = 0; k < 4; ++k) pq[k] = G.pq[k];
+    for (int k = 0; k < 4; ++k) pq[k] = G.pq[(k & 1) << 1 | k >> 1];   // (from the order of codes x + 2z)
   }
   const float* mbase = G.msgs + job * G.M * (int64_t)ms;
   double* ws = a.tws + (int64_t)blockIdx.x * W_SLOT;
