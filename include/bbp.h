@@ -109,7 +109,8 @@ typedef struct bbp_plan_info {
   double flops_bethe;
   int32_t truncating_sweeps;     /* sweeps (BP rounds and closing) that run in the truncating kernel: those whose
                                     boundary MPS can exceed chi, and every sweep of a plan with blocks wider than
-                                    6; their flops count QR, reflection and SVD work (see below) */
+                                    6; their flops are a nominal count of QR, reflection and SVD work at padded
+                                    bonds, more than is executed */
   int32_t message_stride;        /* S: floats per stored dense message, 2^max(6, widest block); the message
                                     arrays of bbp_decode_device and bbp_group are [batch][4][M][S] */
 } bbp_plan_info;

@@ -301,14 +301,15 @@ double sweep_flops(const Plan& p, const SweepDesc& s) {
   return f;
 }
 
-// Algorithmic flops of one sweep in the truncating kernel (bonds padded to 2 chi_max = 32 before the
-// compression, as the kernel executes them): per column, every crossing site and the top cap is factored by
+// Nominal flops of one sweep in the truncating kernels, at padded sizes (every bond 16, 32 before the compression): what
+// launches are ordered by. The kernels carry the number of values kept at each bond and leave out what is zero beyond it,
+// so this is no count of what they execute. Per column, every crossing site and the top cap is factored by
 // Householder QR of a 64 x 32 matrix (2 m n^2 - 2 n^3 / 3), the reflections are applied to the 32 x 16 carry
 // (4 (64 - j) 16 per reflection j), and every site below the top cap takes one-sided Jacobi SVD of a 32 x 32
 // matrix, counted at six sweeps of 496 rotations (a 2 x 32 product and a 4 x 32 rotation each); the absorption
-// products (R times the column tensor) add 2 x 32 x 32 x 64 per site. Narrow sweeps (trunc_shape.hpp) execute
-// the nonzero blocks only: QR of 32 x 16, reflections on the carry's 32 x 8 block, 120 rotations of 16-entry
-// rows per Jacobi sweep, absorption into 32 x 16 from 16 terms.
+// products (R times the column tensor) add 2 x 32 x 32 x 64 per site. Narrow sweeps (trunc_shape.hpp) count the blocks
+// that can be nonzero: QR of 32 x 16, reflections on the carry's 32 x 8 block, 120 rotations of 16-entry rows per
+// Jacobi sweep, absorption into 32 x 16 from 16 terms.
 double trunc_sweep_flops(const SweepDesc& s, int chi) {
   double qr, apply = 0.0, svd, absorb;
   if (trunc_narrow(chi, s.kt, s.kp)) {

@@ -1,5 +1,6 @@
-// sweep_launch.hpp -- host interface of the block-sweep kernels. The kernels are instantiated per sweep
-// length (1..6 steps) in separate translation units (sweep_kernel.hip compiled with BBP_KT = 1..6).
+// sweep_launch.hpp -- host interface of the block-sweep kernels. The kernels are instantiated per sweep length and
+// number of positions across (1..6 each) in separate translation units (sweep_kernel.hip compiled with BBP_KT and
+// BBP_KP), the fused ones per block size, remainder and precision (fused_sweep.hip).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>

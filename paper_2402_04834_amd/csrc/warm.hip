@@ -240,8 +240,8 @@ typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
 // offset lies past the buffer for taps that leave the grid (reads zeros, no branch); the buffer starts at the
 // tile's first neighbour row, so offsets stay below 2^31 whatever the batch. The weights are the MFMA's first operand:
 // a lane ends with four consecutive output channels of a row, one 16-byte store.
-// Measured at d = 17, 16 syndromes (69,696 rows): 128 -> 96 forward 200 us (77 TFLOP/s, half of the FP32 matrix rate),
-// its data gradient 185 us, 128 -> 64 data gradient 133 us, 64 -> 128 forward 128 us. The 64 x 64 tiles with 4-byte
+// Measured at d = 17, 16 syndromes (69,696 rows): 128 -> 96 forward 195 us (79 TFLOP/s, half of the FP32 matrix rate),
+// its data gradient 183 us, 128 -> 64 data gradient 133 us, 64 -> 128 forward 128 us. The 64 x 64 tiles with 4-byte
 // gathers and 64-bit index divisions per element before took 542, about 620, 345 and 265 us.
 template <int MODE, int CS, int NT, int EPI>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void conv_f32(
@@ -390,7 +390,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void c
 // tiles, 16-row stages and two LDS buffers. The LDS tiles keep the activations' layout [row][channel]: MFMA
 // operands are 4-byte reads of 16 consecutive channels at 4 rows, a row stride of 16 modulo 64 floats putting the 64
 // lanes on distinct banks. The partials replace atomic adds of every split into the one gradient. Measured at d = 17,
-// 16 syndromes: 170 us (1152 x 96), 129 us (576 x 128) and 32 us (99 x 64), the reductions 8 us each; before, 399 us on
+// 16 syndromes: 160 us (1152 x 96), 123 us (576 x 128) and 31 us (99 x 64), the reductions 7 us each; before, 399 us on
 // average and 98 us for each bias gradient.
 template <int CIN, int NT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void conv_dw(

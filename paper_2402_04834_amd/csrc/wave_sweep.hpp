@@ -744,7 +744,8 @@ __device__ __forceinline__ void column_multi(const V (&X)[Cap<TOP, KT, T>::PO * 
 
 // --------------------------------------------------------------------------------- column, kp == 1
 // Rounding order (mul2) of the transforms of a one-position sweep: step T, emitted top bond y, emitted bottom bond
-// vb, bottom cap index s.
+// vb, bottom cap index s. Neither order is more accurate: a case keeps the one that its results, and those recorded from
+// it, were first computed with.
 template <int KT, bool TOP, bool BOT, bool Q00, bool BIASED>
 struct SingleOrder {
   static constexpr bool swapped(int T, int y, int vb, int s) {
